@@ -24,12 +24,12 @@
 // staged as zeros (the rest-equilibrium far field; the plate's wall
 // half-spaces), so a population crossing the moving wall, the body or the
 // stationary far wall arrives as zero; the lane of a cell within R of a wall
-// then adds the bounce-back value f_opp(x_p) + 2 w_i rho0 (v_i.U_w)/theta
-// (moving wall only), x_p the half-way mirror cell of the link (the rules of
-// the population kernel), read from the step's input state; at a plate or a
-// box face with the diffuse or the Maxwell wall it adds the diffuse emission
-// (eq. DS) of the link's wall column, mixed with the specular image for the
-// Maxwell wall.  The finalize kernel sums the momentum exchange from the same
+// then adds the moments of the bounce-back values f_opp(x_p) + 2 w_i rho0
+// (v_i.U_w)/theta (moving wall only), x_p the half-way mirror cell of the link
+// (the rules of the population kernel), read from the step's input state; at a
+// plate or a box face with the diffuse or the Maxwell wall those of the
+// diffuse emission (eq. DS) of the link's wall column, mixed with the specular
+// image for the Maxwell wall.  The finalize kernel sums the momentum exchange from the same
 // input state.
 #include <hip/hip_runtime.h>
 
@@ -162,152 +162,241 @@ constexpr bool source_used(int vx, int iy) {
   return false;
 }
 
-// Bounce-back contributions of the wall links of fluid cell (x, y): each link
-// population arrived as zero from the stream; add f_opp(x_p) (+ the
-// moving-wall term) and its moments.  Every cell a link reads (the mirror
-// cell x_p, the diffuse wall's specular source and its crossing rows) lies
-// within R - 1 cells of (x, y) along each axis, so inside the staged tile:
-// the reads come from LDS (C, staged region starting at cell (ox, oy), rows
-// of HW cells), not from global memory.
+// Weight of the velocities with components (+-a, +-b), as an orbit index, or
+// -1: the lattice's weights by |vx| and |vy|.
+template <class L>
+struct WeightMap {
+  int8_t orbit[4][4];
+  constexpr WeightMap() : orbit() {
+    for (int a = 0; a < 4; ++a)
+      for (int b = 0; b < 4; ++b) {
+        const int q = a <= L::R && b <= L::R ? find_q<L>(a, b) : -1;
+        orbit[a][b] = (int8_t)(q >= 0 ? L::orbit[q] : -1);
+      }
+  }
+};
+template <class L>
+__device__ constexpr WeightMap<L> kWeightMap{};
+
+// The weights by |vx| and |vy| (zero where the lattice has no such velocity),
+// in the storage precision and, for the diffuse wall, in FP64; in LDS, so that
+// the lanes of a wavefront can look up different ones.
+template <typename S, bool DSW>
+struct WallTable {
+  S w[4][4];
+  double wd[DSW ? 4 : 1][4];
+};
+
 template <class L, typename S, bool DSW>
-__device__ __forceinline__ Mom<S> add_links(Mom<S> m, const SolveDesc& d, const Pair<S>* C,
-                                            int HW, int ox, int oy, int x, int y, S ladd,
-                                            double U, const KernelLattice& lat,
-                                            const CoefConst<S>& cc) {
-  const lptr<const Pair<S>> T = (lptr<const Pair<S>>)C;
-  // coefficient k (a0, bx, by, cxx, cxy, cyy) of the cell at (cx, cy)
-  auto coef = [&](int cx, int cy, int k) __attribute__((always_inline)) -> S {
-    const Pair<S> p = T[(3 * (cy - oy) + (k >> 1)) * HW + (cx - ox)];
-    return (k & 1) ? p.y : p.x;
-  };
-  const bool is_box = d.geom == GEOM_BOX;
-  // diffuse wall: deviation of the mass crossing the wall in column x, from
-  // the coefficients of rows 0 .. R-1 (population q at row r crosses when
-  // r < -v_qy)
-  double cm = 0.0;
-  // box with diffuse or Maxwell faces: the face and column of this arrival
-  // cell; the column's crossing mass is linear in the coefficients of its R
-  // cells (weights from the host), each within R - 1 cells of this one
-  int face = -1, col = 0;
-  if (DSW && d.wall == WALL_DS && is_box) {
-    face = box_face<L::R>(d, x, y);
-    if (face >= 0) {
-      col = box_column(d, face, x, y);
-      const WallCol& wc = d.wcols[col];
-      static_for<0, L::R>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;  // the cell k + 1 cells from the face
-        const int cx = face == 2 ? d.bx0 - 1 - k : (face == 3 ? d.bx1 + k : x);
-        const int cy = face == 0 ? d.by0 - 1 - k : (face == 1 ? d.by1 + k : y);
-#pragma unroll
-        for (int j = 0; j < 6; ++j) cm += wc.mc[k][j] * (double)coef(cx, cy, j);
-      });
-    }
-  }
-  if (DSW && d.wall == WALL_DS && d.geom == GEOM_PLATE && y < L::R) {
-    static_for<0, L::R>([&](auto rc) __attribute__((always_inline)) {
-      constexpr int r = decltype(rc)::value;
-      const double c0 = coef(x, r, 0), c1 = coef(x, r, 1), c2 = coef(x, r, 2),
-                   c3 = coef(x, r, 3), c4 = coef(x, r, 4), c5 = coef(x, r, 5);
-      static_for<0, L::Q>([&](auto qc) __attribute__((always_inline)) {
-        constexpr int q = decltype(qc)::value;
-        constexpr int vx = L::vx[q], vy = L::vy[q];
-        if constexpr (vy < -r)
-          cm += lat.w[L::orbit[q]] *
-                (c0 + vx * c1 + vy * c2 + vx * vx * c3 + vx * vy * c4 + vy * vy * c5);
-      });
-    });
-  }
-  static_for<0, L::Q>([&](auto qc) __attribute__((always_inline)) {
-    constexpr int q = decltype(qc)::value;
-    constexpr int vx = L::vx[q], vy = L::vy[q];
-    const int sx = x - vx, sy = y - vy;
-    int px = -1, py = -1;
-    bool moving = false, diffuse = false;
-    if (is_box) {
-      if (sx >= d.bx0 && sx < d.bx1 && sy >= d.by0 && sy < d.by1) {
-        px = x < d.bx0 ? 2 * d.bx0 - 1 - sx : (x >= d.bx1 ? 2 * d.bx1 - 1 - sx : x);
-        py = y < d.by0 ? 2 * d.by0 - 1 - sy : (y >= d.by1 ? 2 * d.by1 - 1 - sy : y);
-        moving = true;
-        diffuse = DSW && face >= 0;  // corner links keep bounce-back
-      }
-    } else if (d.geom == GEOM_PLATE) {
-      if constexpr (vy > 0) {
-        if (sy < 0) {
-          px = x;
-          py = -1 - sy;
-          moving = true;
-          diffuse = DSW && d.wall == WALL_DS;
-        }
-      }
-      if constexpr (vy < 0) {
-        if (sy >= d.ny && d.far == FAR_WALL) {
-          px = x;
-          py = 2 * d.ny - 1 - sy;
-        }
-      }
-    }
-    if (py >= 0) {
-      constexpr int o = L::orbit[q];
-      const S wq = cc.w[o];
-      S f;
-      if (DSW && diffuse) {
-        const double wd = lat.w[L::orbit[q]];
-        double e = is_box ? ds_box_arrival(d.wcols[col], d.rho0, U, cm, wd, double(vx), lat.theta)
-                          : ds_arrival<vx>(d, U, cm, wd, lat.theta);
-        if (d.sigma != 1.0) {
-          double p;
-          if (!is_box || face <= 1) {
-            // specular share: the population of (vx, -vy) that crossed the
-            // wall or face from column x - vx at the mirror row (the staged
-            // halo holds the periodic image of a wrapped column)
-            const int sxw = x - vx;
-            p = coef(sxw, py, 0);
-            if constexpr (vx != 0)
-              p += double(vx) * coef(sxw, py, 1) + double(vx * vx) * coef(sxw, py, 3);
-            if constexpr (vy != 0)
-              p += double(-vy) * coef(sxw, py, 2) + double(vy * vy) * coef(sxw, py, 5);
-            if constexpr (vx * vy != 0) p += double(-vx * vy) * coef(sxw, py, 4);
-            p *= wd;
-          } else {
-            // a face normal to the motion: the population of (-vx, vy) that
-            // crossed it from row y - vy at the mirror column, plus the
-            // moving-wall term of the face moving along its normal
-            const int syw = y - vy;
-            p = coef(px, syw, 0);
-            if constexpr (vx != 0)
-              p += double(-vx) * coef(px, syw, 1) + double(vx * vx) * coef(px, syw, 3);
-            if constexpr (vy != 0)
-              p += double(vy) * coef(px, syw, 2) + double(vy * vy) * coef(px, syw, 5);
-            if constexpr (vx * vy != 0) p += double(-vx * vy) * coef(px, syw, 4);
-            p = wd * p + wd * double(vx) * d.ladd_scale * U;
-          }
-          e = d.sigma * e + (1.0 - d.sigma) * p;
-        }
-        f = (S)e;
-      } else {
-        // population of -v at the mirror cell
-        S p = coef(px, py, 0);
-        if constexpr (vx != 0) p += S(-vx) * coef(px, py, 1) + S(vx * vx) * coef(px, py, 3);
-        if constexpr (vy != 0) p += S(-vy) * coef(px, py, 2) + S(vy * vy) * coef(px, py, 5);
-        if constexpr (vx * vy != 0) p += S(vx * vy) * coef(px, py, 4);
-        f = wq * p;
-        if constexpr (vx != 0) {
-          constexpr int a = vx < 0 ? -vx : vx;
-          const S wa = a == 1 ? wq : cc.wx[o][a];
-          if (moving) f = fmadd(vx < 0 ? -wa : wa, ladd, f);
-        }
-      }
-      m.v[0] += f;
-      if constexpr (vx != 0) m.v[1] += S(vx) * f;
-      if constexpr (vy != 0) m.v[2] += S(vy) * f;
-      if constexpr (vx != 0) m.v[3] += S(vx * vx) * f;
-      if constexpr (vx * vy != 0) m.v[4] += S(vx * vy) * f;
-      if constexpr (vy != 0) m.v[5] += S(vy * vy) * f;
-    }
-  });
-  return m;
+__device__ __forceinline__ void fill_wall_table(WallTable<S, DSW>& t, const KernelLattice& lat,
+                                                int i) {
+  const int o = kWeightMap<L>.orbit[i >> 2][i & 3];
+  const double w = o < 0 ? 0.0 : lat.w[o];
+  t.w[i >> 2][i & 3] = (S)w;
+  if constexpr (DSW) t.wd[i >> 2][i & 3] = w;
 }
 
+// Moments of the arrivals from the walls at fluid cell (x, y): each link
+// population arrived as zero from the stream.  A wall or box face with normal
+// axis n is a set of links per distance: at the k-th cell from the face
+// (k = 0..R-1), the arrivals with normal speed |v_n| = k + 1 + r come from the
+// one mirror cell r cells from the face (0 <= r < R - k), whatever their
+// tangential velocity t.  So the links of a cell are summed per mirror cell:
+// every arrival is w (G + t H + t^2 K) with G, H, K from the mirror cell's
+// coefficients (bounce-back, f_opp(x_p) + the moving-wall term) or from the
+// wall's emission (diffuse), and its moments need only S_b = sum w t^b,
+// b = 0..4, over the tangential velocities whose source lies behind the wall
+// (all of them, except near a box corner).  Cells outside the body on both
+// axes have corner links, one mirror cell each (always bounce-back).
+//
+// The loops over mirror cells are kept rolled.  A tile with wall cells runs
+// this code once per launch from a cold instruction cache: as one branch per
+// velocity, unrolled for every row of a lane (20 to 150 KB of code), it took
+// 25 us (bounce-back) and 36-45 us (diffuse) of a launch however small the
+// lattice; per mirror cell (14 KB of code) a launch over a 256 x 256 box takes
+// 14.3 and 23.3 us, over a 256 x 256 plate 9.9 and 15.0 us, without walls
+// 7.8 us.
+//
+// Every cell read here (mirror cells, the specular sources and the crossing
+// rows of the diffuse wall) lies within R - 1 cells of (x, y) along each axis
+// (specular: R tangentially, inside the halo), so inside the staged tile: the
+// reads come from LDS (C, staged region starting at cell (ox, oy), rows of HW
+// cells), not from global memory.
+template <class L, typename S, bool DSW>
+__device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>* C, int HW,
+                                               int ox, int oy, int x, int y, S ladd, double U,
+                                               const WallTable<S, DSW>& tab, double theta) {
+  constexpr int R = L::R;
+  const lptr<const Pair<S>> T = (lptr<const Pair<S>>)C;
+  Mom<S> m{{S(0), S(0), S(0), S(0), S(0), S(0)}};
+  // coefficients of cell (cx, cy) by normal axis: a0, b_t, b_n, c_tt, c_nt, c_nn
+  struct Cell {
+    S a0, bt, bn, ctt, cnt, cnn;
+  };
+  auto cell = [&](int cx, int cy, bool nx_axis) __attribute__((always_inline)) -> Cell {
+    const int i = 3 * (cy - oy) * HW + (cx - ox);
+    const Pair<S> p0 = T[i], p1 = T[i + HW], p2 = T[i + 2 * HW];
+    return nx_axis ? Cell{p0.x, p1.x, p0.y, p2.y, p2.x, p1.y}
+                   : Cell{p0.x, p0.y, p1.x, p1.y, p2.x, p2.y};
+  };
+  const bool is_box = d.geom == GEOM_BOX;
+  const bool inx = !is_box || (x >= d.bx0 && x < d.bx1);
+  const bool iny = is_box && y >= d.by0 && y < d.by1;
+  // moments along the normal and the tangential axis
+  Mom<S> a{{S(0), S(0), S(0), S(0), S(0), S(0)}};  // drho, j_t, j_n, P_tt, P_nt, P_nn
+  auto add = [&](S t0, S t1, S t2, S vn) __attribute__((always_inline)) {
+    a.v[0] += t0;
+    a.v[1] += t1;
+    a.v[2] = fmadd(vn, t0, a.v[2]);
+    a.v[3] += t2;
+    a.v[4] = fmadd(vn, t1, a.v[4]);
+    a.v[5] = fmadd(vn * vn, t0, a.v[5]);
+  };
+  const bool ax = iny;  // normal along x: the faces left and right of the body
+  if (inx || iny) {
+    // a plate's cell may be in reach of both its walls
+    const int npass = d.geom == GEOM_PLATE && d.far == FAR_WALL ? 2 : 1;
+#pragma unroll 1
+    for (int pass = 0; pass < npass; ++pass) {
+      // first fluid cell along the normal, and the sign of the arrivals' v_n
+      int w0, sg;
+      if (!is_box) {
+        w0 = pass ? d.ny - 1 : 0;
+        sg = pass ? -1 : 1;
+      } else if (ax) {
+        w0 = x < d.bx0 ? d.bx0 - 1 : d.bx1;
+        sg = x < d.bx0 ? -1 : 1;
+      } else {
+        w0 = y < d.by0 ? d.by0 - 1 : d.by1;
+        sg = y < d.by0 ? -1 : 1;
+      }
+      const int k = sg * ((ax ? x : y) - w0);
+      if (k >= R) continue;
+      // tangential velocities t with a source behind the wall: tlo <= t <= thi
+      const int tlo = is_box ? (ax ? y - d.by1 : x - d.bx1) + 1 : -R;
+      const int thi = is_box ? (ax ? y - d.by0 : x - d.bx0) : R;
+      const S lad = pass ? S(0) : ladd;
+      const bool diffuse = DSW && d.wall == WALL_DS && pass == 0;
+      // diffuse emission w (ea + eb (e1 v_x + e2 v_x^2)) of the cell's column
+      double ea = 0, eb = 0, e1 = 0, e2 = 0;
+      if (diffuse) {
+        double Mr, Zu, Lu;  // mass emitted per unit density: Mr + Zu
+        if (is_box) {
+          const int face = ax ? (sg < 0 ? 2 : 3) : (sg < 0 ? 0 : 1);
+          const WallCol& wc = d.wcols[box_column(d, face, x, y)];
+          Mr = wc.Mr;
+          Zu = wc.Z1 * U + wc.Z2 * U * U;
+          Lu = wc.L1 * U;
+        } else {
+          Mr = d.ds[0];
+          Zu = d.ds[1] * U * U;
+          Lu = 0;
+        }
+        // deviation of the mass crossing the wall in this column: the
+        // bounce-back partners of all its links
+        double cm = 0;
+#pragma unroll 1
+        for (int r = 0; r < R; ++r) {
+          const int pc = w0 + sg * r;
+          const Cell c = cell(ax ? pc : x, ax ? y : pc, ax);
+#pragma unroll 1
+          for (int n = r + 1; n <= R; ++n) {
+            double s0 = 0, s1 = 0, s2 = 0;
+#pragma unroll
+            for (int t = -R; t <= R; ++t) {
+              const double w = t >= tlo && t <= thi ? tab.wd[n][t < 0 ? -t : t] : 0.0;
+              s0 += w;
+              s1 += w * t;
+              s2 += w * (t * t);
+            }
+            const double vn = sg * n;
+            cm += s0 * ((double)c.a0 - vn * (double)c.bn + vn * vn * (double)c.cnn) +
+                  s1 * (vn * (double)c.cnt - (double)c.bt) + s2 * (double)c.ctt;
+          }
+        }
+        const double z = Mr + Zu, e0 = -U * U / (2 * theta);
+        e1 = U / theta;
+        e2 = U * U / (2 * theta * theta);
+        eb = d.sigma * (d.rho0 * (Mr + Lu) + cm) / z;
+        ea = d.sigma * (d.rho0 * (Lu - Zu) + cm) / z + eb * e0;
+      }
+#pragma unroll 1
+      for (int r = 0; r < R - k; ++r) {
+        const int n = k + 1 + r;
+        const S vn = (S)(sg * n);
+        S s0 = 0, s1 = 0, s2 = 0, s3 = 0, s4 = 0;
+#pragma unroll
+        for (int t = -R; t <= R; ++t) {
+          const S w = t >= tlo && t <= thi ? tab.w[n][t < 0 ? -t : t] : S(0);
+          s0 += w;
+          s1 = fmadd(S(t), w, s1);
+          s2 = fmadd(S(t * t), w, s2);
+          s3 = fmadd(S(t * t * t), w, s3);
+          s4 = fmadd(S(t * t * t * t), w, s4);
+        }
+        const int pc = w0 + sg * r;
+        S G, H, K;
+        if (diffuse) {
+          G = (S)(ax ? ea + eb * (e1 * (sg * n) + e2 * (n * n)) : ea);
+          H = (S)(ax ? 0.0 : eb * e1);
+          K = (S)(ax ? 0.0 : eb * e2);
+        } else {
+          Cell c = cell(ax ? pc : x, ax ? y : pc, ax);
+          // the moving-wall term acts like a shift of bx by its amplitude
+          c.bn -= ax ? lad : S(0);
+          c.bt -= ax ? S(0) : lad;
+          G = fmadd(vn, fmadd(vn, c.cnn, -c.bn), c.a0);
+          H = fmadd(vn, c.cnt, -c.bt);
+          K = c.ctt;
+        }
+        add(s0 * G + s1 * H + s2 * K, s1 * G + s2 * H + s3 * K, s2 * G + s3 * H + s4 * K, vn);
+        if (DSW && diffuse && d.sigma != 1.0) {
+          // Maxwell wall: the specular share, the population of (t, -v_n) that
+          // crossed the wall from the mirror cell's neighbour t cells back
+          // (plus the moving-wall term on the faces normal to the motion)
+          const S ws = (S)(1.0 - d.sigma);
+#pragma unroll 1
+          for (int t = -R; t <= R; ++t) {
+            const S w = t >= tlo && t <= thi ? ws * tab.w[n][t < 0 ? -t : t] : S(0);
+            if (w == S(0)) continue;
+            Cell c = cell(ax ? pc : x - t, ax ? y - t : pc, ax);
+            c.bn -= ax ? lad : S(0);
+            const S ts = (S)t;
+            const S f = w * (c.a0 + ts * (c.bt + ts * c.ctt - vn * c.cnt) +
+                             vn * (vn * c.cnn - c.bn));
+            add(f, ts * f, ts * ts * f, vn);
+          }
+        }
+      }
+    }
+  } else {
+    // corner links: |v_x| >= i and |v_y| >= j, one mirror cell each
+    const bool lo_x = x < d.bx0, lo_y = y < d.by0;
+    const int i = lo_x ? d.bx0 - x : x - d.bx1 + 1, j = lo_y ? d.by0 - y : y - d.by1 + 1;
+#pragma unroll 1
+    for (int b = j; b <= R; ++b)
+#pragma unroll 1
+      for (int c0 = i; c0 <= R; ++c0) {
+        const S w = tab.w[c0][b];
+        if (w == S(0)) continue;
+        const int px = lo_x ? d.bx0 - 1 - (c0 - i) : d.bx1 + (c0 - i);
+        const int py = lo_y ? d.by0 - 1 - (b - j) : d.by1 + (b - j);
+        Cell c = cell(px, py, false);
+        c.bt -= ladd;
+        const S vx = (S)(lo_x ? -c0 : c0), vy = (S)(lo_y ? -b : b);
+        const S f = w * (c.a0 + vx * (vx * c.ctt + vy * c.cnt - c.bt) +
+                         vy * (vy * c.cnn - c.bn));
+        add(f, vx * f, vx * vx * f, vy);
+      }
+  }
+  m.v[0] = a.v[0];
+  m.v[1] = ax ? a.v[2] : a.v[1];
+  m.v[2] = ax ? a.v[1] : a.v[2];
+  m.v[3] = ax ? a.v[5] : a.v[3];
+  m.v[4] = a.v[4];
+  m.v[5] = ax ? a.v[3] : a.v[5];
+  return m;
+}
 
 }  // namespace
 
@@ -524,16 +613,44 @@ __device__ __forceinline__ void stage_load(const SolveDesc& d, const TileCtx<S>&
     for (int k = 0; k < 6; ++k) g.halo[it][k] = buf_load<S>(rs[k], oh[it]);
 }
 
-// Moments, bounce-back corrections and collision of the RB cells of this
+// The cells of a solve that may have a wall link: rows and columns within R of
+// the body or of a plate's walls (uniform values).
+template <class L>
+struct WallBand {
+  int x0 = 0, x1 = 0, y0 = 0, y1 = 0, far0;
+  __device__ __forceinline__ explicit WallBand(const SolveDesc& d) {
+    far0 = 0x7fffffff;
+    if (d.geom == GEOM_BOX) {
+      x0 = d.bx0 - L::R;
+      x1 = d.bx1 + L::R;
+      y0 = d.by0 - L::R;
+      y1 = d.by1 + L::R;
+    } else if (d.geom == GEOM_PLATE) {
+      x1 = d.nx;
+      y1 = L::R;  // moving wall below row 0
+      if (d.far == FAR_WALL) far0 = d.ny - L::R;
+    }
+  }
+  // some cell of the 64 columns from cx and the `rows` rows from cy
+  __device__ __forceinline__ bool meets(int cx, int cy, int rows) const {
+    return (cx < x1 && cx + kCoefTileW > x0 && cy < y1 && cy + rows > y0) || cy + rows > far0;
+  }
+  __device__ __forceinline__ bool has(int x, int y) const {
+    return (x >= x0 && x < x1 && y >= y0 && y < y1) || y >= far0;
+  }
+};
+
+// Moments, wall arrivals and collision of the RB cells of this
 // thread, from the staged tile in LDS (staged row r holds the pairs
 // (a0, bx), (by, cxx), (cxy, cyy) of its HW cells as three runs of HW): the
 // new coefficients of the cells in the lattice and the fluid go to res.  U:
 // the wall drive U_w of the step.
 template <class L, typename S, int RB, bool DSW>
 __device__ __forceinline__ void compute_tile(const SolveDesc& d, const TileCtx<S>& t, int tile,
-                                             const Pair<S>* C, const KernelLattice& lat,
-                                             const CoefConst<S>& cc, int tid,
-                                             S (&res)[RB][6], uint32_t& valid, double U) {
+                                             const Pair<S>* C, const WallTable<S, DSW>& tab,
+                                             const KernelLattice& lat, const CoefConst<S>& cc,
+                                             int tid, S (&res)[RB][6], uint32_t& valid,
+                                             double U) {
   using T = CoefTile<L, RB>;
   constexpr int R = T::R, HW = T::HW;
   const int nx = d.nx, ny = d.ny;
@@ -631,19 +748,23 @@ __device__ __forceinline__ void compute_tile(const SolveDesc& d, const TileCtx<S
     for (int k = 0; k < RB; ++k) row_fence(acc[k]);
   });
 
-  // wall band of the tile (uniform): rows and columns whose cells may have a link
-  int wx0 = 0, wx1 = nx, wy0 = 0, wy1 = 0;
-  if (is_box) {
-    wx0 = bx0 - R;
-    wx1 = bx1 + R;
-    wy0 = by0 - R;
-    wy1 = by1 + R;
-  } else if (d.geom == GEOM_PLATE) {
-    wy1 = R;  // moving wall below row 0
+  // wall arrivals of the cells within R of a wall (uniform per wavefront: the
+  // band of rows and columns whose cells may have a link)
+  const WallBand<L> band(d);
+  if (band.meets(x0, yb, RB)) {
+#pragma unroll 1
+    for (int k = 0; k < RB; ++k) {
+      const int y = yb + k;
+      const bool in = y < ny && x < nx && !(is_box && y >= by0 && y < by1 && x >= bx0 && x < bx1);
+      if (!(in && band.has(x, y))) continue;
+      const Mom<S> m = wall_moments<L, S, DSW>(d, C, HW, x0 - R, y0 - R, x, y,
+                                               (S)(d.ladd_scale * U), U, tab, lat.theta);
+#pragma unroll
+      for (int kk = 0; kk < RB; ++kk)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) acc[kk].v[j] += k == kk ? m.v[j] : S(0);
+    }
   }
-  const bool far_band = d.geom == GEOM_PLATE && d.far == FAR_WALL;
-  const bool wave_has_wall = (x0 < wx1 && x0 + kCoefTileW > wx0 && yb < wy1 && yb + RB > wy0) ||
-                             (far_band && yb + RB > ny - R);
 
   const S th = cc.theta;
   const S inv_th = cc.inv_theta;
@@ -658,20 +779,10 @@ __device__ __forceinline__ void compute_tile(const SolveDesc& d, const TileCtx<S
   // (a compile-time loop: unrolled whatever the size of the wall code)
   static_for<0, RB>([&](auto kc) __attribute__((always_inline)) {
     constexpr int k = decltype(kc)::value;
-    Mom<S> m = acc[k];
+    const Mom<S>& m = acc[k];
     const int y = yb + k;
     const bool in = y < ny && x < nx && !(is_box && y >= by0 && y < by1 && x >= bx0 && x < bx1);
     valid |= in ? 1u << k : 0u;
-    if (wave_has_wall) {
-      const bool near =
-          in && ((y >= wy0 && y < wy1 && x >= wx0 && x < wx1) || (far_band && y >= ny - R));
-      if (near) {
-        S ladd = (S)(d.ladd_scale * U);
-        // computed per cell in the band: keeps its products out of the common path
-        asm volatile("" : "+v"(ladd));
-        m = add_links<L, S, DSW>(m, d, C, HW, x0 - R, y0 - R, x, y, ladd, U, lat, cc);
-      }
-    }
     const S drho = m.v[0], jx = m.v[1], jy = m.v[2];
     const S rho = rho0 + drho;
     S inv_rho;
@@ -771,6 +882,7 @@ __global__ __launch_bounds__(64 * kCoefWaves) void coef_kernel(const SolveDesc* 
   // staged row r, pair j, column c at C[(3 r + j) HW + c]: the reads of a
   // pair are 64-bit (128-bit) loads at consecutive lanes
   __shared__ Pair<S> C[T::HH * 3 * T::HW];
+  __shared__ WallTable<S, DSW> tab;
   const WorkItem wi = kread_item(&work[blockIdx.x]);
   if (wi.tile < 0) return;
   const SolveDesc& d = descs[wi.solve];
@@ -782,6 +894,10 @@ __global__ __launch_bounds__(64 * kCoefWaves) void coef_kernel(const SolveDesc* 
   asm volatile("" : "+v"(nv));
   const double U = as_global(d.drive)[nv].u;
   const int tid = (int)threadIdx.x;
+  if (WallBand<L>(d).meets((wi.tile % d.tiles_x) * kCoefTileW, (wi.tile / d.tiles_x) * T::TH,
+                           T::TH) &&
+      tid < 16)
+    fill_wall_table<L>(tab, lat, tid);
   {
     // all loads of a thread are issued before the first LDS store, so the
     // block waits for one memory round trip, not one per staged cell
@@ -792,7 +908,7 @@ __global__ __launch_bounds__(64 * kCoefWaves) void coef_kernel(const SolveDesc* 
   __syncthreads();
   S res[RB][6];
   uint32_t valid = 0;
-  compute_tile<L, S, RB, DSW>(d, ctx, wi.tile, C, lat, cc, tid, res, valid, U);
+  compute_tile<L, S, RB, DSW>(d, ctx, wi.tile, C, tab, lat, cc, tid, res, valid, U);
   store_tile<L, S, RB>(d, ctx, wi.tile, tid, res, valid, streaming != 0);
 }
 
