@@ -131,7 +131,8 @@ typedef struct lbm_params {
   uint32_t far;          /* LBM_FAR_* */
   uint32_t tile;         /* kernel tile.  Populations: 0 (= 1), 1, 2 or 4; one workgroup of
                             256*tile threads updates 256*tile consecutive cells, one per
-                            thread.  Coefficients: 0 (= 3), 1, 2 or 3 = K; one workgroup
+                            thread (plates and periodic lattices of at most 16 columns run
+                            a kernel of their own, whatever the tile).  Coefficients: 0 (= 3), 1, 2 or 3 = K; one workgroup
                             of 256 threads updates a tile of 64 columns x 4K rows, K
                             cells per thread.  Batch members kept in the same
                             representation must agree. */
@@ -201,7 +202,8 @@ int lbm_create_static(const lbm_params* p, void* hip_stream, lbm_solver** out);
 
 /* Enqueue nsteps steps on the solver's stream and return without waiting.
  * Calls of 32 steps or more replay a HIP graph of 32 steps that the first
- * such call captures on the stream.  On the null stream, or if that first
+ * such call captures on the stream; populations of at most 16 columns (plates
+ * and periodic lattices) take several steps per launch instead.  On the null stream, or if that first
  * call finds the stream already being captured by the caller, the solver
  * launches step by step from then on (into the caller's capture, if any).
  * Results are the same either way.
@@ -285,7 +287,8 @@ int lbm_destroy(lbm_solver* s);
  * A batch advances many solvers -- uneven lattices with the same lattice,
  * storage and collision, created on the batch's stream -- with one fused
  * stream-collide launch per step over the tiles of every member of a kind
- * and one launch that reduces each member's wall force.  Each member runs the
+ * and one launch that reduces each member's wall force (narrow plates: one
+ * launch per several steps that does both).  Each member runs the
  * kernel it runs when stepped alone, so its results are bit-identical alone
  * and in any mix.  Members may join and leave between steps
  * (continuous batching); a member stops when it reaches its max_steps.

@@ -95,6 +95,53 @@ void order_tiles_banded(std::vector<WorkItem>* out, int32_t solve, int32_t ntile
     }
 }
 
+ColumnShape column_shape(int Q, int nx, int rows, int nsub) {
+  const int R = Q == 9 ? D2Q9::R : D2Q37::R;
+  const int cells = (rows + 2 * R * nsub) * nx;
+  ColumnShape sh;
+  sh.rows = rows;
+  sh.nsub = nsub;
+  sh.threads = (cells + 63) / 64 * 64 + 64;  // the last wavefront for the force
+  return sh;
+}
+
+// Steps per launch: a step's share of the launch (about 4 us) falls as 1/T, the
+// halo it updates (R rows per step left) grows as R (T - 1) / 2 rows per side;
+// D2Q37 is flat from 9 to 15 (a 4 x 2048 plate: 1.67 us per step at 5, 1.47 at
+// 11), D2Q9 from 15 to 31 (4 x 256 FP64: 1.32 us at 5, 0.90 at 31).
+// Rows per workgroup: the fewest with which the launch's workgroups get a
+// compute unit each (five 4 x 2048 plates, 256 CUs: 4.2 us per step at 24
+// rows, 430 workgroups; 2.7 at 41 to 48), 8 at least (below, the halo is most
+// of the work: 0.89 us at 4 to 8 for 4 x 256).
+ColumnPlan column_plan(int Q, int nx, const std::vector<int>& ny) {
+  const int R = Q == 9 ? D2Q9::R : D2Q37::R;
+  const int most = Q == 9 ? kColumnMaxSub : 11, least_rows = 8;
+  ColumnPlan plan;
+  // the halo leaves room for the least rows; wide lattices take fewer steps
+  for (int t = 1; t <= most; t += 2)
+    if ((least_rows + 2 * R * t) * nx <= kColumnCells) plan.max_sub = t;
+  const int fit = kColumnCells / nx;
+  for (plan.rows = least_rows;; ++plan.rows) {
+    int64_t groups = 0;
+    for (int n : ny) groups += (n + plan.rows - 1) / plan.rows;
+    if (groups <= 256 || plan.rows + 1 + 2 * R * std::min(plan.max_sub, 9) > fit) break;
+  }
+  while (plan.max_sub > 1 && plan.rows + 2 * R * plan.max_sub > fit) plan.max_sub -= 2;
+  return plan;
+}
+
+std::vector<int> odd_pieces(int64_t n, int max_sub) {
+  std::vector<int> out;
+  if (n <= 0) return out;
+  int64_t m = (n + max_sub - 1) / max_sub;
+  m += (m ^ n) & 1;  // as many odd numbers as n is odd or even
+  int64_t base = n / m;
+  base -= base % 2 == 0;
+  int64_t twos = (n - m * base) / 2;
+  for (int64_t i = 0; i < m; ++i) out.push_back((int)(base + (i < twos ? 2 : 0)));
+  return out;
+}
+
 // Work-list length order_tiles (and order_tiles_banded) produces for one
 // solve starting aligned.
 int64_t ordered_length(int64_t ntiles, int64_t span) {
@@ -139,6 +186,12 @@ bool uses_coefficients(const lbm_params* p) {
     return true;
   return p->representation == LBM_REPR_AUTO && p->collision == LBM_COLL_REGULARIZED &&
          p->nx >= kCoefTileW && coefficient_plane_fits(p);
+}
+
+// Stepped by the column kernel: plates and periodic lattices of a few columns
+// kept as populations (see column.hip).
+bool uses_columns(const lbm_params* p) {
+  return !uses_coefficients(p) && p->geometry != LBM_GEOM_BOX && p->nx <= kColumnMaxNx;
 }
 
 int validate(const lbm_params* p, HostLattice* lat) {
@@ -489,6 +542,7 @@ void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay) {
     lay->buf_elems = lay->qs * L.Q;
   }
   lay->mom = uses_coefficients(p);
+  lay->column = uses_columns(p);
   lay->loadable = !(lay->mom && p->representation == LBM_REPR_COEFFICIENTS_NOLOAD);
   if (lay->mom) {
     lay->coef_k = p->tile ? (int32_t)p->tile : kCoefKDefault;
@@ -764,6 +818,8 @@ int lbm::create_solver(const lbm_params* p, void* stream, void* dev_buf, uint64_
     s->owned = true;
   }
   s->graphs_ok = graphs;
+  if (s->lay.column)
+    s->column = column_plan((int)p->lattice, p->nx, {p->ny});
   rc = init_solver(s);
   if (rc) {
     if (s->owned) (void)hipFree(s->base);
@@ -805,6 +861,33 @@ int launch_one_step(lbm_solver* s) {
   return LBM_OK;
 }
 
+// Enqueue the launches of n steps (no host bookkeeping).
+int launch_steps(lbm_solver* s, int64_t n) {
+  if (!s->lay.column) {
+    int rc = LBM_OK;
+    for (int64_t k = 0; k < n && rc == LBM_OK; ++k) rc = launch_one_step(s);
+    return rc;
+  }
+  const bool f64 = s->p.storage == LBM_STORE_F64;
+  const int Q = (int)s->p.lattice, rows = s->column.rows;
+  while (n > 0) {
+    // one advance of the step counter for all the launches of a block
+    const int block = (int)std::min<int64_t>(n, kColumnBlock);
+    int dn = 0;
+    for (int nsub : odd_pieces(block, s->column.max_sub)) {
+      if (launch_column(Q, f64, s->p.collision == LBM_COLL_BGK, s->p.wall != LBM_WALL_BB,
+                        column_shape(Q, s->p.nx, rows, nsub), s->d_desc, nullptr,
+                        (s->p.ny + rows - 1) / rows, s->klat, dn, s->stream) != hipSuccess)
+        return LBM_EHIP;
+      dn += nsub;
+    }
+    if (launch_advance(s->d_desc, s->d_solves, 1, block, s->stream) != hipSuccess)
+      return LBM_EHIP;
+    n -= block;
+  }
+  return LBM_OK;
+}
+
 // Capture kGraphSteps steps of a solver whose state is in its steady
 // representation (no pending population load).
 bool capture_steps(lbm_solver* s) {
@@ -814,8 +897,7 @@ bool capture_steps(lbm_solver* s) {
     (void)hipGetLastError();
     return false;
   }
-  bool ok = true;
-  for (int k = 0; k < kGraphSteps && ok; ++k) ok = launch_one_step(s) == LBM_OK;
+  const bool ok = launch_steps(s, kGraphSteps) == LBM_OK;
   if (hipStreamEndCapture(s->stream, &g) != hipSuccess || !ok) {
     (void)hipGetLastError();
     if (g) (void)hipGraphDestroy(g);
@@ -919,11 +1001,20 @@ int lbm_step(lbm_solver* s, int64_t nsteps) {
     ++k;
   }
   // steady chunks replay one captured graph
-  if (nsteps - k >= kGraphSteps && s->graphs_ok && !s->graph && !capture_steps(s))
+  // (not of the column kernel: its launches of several steps keep the device
+  // busy without, and one advance of the counter serves them all)
+  if (nsteps - k >= kGraphSteps && s->graphs_ok && !s->lay.column && !s->graph &&
+      !capture_steps(s))
     s->graphs_ok = false;
   for (; s->graph && k + kGraphSteps <= nsteps; k += kGraphSteps) {
     if (hipGraphLaunch(s->graph, s->stream) != hipSuccess) return LBM_EHIP;
     s->steps += kGraphSteps;
+  }
+  if (s->lay.column && k < nsteps) {
+    const int rc = launch_steps(s, nsteps - k);
+    if (rc) return rc;
+    s->steps += nsteps - k;
+    k = nsteps;
   }
   for (; k < nsteps; ++k) {
     int rc = step_one(s);

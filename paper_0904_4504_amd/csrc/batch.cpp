@@ -26,10 +26,13 @@ struct lbm_batch {
   // current launch set (members that still have steps to run)
   std::vector<lbm_solver*> active;
   bool dirty = true;
-  // work items in four consecutive groups, one launch each: population
-  // kernel (bounce-back wall, diffuse wall), coefficient kernel (the same);
-  // every member runs the kernel instantiation it runs alone
-  int ngroup[4] = {0, 0, 0, 0};
+  // work items in six consecutive groups, one launch each: population kernel
+  // (bounce-back wall, diffuse wall), coefficient kernel and column kernel
+  // (the same); every member runs the kernel instantiation it runs alone
+  int ngroup[6] = {0, 0, 0, 0, 0, 0};
+  ColumnPlan column;      // of the column-kernel members
+  int column_nx = 0;      // their widest lattice
+  int ncolumn = 0;        // how many (the last of the launch set's solve list)
   // coefficient groups whose state streams from HBM (nontemporal stores)
   bool streaming[4] = {false, false, false, false};
   SolveDesc* d_descs = nullptr;
@@ -82,8 +85,16 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   std::vector<SolveDesc> descs;
   // coefficient groups: every member's wall tiles first (they are the slowest
   // tiles of the launch), then the rest
-  std::vector<WorkItem> group[4], front[4], work;
-  std::vector<int32_t> solves;
+  std::vector<WorkItem> group[6], front[6], work;
+  std::vector<int32_t> solves, columns;
+  std::vector<int> column_ny;
+  b->column_nx = 0;
+  for (lbm_solver* s : act)
+    if (s->lay.column) {
+      b->column_nx = std::max(b->column_nx, s->p.nx);
+      column_ny.push_back(s->p.ny);
+    }
+  if (b->column_nx) b->column = column_plan(b->Q, b->column_nx, column_ny);
   uint64_t state[4] = {0, 0, 0, 0};  // coefficient state bytes per group
   for (size_t i = 0; i < act.size(); ++i) {
     const Layout& lay = act[i]->lay;
@@ -91,10 +102,13 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   }
   for (size_t i = 0; i < act.size(); ++i) {
     descs.push_back(act[i]->desc);
-    solves.push_back((int32_t)i);
     const Layout& lay = act[i]->lay;
-    const int k = (lay.mom ? 2 : 0) + (act[i]->p.wall != LBM_WALL_BB);
-    if (lay.mom) {
+    (lay.column ? columns : solves).push_back((int32_t)i);
+    const int k = (lay.mom ? 2 : lay.column ? 4 : 0) + (act[i]->p.wall != LBM_WALL_BB);
+    if (lay.column) {
+      const int tiles = (act[i]->p.ny + b->column.rows - 1) / b->column.rows;
+      for (int t = 0; t < tiles; ++t) group[k].push_back(WorkItem{(int32_t)i, t});
+    } else if (lay.mom) {
       order_coef_tiles(&front[k], &group[k], (int32_t)i,
                        coef_wall_tiles(&act[i]->p, lay, act[i]->lat.R), lay.mntiles, lay.tiles_x,
                        state[k] <= kCachedStateBytes);
@@ -103,13 +117,15 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
                   (act[i]->p.nx + lay.cells_per_tile - 1) / lay.cells_per_tile);
     }
   }
-  for (int k = 0; k < 4; ++k) {
+  b->ncolumn = (int)columns.size();
+  solves.insert(solves.end(), columns.begin(), columns.end());
+  for (int k = 0; k < 6; ++k) {
     if (!front[k].empty()) {
       join_front(&front[k], group[k]);
       group[k].swap(front[k]);
     }
     b->ngroup[k] = (int)group[k].size();
-    b->streaming[k] = state[k] > kCachedStateBytes;
+    if (k < 4) b->streaming[k] = state[k] > kCachedStateBytes;
     work.insert(work.end(), group[k].begin(), group[k].end());
   }
   if (act.empty()) return LBM_OK;
@@ -151,55 +167,102 @@ int collect_timing(lbm_batch* b) {
   return LBM_OK;
 }
 
-int launch_one(lbm_batch* b) {
+// The launches of column-kernel members, nsub steps each, dn steps after the
+// last advance of their counters.
+hipError_t launch_columns(lbm_batch* b, int nsub, int dn, KernelEvents ev) {
+  const bool f64 = b->storage == LBM_STORE_F64;
+  const WorkItem* work = b->d_work;
+  for (int k = 0; k < 4; ++k) work += b->ngroup[k];
+  for (int k = 4; k < 6; ++k) {
+    const int n = b->ngroup[k];
+    if (n == 0) continue;
+    const hipError_t e =
+        launch_column(b->Q, f64, b->collision == LBM_COLL_BGK, k & 1,
+                      column_shape(b->Q, b->column_nx, b->column.rows, nsub), b->d_descs,
+                      work, n, b->active[0]->klat, dn, b->stream, ev);
+    if (e != hipSuccess) return e;
+    work += n;
+  }
+  return hipSuccess;
+}
+
+// The population- and coefficient-kernel launches of one step.
+hipError_t launch_tiles(lbm_batch* b, KernelEvents ev) {
   const bool f64 = b->storage == LBM_STORE_F64, bgk = b->collision == LBM_COLL_BGK;
   const KernelLattice& lat = b->active[0]->klat;
-  int nlaunch = 0;
-  for (int k = 0; k < 4; ++k) nlaunch += b->ngroup[k] > 0;
-  // ev: the launch records its own start and end (it is the only step
-  // kernel launch of the launch set)
-  auto step = [&](KernelEvents ev) {
-    const KernelEvents own = nlaunch == 1 ? ev : KernelEvents{};
-    const WorkItem* work = b->d_work;
-    for (int k = 0; k < 4; ++k) {
-      const int n = b->ngroup[k];
-      if (n == 0) continue;
-      const bool ds = k & 1;
-      const hipError_t e =
-          k < 2 ? launch_step(b->Q, f64, bgk, ds, b->cpt, false, b->d_descs, work, n, lat,
-                              b->stream, own)
-                : launch_coef(b->Q, f64, b->coef_k, ds, b->streaming[k], b->d_descs, work, n,
-                              lat, b->stream, own);
-      if (e != hipSuccess) return e;
-      work += n;
-    }
-    return hipSuccess;
-  };
-  if (b->timing) {
-    if (b->ev_used + 2 > 4096) {
-      int rc = collect_timing(b);
-      if (rc) return rc;
-    }
-    hipEvent_t e0 = next_event(b), e1 = next_event(b);
-    if (!e0 || !e1) return LBM_EHIP;
-    if (nlaunch > 1) {
-      // several launches: events around them
-      if (hipEventRecord(e0, b->stream) != hipSuccess) return LBM_EHIP;
-      if (step(KernelEvents{}) != hipSuccess) return LBM_EHIP;
-      if (hipEventRecord(e1, b->stream) != hipSuccess) return LBM_EHIP;
-    } else if (step(KernelEvents{e0, e1}) != hipSuccess) {
-      return LBM_EHIP;
-    }
-  } else if (step(KernelEvents{}) != hipSuccess) {
-    return LBM_EHIP;
+  const WorkItem* work = b->d_work;
+  for (int k = 0; k < 4; ++k) {
+    const int n = b->ngroup[k];
+    if (n == 0) continue;
+    const bool ds = k & 1;
+    const hipError_t e =
+        k < 2 ? launch_step(b->Q, f64, bgk, ds, b->cpt, false, b->d_descs, work, n, lat,
+                            b->stream, ev)
+              : launch_coef(b->Q, f64, b->coef_k, ds, b->streaming[k], b->d_descs, work, n, lat,
+                            b->stream, ev);
+    if (e != hipSuccess) return e;
+    work += n;
   }
-  if (launch_finalize(f64, b->d_descs, b->d_solves, (int)b->active.size(), 2, b->stream) !=
-      hipSuccess)
+  return hipSuccess;
+}
+
+// The finalize of the members that the column kernel does not serve.
+hipError_t launch_finalizes(lbm_batch* b) {
+  return launch_finalize(b->storage == LBM_STORE_F64, b->d_descs, b->d_solves,
+                         (int)b->active.size() - b->ncolumn, 2, b->stream);
+}
+
+// One step of every member, its step-kernel launches timed.
+int launch_timed(lbm_batch* b) {
+  int nlaunch = 0;
+  for (int k = 0; k < 6; ++k) nlaunch += b->ngroup[k] > 0;
+  if (b->ev_used + 2 > 4096) {
+    int rc = collect_timing(b);
+    if (rc) return rc;
+  }
+  hipEvent_t e0 = next_event(b), e1 = next_event(b);
+  if (!e0 || !e1) return LBM_EHIP;
+  // a single launch records its own start and end; several: events around them
+  const KernelEvents own = nlaunch == 1 ? KernelEvents{e0, e1} : KernelEvents{};
+  if (nlaunch > 1 && hipEventRecord(e0, b->stream) != hipSuccess) return LBM_EHIP;
+  if (launch_columns(b, 1, 0, own) != hipSuccess || launch_tiles(b, own) != hipSuccess)
+    return LBM_EHIP;
+  if (nlaunch > 1 && hipEventRecord(e1, b->stream) != hipSuccess) return LBM_EHIP;
+  if (launch_advance(b->d_descs, b->d_solves + (b->active.size() - b->ncolumn), b->ncolumn, 1,
+                     b->stream) != hipSuccess ||
+      launch_finalizes(b) != hipSuccess)
     return LBM_EHIP;
   return LBM_OK;
 }
 
-// Capture graph_chunk steps of the current launch set into a graph.
+// n steps of the column-kernel members, several per launch.
+int launch_column_steps(lbm_batch* b, int64_t n) {
+  const int nfin = (int)b->active.size() - b->ncolumn;
+  for (int64_t left = b->ncolumn ? n : 0; left > 0;) {
+    const int block = (int)std::min<int64_t>(left, kColumnBlock);
+    int dn = 0;
+    for (int nsub : odd_pieces(block, b->column.max_sub)) {
+      if (launch_columns(b, nsub, dn, KernelEvents{}) != hipSuccess) return LBM_EHIP;
+      dn += nsub;
+    }
+    if (launch_advance(b->d_descs, b->d_solves + nfin, b->ncolumn, block, b->stream) !=
+        hipSuccess)
+      return LBM_EHIP;
+    left -= block;
+  }
+  return LBM_OK;
+}
+
+// n steps of the other members, step by step.
+int launch_tile_steps(lbm_batch* b, int64_t n) {
+  const int nfin = (int)b->active.size() - b->ncolumn;
+  for (int64_t k = 0; nfin > 0 && k < n; ++k)
+    if (launch_tiles(b, KernelEvents{}) != hipSuccess || launch_finalizes(b) != hipSuccess)
+      return LBM_EHIP;
+  return LBM_OK;
+}
+
+// Capture graph_chunk steps of the members stepped by tiles into a graph.
 bool capture(lbm_batch* b) {
   if (b->stream == nullptr) return false;  // the null stream cannot be captured
   hipGraph_t g = nullptr;
@@ -207,11 +270,7 @@ bool capture(lbm_batch* b) {
     (void)hipGetLastError();
     return false;
   }
-  bool ok = true;
-  const bool timing = b->timing;
-  b->timing = false;
-  for (int k = 0; k < b->graph_chunk && ok; ++k) ok = launch_one(b) == LBM_OK;
-  b->timing = timing;
+  const bool ok = launch_tile_steps(b, b->graph_chunk) == LBM_OK;
   if (hipStreamEndCapture(b->stream, &g) != hipSuccess || !ok) {
     (void)hipGetLastError();
     if (g) (void)hipGraphDestroy(g);
@@ -323,13 +382,20 @@ int lbm_batch_step(lbm_batch* b, int64_t nsteps) {
     int rc = refresh(b, act);
     if (rc) return rc;
     int64_t k = 0;
-    if (b->graphs_enabled && !b->timing && chunk >= b->graph_chunk) {
-      if (!b->graph && !capture(b)) b->graphs_enabled = false;
-      for (; b->graph && k + b->graph_steps <= chunk; k += b->graph_steps)
-        if (hipGraphLaunch(b->graph, b->stream) != hipSuccess) return LBM_EHIP;
+    if (b->timing) {
+      for (; k < chunk; ++k)
+        if ((rc = launch_timed(b))) return rc;
+    } else {
+      // members do not interact: the column-kernel ones take the whole chunk
+      // first, then the others step by step, in graphs where the chunk allows
+      if ((rc = launch_column_steps(b, chunk))) return rc;
+      if ((int)act.size() > b->ncolumn && b->graphs_enabled && chunk >= b->graph_chunk) {
+        if (!b->graph && !capture(b)) b->graphs_enabled = false;
+        for (; b->graph && k + b->graph_steps <= chunk; k += b->graph_steps)
+          if (hipGraphLaunch(b->graph, b->stream) != hipSuccess) return LBM_EHIP;
+      }
+      if ((rc = launch_tile_steps(b, chunk - k))) return rc;
     }
-    for (; k < chunk; ++k)
-      if ((rc = launch_one(b))) return rc;
     for (size_t i = 0; i < b->members.size(); ++i)
       if (left[i] > 0) {
         b->members[i]->steps += chunk;

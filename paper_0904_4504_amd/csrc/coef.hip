@@ -76,14 +76,6 @@ CoefConst<S> coef_const(const KernelLattice& lat) {
 
 namespace {
 
-// Index of velocity (vx, vy) in lattice L, or -1.
-template <class L>
-constexpr int find_q(int vx, int vy) {
-  for (int q = 0; q < L::Q; ++q)
-    if (L::vx[q] == vx && L::vy[q] == vy) return q;
-  return -1;
-}
-
 template <typename S>
 __device__ __forceinline__ S fmadd(S a, S b, S c) {
   if constexpr (sizeof(S) == 4)
@@ -157,7 +149,7 @@ template <class L, int RB>
 constexpr bool source_used(int vx, int iy) {
   for (int k = 0; k < RB; ++k) {
     const int vy = k - iy;
-    if (vy >= -L::R && vy <= L::R && find_q<L>(vx, vy) >= 0) return true;
+    if (vy >= -L::R && vy <= L::R && find_velocity<L>(vx, vy) >= 0) return true;
   }
   return false;
 }
@@ -170,7 +162,7 @@ struct WeightMap {
   constexpr WeightMap() : orbit() {
     for (int a = 0; a < 4; ++a)
       for (int b = 0; b < 4; ++b) {
-        const int q = a <= L::R && b <= L::R ? find_q<L>(a, b) : -1;
+        const int q = a <= L::R && b <= L::R ? find_velocity<L>(a, b) : -1;
         orbit[a][b] = (int8_t)(q >= 0 ? L::orbit[q] : -1);
       }
   }
@@ -478,7 +470,7 @@ template <class L>
 constexpr int pull_q(int dx, int iy, int k) {
   const int vy = k - iy;
   if (vy < -L::R || vy > L::R) return -1;
-  return find_q<L>(-dx, vy);
+  return find_velocity<L>(-dx, vy);
 }
 
 // First column offset of source row iy that feeds output row k (with

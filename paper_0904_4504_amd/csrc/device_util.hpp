@@ -34,4 +34,26 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Sum over the wavefront in lane 63 (other lanes: partial sums), by shifts
+// within rows of 16 lanes and broadcasts between them: register moves of a few
+// cycles, where a shuffle goes through the LDS unit.
+__device__ __forceinline__ double wave_sum_63(double v) {
+  auto from = [](double x, auto ctrl) __attribute__((always_inline)) {
+    constexpr int c = decltype(ctrl)::value;
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, c, 0xf, 0xf,
+                                                              false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), c, 0xf,
+                                                              0xf, false);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  };
+  v += from(v, std::integral_constant<int, 0x111>{});  // row_shr:1
+  v += from(v, std::integral_constant<int, 0x112>{});  // row_shr:2
+  v += from(v, std::integral_constant<int, 0x114>{});  // row_shr:4
+  v += from(v, std::integral_constant<int, 0x118>{});  // row_shr:8
+  v += from(v, std::integral_constant<int, 0x142>{});  // row_bcast:15
+  v += from(v, std::integral_constant<int, 0x143>{});  // row_bcast:31
+  return v;
+}
+
 }  // namespace lbm

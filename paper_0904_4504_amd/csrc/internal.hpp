@@ -21,6 +21,15 @@ hipError_t launch_step(int Q, bool f64, bool bgk, bool ds, int cpt, bool outm,
 hipError_t launch_coef(int Q, bool f64, int k, bool ds, bool streaming, const SolveDesc* descs,
                        const WorkItem* work, int nwork, const KernelLattice& lat,
                        hipStream_t stream, KernelEvents ev = {});
+// nsub steps of narrow lattices, dn steps after the counters' last advance.
+// work: (solve, tile of `rows` rows) items, or null for nwork tiles of solve 0.
+hipError_t launch_column(int Q, bool f64, bool bgk, bool ds, const ColumnShape& shape,
+                         const SolveDesc* descs, const WorkItem* work, int nwork,
+                         const KernelLattice& lat, int dn, hipStream_t stream,
+                         KernelEvents ev = {});
+// Advance the step counters of the listed solves.
+hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int count, int nsteps,
+                          hipStream_t stream);
 hipError_t launch_finalize(bool f64, const SolveDesc* descs, const int32_t* solves, int nsolves,
                            int mode, hipStream_t stream);
 
@@ -39,6 +48,7 @@ struct HostLattice {
 
 // Where every region lives inside the one device allocation.
 struct Layout {
+  bool column = false;  // stepped by the column kernel
   int64_t pitch = 0, qs = 0, ys = 0, buf_elems = 0;
   int32_t ntiles = 0, cells_per_tile = kBlock, cpt = 1;
   int32_t nlinks = 0, nfcells = 0, nwcols = 0, nwlinks = 0, nlweights = 0, ncweights = 0;
@@ -81,6 +91,18 @@ void order_coef_tiles(std::vector<WorkItem>* front, std::vector<WorkItem>* rest,
 // stream from HBM: the row-interleaved order (adjacent rows in flight on all
 // XCDs at once) and nontemporal stores.
 constexpr uint64_t kCachedStateBytes = (uint64_t)192 << 20;
+// Most column-kernel steps between two advances of the step counter.
+constexpr int kColumnBlock = 1024;
+// Split of column-kernel launches: rows per workgroup and the most steps per
+// launch, for lattices of ny rows each and at most nx columns.
+struct ColumnPlan {
+  int rows = 0, max_sub = 1;
+};
+ColumnPlan column_plan(int Q, int nx, const std::vector<int>& ny);
+ColumnShape column_shape(int Q, int nx, int rows, int nsub);
+// n as a sum of odd numbers of at most max_sub (odd): the steps per launch of
+// a call of n steps.
+std::vector<int> odd_pieces(int64_t n, int max_sub);
 // front, padded with no-ops to a multiple of 8 items, then rest.
 void join_front(std::vector<WorkItem>* front, const std::vector<WorkItem>& rest);
 
@@ -99,6 +121,7 @@ struct lbm_solver {
   lbm::HostLattice lat;
   lbm::Layout lay;
   lbm::KernelLattice klat{};
+  lbm::ColumnPlan column;     // of lattices stepped by the column kernel
   hipStream_t stream = nullptr;
   char* base = nullptr;       // device allocation (owned or caller's)
   void* bufs[2] = {nullptr, nullptr};  // population buffers; bufs[steps & 1] is current

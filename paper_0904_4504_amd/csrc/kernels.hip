@@ -593,18 +593,7 @@ __device__ void finalize_solve(const SolveDesc& d, int mode) {
     }
     fx = d.fstatic[0] + d.kladd[0] * dr.u + sx;
     fy = d.fstatic[1] + d.kladd[1] * dr.u + sy;
-    if (d.wall == WALL_DS && d.geom == GEOM_PLATE) {
-      // the diffuse emissions' share of -sum v_i f_i^adv over the links:
-      // every column emits w_i rho_w E_i(U) along each link, rho_w from the
-      // column's crossing mass (rest part nx rho0 A1, deviation sm)
-      const double U = dr.u, uu = U * U;
-      const double emit = d.ds[0] + uu * d.ds[1];
-      const double nr = d.ds[5];
-      fx -= d.sigma * (nr * d.ds[0] * U * d.ds[2] + sm * U * d.ds[2]) / emit;
-      fy -= d.sigma *
-            (nr * uu * (d.ds[0] * d.ds[4] - d.ds[1] * d.ds[3]) + sm * (d.ds[3] + uu * d.ds[4])) /
-            emit;
-    }
+    if (d.wall == WALL_DS && d.geom == GEOM_PLATE) add_emission_force(wall_emission(d), dr.u, sm, &fx, &fy);
     const int64_t h = n % d.hist_cap;
     d.hist[2 * h] = fx;
     d.hist[2 * h + 1] = fy;

@@ -45,6 +45,14 @@ struct D2Q37 {
                                    5, 5, 6, 6, 6, 6, 6, 6, 6, 6, 7, 7, 7, 7, 7, 7, 7, 7};
 };
 
+// Index of the velocity (vx, vy), or -1, evaluated at compile time.
+template <class L>
+constexpr int find_velocity(int vx, int vy) {
+  for (int q = 0; q < L::Q; ++q)
+    if (L::vx[q] == vx && L::vy[q] == vy) return q;
+  return -1;
+}
+
 // Index of the opposite velocity (v_opp = -v), evaluated at compile time.
 template <class L>
 constexpr int opposite(int i) {

@@ -21,7 +21,26 @@ constexpr int kCoefKDefault = 3;
 // each (K cells per thread).
 constexpr int kCoefWaves = 4;    // coefficient kernel: wavefronts per workgroup
 __host__ __device__ constexpr int coef_tile_rows(int K) { return kCoefWaves * K; }
-constexpr int kMaxSlots = 1 << 20;
+
+// Column kernel (several steps per launch of lattices of a few columns).
+constexpr int kColumnMaxNx = 16;    // widest lattice it takes
+constexpr int kColumnThreads = 512; // most threads of a workgroup (7 waves of cells, 1 for the force)
+constexpr int kColumnMaxSub = 31;   // most steps per launch (odd)
+// Cells of a workgroup, one thread each; its Q populations of them take 66
+// (D2Q37 FP32) to 133 KB (FP64) of the 160 KB of LDS.
+constexpr int kColumnCells = kColumnThreads - 64;
+// LDS stride between lattice columns: where it fits, such that the lanes of a
+// wavefront (64 / nx rows of nx columns) hit every bank equally often.
+__host__ __device__ constexpr int column_stride(int region, int nx, int es) {
+  const int mod = es == 8 ? 16 : 32, want = mod / nx > 0 ? mod / nx : 1;
+  const int ys = region + (mod + want - region % mod) % mod;
+  return ys * nx <= kColumnCells ? ys : region;
+}
+// Shape of a column-kernel launch: rows per workgroup, steps per launch (odd),
+// threads for the widest lattice of the launch.
+struct ColumnShape {
+  int rows = 0, nsub = 1, threads = 0;
+};
 
 enum Geom : int32_t { GEOM_PLATE = 0, GEOM_BOX = 1, GEOM_PERIODIC = 2 };
 enum Far : int32_t { FAR_WALL = 0, FAR_EQ = 1 };

@@ -26,6 +26,27 @@ __device__ __forceinline__ double ds_arrival(const SolveDesc& d, double U, doubl
   return wq * (d.rho0 * (d.ds[0] * e - uu * d.ds[1]) + cm * (1 + e)) / emit;
 }
 
+// The diffuse emissions' share of a plate's wall force, -sum v_i f_i^adv over
+// the links: every column emits w_i rho_w E_i(U) along each link, rho_w from
+// the column's crossing mass (rest part nx rho0 A1, deviation sm summed over
+// the columns).
+struct WallEmission {
+  double ds[6], sigma;
+};
+__device__ __forceinline__ WallEmission wall_emission(const SolveDesc& d) {
+  return WallEmission{{d.ds[0], d.ds[1], d.ds[2], d.ds[3], d.ds[4], d.ds[5]}, d.sigma};
+}
+__device__ __forceinline__ void add_emission_force(const WallEmission& w, double U, double sm,
+                                                   double* fx, double* fy) {
+  const double uu = U * U;
+  const double emit = w.ds[0] + uu * w.ds[1];
+  const double nr = w.ds[5];
+  *fx -= w.sigma * (nr * w.ds[0] * U * w.ds[2] + sm * U * w.ds[2]) / emit;
+  *fy -= w.sigma *
+         (nr * uu * (w.ds[0] * w.ds[4] - w.ds[1] * w.ds[3]) + sm * (w.ds[3] + uu * w.ds[4])) /
+         emit;
+}
+
 // Box with diffuse or Maxwell faces: face of a fluid cell (x, y) within R
 // cells of the body, by the axis on which the cell lies outside the body's
 // range: 0 below the body, 1 above, 2 left, 3 right; -1 if outside on both

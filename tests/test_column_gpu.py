@@ -1,0 +1,56 @@
+"""Narrow lattices (the column kernel: several steps per launch): parity with
+the oracle at the edges of its tiles and any split of a run into calls."""
+import math
+
+import numpy as np
+import pytest
+
+import lbm_inputs as W
+import oracle as O
+from tests.test_parity_gpu import P, _f0, _oracle_params  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# rows of a workgroup are 8 and up: one tile, a full one, one row over, several
+SIZES = [(3, 3), (4, 8), (4, 9), (5, 37), (7, 64), (16, 29), (15, 130)]
+
+
+@pytest.mark.parametrize("geom,far,wall,sigma,coll", [
+    (W.PLATE, W.FAR_WALL, "bb", 1.0, "regularized"),
+    (W.PLATE, W.FAR_EQ, "maxwell", 0.35, "regularized"),
+    (W.PLATE, W.FAR_WALL, "ds", 1.0, "bgk"),
+    (W.PERIODIC, W.FAR_EQ, "bb", 1.0, "bgk"),
+])
+@pytest.mark.parametrize("Q", [9, 37])
+@pytest.mark.parametrize("nx,ny", SIZES)
+def test_column_kernel(P, nx, ny, Q, geom, far, wall, sigma, coll):  # noqa: F811
+    """Fields and forces after 71 steps in calls of 1, 2, 13, 32 and 23 against
+    the long-double oracle (FP64: 71 steps of a few roundings, 1e-12), and the
+    same bits from one call per step; FP32 within 2e-5."""
+    calls = [1, 2, 13, 32, 23]
+    n = sum(calls)
+    print(f"case {nx}x{ny} Q{Q} {geom} {far} {wall} {coll}", flush=True)
+    v, w, th = P.lattice(Q)
+    for storage in ("f64", "f32dev"):
+        s = W.Solve(Q=Q, geometry=geom, far=far, nx=nx, ny=ny, tau=0.9, omega=2 * math.pi / 40,
+                    nsteps=n, window_first=5, window_count=n - 9, storage=storage,
+                    collision=coll, wall=wall, accommodation=sigma)
+        f0 = _f0(s, w, seed=11, amp=1e-3)
+        out = []
+        for split in (calls, [1] * n):
+            with P.Solver(P.params_from_solve(s)) as sv:
+                sv.set_populations(f0)
+                for k in split:
+                    sv.step(k)
+                out.append((*sv.force_history(), sv.get_deviations(), sv.lockin()[0]))
+        assert all(np.array_equal(a, b) for a, b in zip(*out))
+        ox, oy, of = O.run(_oracle_params(s), n, f0=f0, want_state=True, variant="ld")
+        rest = w[:, None, None] * s.rho0
+        tol = 1e-12 if storage == "f64" else 2e-5
+        fx, fy, f, _ = out[0]
+        assert np.max(np.abs(f - (of - rest))) <= tol * np.max(np.abs(of - rest)) + \
+            2 * np.spacing(np.max(w))
+        if geom == W.PLATE:
+            scale = max(np.max(np.abs(ox)), np.max(np.abs(oy)))
+            assert np.max(np.abs(fx - ox)) <= tol * scale
+            assert np.max(np.abs(fy - oy)) <= tol * scale
