@@ -132,10 +132,12 @@ typedef struct lbm_params {
   uint32_t tile;         /* kernel tile.  Populations: 0 (= 1), 1, 2 or 4; one workgroup of
                             256*tile threads updates 256*tile consecutive cells, one per
                             thread (plates and periodic lattices of at most 16 columns run
-                            a kernel of their own, whatever the tile).  Coefficients: 0 (= 3), 1, 2 or 3 = K; one workgroup
+                            a kernel of their own, whatever the tile).  Coefficients: 0
+                            (chosen by the size of each launch), 1, 2 or 3 = K; one workgroup
                             of 256 threads updates a tile of 64 columns x 4K rows, K
                             cells per thread.  Batch members kept in the same
-                            representation must agree. */
+                            representation must agree (0 counts as 1 for populations, as
+                            3 for coefficients). */
   uint32_t representation; /* device state: 0 = automatic, 1 = the Q populations, 2 = the six
                             H2 coefficients of the regularized post-collision state
                             (regularized collision only; automatic picks 2 when nx >= 64
@@ -286,9 +288,8 @@ int lbm_destroy(lbm_solver* s);
 /* ------------------------------------------------------------------ batches
  * A batch advances many solvers -- uneven lattices with the same lattice,
  * storage and collision, created on the batch's stream -- with one fused
- * stream-collide launch per step over the tiles of every member of a kind
- * and one launch that reduces each member's wall force (narrow plates: one
- * launch per several steps that does both).  Each member runs the
+ * launch per step and kind of member that updates all their tiles and reduces
+ * their wall forces (narrow plates: one launch per several steps).  Each member runs the
  * kernel it runs when stepped alone, so its results are bit-identical alone
  * and in any mix.  Members may join and leave between steps
  * (continuous batching); a member stops when it reaches its max_steps.

@@ -37,11 +37,34 @@ void order_tiles(std::vector<WorkItem>* out, int32_t solve, int32_t ntiles, int3
       }
 }
 
-// Coefficient-kernel tiles (of a solve with this layout) that hold a cell
+// Small launches take one row per wavefront: few workgroups per compute unit,
+// so a step is the chain of one wavefront, which K rows make K times as long
+// (a 256 x 256 box, K = 1, 2, 3: FP32 8.8, 11.6, 14.6 us per step, FP64 9.9,
+// 13.4, 17.3).  Large ones share the halo and the source cells among more rows.
+// The lines: FP32 768 x 768 13.7, 14.1, 15.2, 1024 x 1024 21.5, 18.3, 18.2,
+// 1400 x 1400 33.0, 27.0, 25.6; FP64 512 x 512 12.9, 14.5, 17.2, 768 x 768
+// 21.9, 20.5, 21.5, 1400 x 1400 53.6, 45.6, 51.0 (K = 3 leaves two workgroups
+// per compute unit by LDS).  A cell's bits do not depend on K.
+int coef_k_for(uint32_t tile, bool f64, int64_t cells) {
+  if (tile) return (int)tile;
+  if (f64) return cells <= 400000 ? 1 : 2;
+  return cells <= 720000 ? 1 : kCoefKDefault;
+}
+
+CoefGrid coef_grid(const lbm_params* p, int K) {
+  const int th = coef_tile_rows(K);
+  CoefGrid g;
+  g.tiles_x = (p->nx + kCoefTileW - 1) / kCoefTileW;
+  g.ntiles = g.tiles_x * ((p->ny + th - 1) / th);
+  return g;
+}
+
+// Coefficient-kernel tiles (of K cells per thread) that hold a cell
 // with a wall link: the band of R cells around the body, the plate's wall rows
 // (the same band the kernel tests per wavefront).
-std::vector<char> coef_wall_tiles(const lbm_params* p, const Layout& lay, int R) {
-  std::vector<char> wall((size_t)lay.mntiles, 0);
+std::vector<char> coef_wall_tiles(const lbm_params* p, int K, int R) {
+  const CoefGrid grid = coef_grid(p, K);
+  std::vector<char> wall((size_t)grid.ntiles, 0);
   int wx0 = 0, wx1 = p->nx, wy0 = 0, wy1 = 0;
   bool far_band = false;
   if (p->geometry == LBM_GEOM_BOX) {
@@ -53,9 +76,9 @@ std::vector<char> coef_wall_tiles(const lbm_params* p, const Layout& lay, int R)
     wy1 = R;
     far_band = p->far == LBM_FAR_WALL;
   }
-  const int th = coef_tile_rows(lay.coef_k);
-  for (int32_t t = 0; t < lay.mntiles; ++t) {
-    const int x0 = (t % lay.tiles_x) * kCoefTileW, y0 = (t / lay.tiles_x) * th;
+  const int th = coef_tile_rows(K);
+  for (int32_t t = 0; t < grid.ntiles; ++t) {
+    const int x0 = (t % grid.tiles_x) * kCoefTileW, y0 = (t / grid.tiles_x) * th;
     wall[t] = (x0 < wx1 && x0 + kCoefTileW > wx0 && y0 < wy1 && y0 + th > wy0) ||
               (far_band && y0 + th > p->ny - R);
   }
@@ -289,7 +312,7 @@ void mirror_of(const lbm_params* p, const HostLattice& L, int x, int y, int q, i
 // df_opp(x_p) = w_i (a0 - vx bx - vy by + vx^2 cxx + vx vy cxy + vy^2 cyy)).
 // At a diffuse wall (eq. DS) the arrival f_i^adv is the wall's emission: the
 // tables then carry -v_i df_opp(x_p) and the crossing mass df_opp(x_p), and
-// the emission's share follows from the lattice sums in `ds` (finalize).
+// the emission's share follows from the lattice sums in `ds` (wall_force).
 struct ForceTables {
   std::vector<ForceLink> links;
   std::vector<ForceCell> cells;
@@ -311,7 +334,7 @@ bool diffuse_box(const lbm_params* p) {
 // by arrival y; in a column by arrival cell and direction), then the corner
 // links; per column the lattice sums of its links (long double).  The force
 // is -sum v_l (f_partner + f_arrival) over every link: the rest-state parts
-// give fstatic, the rest is formed per link by the finalize.
+// give fstatic, the rest is formed per link by wall_force.
 void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& lay,
                        ForceTables* t) {
   const int R = L.R;
@@ -546,9 +569,7 @@ void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay) {
   lay->loadable = !(lay->mom && p->representation == LBM_REPR_COEFFICIENTS_NOLOAD);
   if (lay->mom) {
     lay->coef_k = p->tile ? (int32_t)p->tile : kCoefKDefault;
-    const int th = coef_tile_rows(lay->coef_k);
-    lay->tiles_x = (p->nx + kCoefTileW - 1) / kCoefTileW;
-    lay->mntiles = lay->tiles_x * ((p->ny + th - 1) / th);
+    lay->launch_k = coef_k_for(p->tile, es == 8, (int64_t)p->nx * p->ny);
     // element (k, y, x) of a buffer at k*mks + y*mpitch + x.  Row-interleaved
     // where the whole buffer stays addressable with 32-bit byte offsets: the
     // six coefficient rows of lattice row y side by side, so the staged rows
@@ -582,14 +603,16 @@ void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay) {
   };
   lay->off_desc = take(sizeof(SolveDesc));
   lay->off_state = take(sizeof(SolveState));
-  // XCD-aware order pads each group of 8 rows to full length
-  lay->nwork = (int32_t)ordered_length(lay->ntiles, (p->nx + lay->cells_per_tile - 1) /
-                                                        lay->cells_per_tile);
+  // the force's item and padding, then the XCD-aware order, which pads each
+  // group of 8 rows to full length
+  lay->nwork = 8 + (int32_t)ordered_length(lay->ntiles, (p->nx + lay->cells_per_tile - 1) /
+                                                            lay->cells_per_tile);
   lay->off_work = take(sizeof(WorkItem) * (uint64_t)lay->nwork);
   if (lay->mom) {
-    int64_t nwall = 0;
-    for (char w : coef_wall_tiles(p, *lay, L.R)) nwall += w;
-    lay->mnwork = (int32_t)((nwall + 7) / 8 * 8 + ordered_length(lay->mntiles, lay->tiles_x));
+    int64_t nfront = 1;  // the force's item and the wall tiles
+    for (char w : coef_wall_tiles(p, lay->launch_k, L.R)) nfront += w;
+    const CoefGrid g = coef_grid(p, lay->launch_k);
+    lay->mnwork = (int32_t)((nfront + 7) / 8 * 8 + ordered_length(g.ntiles, g.tiles_x));
     lay->off_mwork = take(sizeof(WorkItem) * (uint64_t)lay->mnwork);
   }
   lay->off_solves = take(sizeof(int32_t));
@@ -694,18 +717,21 @@ int init_solver(lbm_solver* s) {
     d.mbuf[1] = b + lay.off_mbuf[1];
     d.mks = lay.mks;
     d.mys = lay.mpitch;
-    d.tiles_x = lay.tiles_x;
+    d.tiles_x = coef_grid(p, lay.launch_k).tiles_x;
   }
 
   for (int k = 0; k < 8; ++k) s->klat.w[k] = s->lat.lw.w_orbit[k];
   s->klat.theta = s->lat.lw.theta;
 
-  std::vector<WorkItem> work, mwork;
-  order_tiles(&work, 0, lay.ntiles, (p->nx + lay.cells_per_tile - 1) / lay.cells_per_tile);
+  std::vector<WorkItem> work{WorkItem{0, kForceTile}}, mwork, rest;
+  order_tiles(&rest, 0, lay.ntiles, (p->nx + lay.cells_per_tile - 1) / lay.cells_per_tile);
+  join_front(&work, rest);
   if (lay.mom) {
-    std::vector<WorkItem> rest;
-    order_coef_tiles(&mwork, &rest, 0, coef_wall_tiles(p, lay, s->lat.R), lay.mntiles,
-                     lay.tiles_x, 2 * lay.mbuf_bytes <= kCachedStateBytes);
+    const CoefGrid g = coef_grid(p, lay.launch_k);
+    mwork.push_back(WorkItem{0, kForceTile});
+    rest.clear();
+    order_coef_tiles(&mwork, &rest, 0, coef_wall_tiles(p, lay.launch_k, s->lat.R), g.ntiles,
+                     g.tiles_x, 2 * lay.mbuf_bytes <= kCachedStateBytes);
     join_front(&mwork, rest);
     if ((int32_t)mwork.size() != lay.mnwork) return LBM_EINVAL;
   }
@@ -832,49 +858,43 @@ int lbm::create_solver(const lbm_params* p, void* stream, void* dev_buf, uint64_
 
 // One step of a single solver: the population kernel, the population kernel
 // writing coefficients (first step after populations were loaded into a
-// coefficient solver), or the coefficient kernel; then the finalize.
+// coefficient solver), or the coefficient kernel.
 namespace {
 
-// Enqueue one step's launches (no host bookkeeping).
-int launch_one_step(lbm_solver* s) {
+// Enqueue one step's launch, dn steps after the last advance of the counter.
+int launch_one_step(lbm_solver* s, int dn) {
   const bool f64 = s->p.storage == LBM_STORE_F64;
   const bool bgk = s->p.collision == LBM_COLL_BGK;
   const int Q = (int)s->p.lattice;
   const bool ds = s->p.wall != LBM_WALL_BB;
-  int mode = 0;
   hipError_t e;
   if (!s->lay.mom) {
     e = launch_step(Q, f64, bgk, ds, s->lay.cpt, false, s->d_desc, s->d_work, s->lay.nwork,
-                    s->klat, s->stream);
+                    s->klat, dn, s->stream);
   } else if (s->pop_pending) {
-    e = launch_step(Q, f64, false, ds, 1, true, s->d_desc, s->d_work, s->lay.nwork, s->klat,
+    e = launch_step(Q, f64, false, ds, 1, true, s->d_desc, s->d_work, s->lay.nwork, s->klat, dn,
                     s->stream);
     s->pop_pending = false;
   } else {
-    e = launch_coef(Q, f64, s->lay.coef_k, ds, 2 * s->lay.mbuf_bytes > kCachedStateBytes,
-                    s->d_desc, s->d_mwork, s->lay.mnwork, s->klat, s->stream);
-    mode = 1;
+    e = launch_coef(Q, f64, s->lay.launch_k, ds, 2 * s->lay.mbuf_bytes > kCachedStateBytes,
+                    s->d_desc, s->d_mwork, s->lay.mnwork, s->klat, dn, s->stream);
   }
-  if (e != hipSuccess) return LBM_EHIP;
-  if (launch_finalize(f64, s->d_desc, s->d_solves, 1, mode, s->stream) != hipSuccess)
-    return LBM_EHIP;
-  return LBM_OK;
+  return e == hipSuccess ? LBM_OK : LBM_EHIP;
 }
 
 // Enqueue the launches of n steps (no host bookkeeping).
 int launch_steps(lbm_solver* s, int64_t n) {
-  if (!s->lay.column) {
-    int rc = LBM_OK;
-    for (int64_t k = 0; k < n && rc == LBM_OK; ++k) rc = launch_one_step(s);
-    return rc;
-  }
   const bool f64 = s->p.storage == LBM_STORE_F64;
   const int Q = (int)s->p.lattice, rows = s->column.rows;
   while (n > 0) {
     // one advance of the step counter for all the launches of a block
-    const int block = (int)std::min<int64_t>(n, kColumnBlock);
+    const int block = (int)std::min<int64_t>(n, kStepBlock);
+    for (int k = 0; !s->lay.column && k < block; ++k) {
+      const int rc = launch_one_step(s, k);
+      if (rc) return rc;
+    }
     int dn = 0;
-    for (int nsub : odd_pieces(block, s->column.max_sub)) {
+    for (int nsub : odd_pieces(s->lay.column ? block : 0, s->column.max_sub)) {
       if (launch_column(Q, f64, s->p.collision == LBM_COLL_BGK, s->p.wall != LBM_WALL_BB,
                         column_shape(Q, s->p.nx, rows, nsub), s->d_desc, nullptr,
                         (s->p.ny + rows - 1) / rows, s->klat, dn, s->stream) != hipSuccess)
@@ -917,7 +937,7 @@ bool capture_steps(lbm_solver* s) {
 }  // namespace
 
 int step_one(lbm_solver* s) {
-  const int rc = launch_one_step(s);
+  const int rc = launch_steps(s, 1);
   if (rc) return rc;
   ++s->steps;
   return LBM_OK;
@@ -1010,15 +1030,10 @@ int lbm_step(lbm_solver* s, int64_t nsteps) {
     if (hipGraphLaunch(s->graph, s->stream) != hipSuccess) return LBM_EHIP;
     s->steps += kGraphSteps;
   }
-  if (s->lay.column && k < nsteps) {
+  if (k < nsteps) {
     const int rc = launch_steps(s, nsteps - k);
     if (rc) return rc;
     s->steps += nsteps - k;
-    k = nsteps;
-  }
-  for (; k < nsteps; ++k) {
-    int rc = step_one(s);
-    if (rc) return rc;
   }
   return LBM_OK;
 }

@@ -1,7 +1,7 @@
 // Batched execution: many solvers (uneven lattices, same velocity set,
-// storage and collision) advanced by one fused stream-collide launch per
-// step over the tiles of every member, plus one finalize launch that reduces
-// each member's wall force.  Members join and leave between steps
+// storage and collision) advanced by one launch per step and kind of member
+// over the tiles of all of them, each launch with a workgroup per member for
+// its wall force.  Members join and leave between steps
 // (continuous batching); a member stops when it reaches its max_steps.
 // Steady-state chunks are replayed from a captured HIP graph.
 #include <hip/hip_runtime.h>
@@ -14,6 +14,11 @@
 
 using namespace lbm;
 
+namespace {
+// kinds of launch of a batch (even: bounce-back, odd: diffuse or Maxwell wall)
+constexpr int kPop = 0, kTiles = 2, kColumns = 4, kGroups = 6;
+}  // namespace
+
 struct lbm_batch {
   hipStream_t stream = nullptr;
   std::vector<lbm_solver*> members;
@@ -21,20 +26,21 @@ struct lbm_batch {
   uint32_t storage = 0, collision = 0;
   int cpt = 1;
   bool have_pop = false;  // some member keeps populations (sets cpt)
-  int coef_k = 0;
+  int coef_k = 0;         // their tile as asked for, and the K of their launch
+  int launch_k = 0;
   bool have_mom = false;  // some member keeps coefficients (sets coef_k)
   // current launch set (members that still have steps to run)
   std::vector<lbm_solver*> active;
   bool dirty = true;
-  // work items in six consecutive groups, one launch each: population kernel
-  // (bounce-back wall, diffuse wall), coefficient kernel and column kernel
-  // (the same); every member runs the kernel instantiation it runs alone
-  int ngroup[6] = {0, 0, 0, 0, 0, 0};
+  // work items in consecutive groups, one launch each: population kernel
+  // (bounce-back wall, diffuse wall), coefficient kernel, column
+  // kernel (the same); every member runs the kernel it runs alone
+  int ngroup[kGroups] = {};
   ColumnPlan column;      // of the column-kernel members
   int column_nx = 0;      // their widest lattice
   int ncolumn = 0;        // how many (the last of the launch set's solve list)
   // coefficient groups whose state streams from HBM (nontemporal stores)
-  bool streaming[4] = {false, false, false, false};
+  bool streaming[kGroups] = {};
   SolveDesc* d_descs = nullptr;
   WorkItem* d_work = nullptr;   // population-kernel items, then coefficient-kernel items
   int32_t* d_solves = nullptr;
@@ -75,7 +81,6 @@ int grow(T** ptr, size_t* cap, size_t need) {
   return LBM_OK;
 }
 
-// Rebuild the device launch set from the members that have steps left.
 // Rebuild the device launch set from the given members.
 int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   if (!b->dirty && act == b->active) return LBM_OK;
@@ -83,9 +88,9 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   b->active = act;
   b->dirty = false;
   std::vector<SolveDesc> descs;
-  // coefficient groups: every member's wall tiles first (they are the slowest
-  // tiles of the launch), then the rest
-  std::vector<WorkItem> group[6], front[6], work;
+  // first every member's force item and (coefficient groups) its wall tiles,
+  // the slowest tiles of the launch, then the rest
+  std::vector<WorkItem> group[kGroups], front[kGroups], work;
   std::vector<int32_t> solves, columns;
   std::vector<int> column_ny;
   b->column_nx = 0;
@@ -95,23 +100,34 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
       column_ny.push_back(s->p.ny);
     }
   if (b->column_nx) b->column = column_plan(b->Q, b->column_nx, column_ny);
-  uint64_t state[4] = {0, 0, 0, 0};  // coefficient state bytes per group
-  for (size_t i = 0; i < act.size(); ++i) {
-    const Layout& lay = act[i]->lay;
-    if (lay.mom) state[2 + (act[i]->p.wall != LBM_WALL_BB)] += 2 * lay.mbuf_bytes;
-  }
+  uint64_t state[kGroups] = {};  // coefficient state bytes per group
+  auto kind = [](const lbm_solver* s) {
+    const Layout& lay = s->lay;
+    return (lay.mom ? kTiles : lay.column ? kColumns : kPop) + (s->p.wall != LBM_WALL_BB);
+  };
+  uint32_t tile = UINT32_MAX;
+  int64_t coef_cells = 0;
+  for (const lbm_solver* s : act)
+    if (s->lay.mom) {
+      state[kind(s)] += 2 * s->lay.mbuf_bytes;
+      tile = std::min(tile, s->p.tile);
+      coef_cells += (int64_t)s->p.nx * s->p.ny;
+    }
+  b->launch_k = coef_cells ? coef_k_for(tile, b->storage == LBM_STORE_F64, coef_cells) : 0;
   for (size_t i = 0; i < act.size(); ++i) {
     descs.push_back(act[i]->desc);
     const Layout& lay = act[i]->lay;
     (lay.column ? columns : solves).push_back((int32_t)i);
-    const int k = (lay.mom ? 2 : lay.column ? 4 : 0) + (act[i]->p.wall != LBM_WALL_BB);
+    const int k = kind(act[i]);
+    if (!lay.column) front[k].push_back(WorkItem{(int32_t)i, kForceTile});
     if (lay.column) {
       const int tiles = (act[i]->p.ny + b->column.rows - 1) / b->column.rows;
       for (int t = 0; t < tiles; ++t) group[k].push_back(WorkItem{(int32_t)i, t});
     } else if (lay.mom) {
+      const CoefGrid g = coef_grid(&act[i]->p, b->launch_k);
       order_coef_tiles(&front[k], &group[k], (int32_t)i,
-                       coef_wall_tiles(&act[i]->p, lay, act[i]->lat.R), lay.mntiles, lay.tiles_x,
-                       state[k] <= kCachedStateBytes);
+                       coef_wall_tiles(&act[i]->p, b->launch_k, act[i]->lat.R), g.ntiles,
+                       g.tiles_x, state[k] <= kCachedStateBytes);
     } else {
       order_tiles(&group[k], (int32_t)i, lay.ntiles,
                   (act[i]->p.nx + lay.cells_per_tile - 1) / lay.cells_per_tile);
@@ -119,13 +135,13 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   }
   b->ncolumn = (int)columns.size();
   solves.insert(solves.end(), columns.begin(), columns.end());
-  for (int k = 0; k < 6; ++k) {
+  for (int k = 0; k < kGroups; ++k) {
     if (!front[k].empty()) {
       join_front(&front[k], group[k]);
       group[k].swap(front[k]);
     }
     b->ngroup[k] = (int)group[k].size();
-    if (k < 4) b->streaming[k] = state[k] > kCachedStateBytes;
+    b->streaming[k] = state[k] > kCachedStateBytes;
     work.insert(work.end(), group[k].begin(), group[k].end());
   }
   if (act.empty()) return LBM_OK;
@@ -172,8 +188,8 @@ int collect_timing(lbm_batch* b) {
 hipError_t launch_columns(lbm_batch* b, int nsub, int dn, KernelEvents ev) {
   const bool f64 = b->storage == LBM_STORE_F64;
   const WorkItem* work = b->d_work;
-  for (int k = 0; k < 4; ++k) work += b->ngroup[k];
-  for (int k = 4; k < 6; ++k) {
+  for (int k = 0; k < kColumns; ++k) work += b->ngroup[k];
+  for (int k = kColumns; k < kGroups; ++k) {
     const int n = b->ngroup[k];
     if (n == 0) continue;
     const hipError_t e =
@@ -186,36 +202,31 @@ hipError_t launch_columns(lbm_batch* b, int nsub, int dn, KernelEvents ev) {
   return hipSuccess;
 }
 
-// The population- and coefficient-kernel launches of one step.
-hipError_t launch_tiles(lbm_batch* b, KernelEvents ev) {
+// The population- and coefficient-kernel launches of one step, dn steps after
+// the last advance of the members' counters.
+hipError_t launch_tiles(lbm_batch* b, int dn, KernelEvents ev) {
   const bool f64 = b->storage == LBM_STORE_F64, bgk = b->collision == LBM_COLL_BGK;
   const KernelLattice& lat = b->active[0]->klat;
   const WorkItem* work = b->d_work;
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < kColumns; ++k) {
     const int n = b->ngroup[k];
     if (n == 0) continue;
     const bool ds = k & 1;
     const hipError_t e =
-        k < 2 ? launch_step(b->Q, f64, bgk, ds, b->cpt, false, b->d_descs, work, n, lat,
-                            b->stream, ev)
-              : launch_coef(b->Q, f64, b->coef_k, ds, b->streaming[k], b->d_descs, work, n, lat,
-                            b->stream, ev);
+        k < kTiles ? launch_step(b->Q, f64, bgk, ds, b->cpt, false, b->d_descs, work, n, lat, dn,
+                                 b->stream, ev)
+                   : launch_coef(b->Q, f64, b->launch_k, ds, b->streaming[k], b->d_descs, work, n,
+                                 lat, dn, b->stream, ev);
     if (e != hipSuccess) return e;
     work += n;
   }
   return hipSuccess;
 }
 
-// The finalize of the members that the column kernel does not serve.
-hipError_t launch_finalizes(lbm_batch* b) {
-  return launch_finalize(b->storage == LBM_STORE_F64, b->d_descs, b->d_solves,
-                         (int)b->active.size() - b->ncolumn, 2, b->stream);
-}
-
 // One step of every member, its step-kernel launches timed.
 int launch_timed(lbm_batch* b) {
   int nlaunch = 0;
-  for (int k = 0; k < 6; ++k) nlaunch += b->ngroup[k] > 0;
+  for (int k = 0; k < kGroups; ++k) nlaunch += b->ngroup[k] > 0;
   if (b->ev_used + 2 > 4096) {
     int rc = collect_timing(b);
     if (rc) return rc;
@@ -225,21 +236,20 @@ int launch_timed(lbm_batch* b) {
   // a single launch records its own start and end; several: events around them
   const KernelEvents own = nlaunch == 1 ? KernelEvents{e0, e1} : KernelEvents{};
   if (nlaunch > 1 && hipEventRecord(e0, b->stream) != hipSuccess) return LBM_EHIP;
-  if (launch_columns(b, 1, 0, own) != hipSuccess || launch_tiles(b, own) != hipSuccess)
+  if (launch_columns(b, 1, 0, own) != hipSuccess || launch_tiles(b, 0, own) != hipSuccess)
     return LBM_EHIP;
   if (nlaunch > 1 && hipEventRecord(e1, b->stream) != hipSuccess) return LBM_EHIP;
-  if (launch_advance(b->d_descs, b->d_solves + (b->active.size() - b->ncolumn), b->ncolumn, 1,
-                     b->stream) != hipSuccess ||
-      launch_finalizes(b) != hipSuccess)
-    return LBM_EHIP;
-  return LBM_OK;
+  return launch_advance(b->d_descs, b->d_solves, (int)b->active.size(), 1, b->stream) ==
+                 hipSuccess
+             ? LBM_OK
+             : LBM_EHIP;
 }
 
 // n steps of the column-kernel members, several per launch.
 int launch_column_steps(lbm_batch* b, int64_t n) {
   const int nfin = (int)b->active.size() - b->ncolumn;
   for (int64_t left = b->ncolumn ? n : 0; left > 0;) {
-    const int block = (int)std::min<int64_t>(left, kColumnBlock);
+    const int block = (int)std::min<int64_t>(left, kStepBlock);
     int dn = 0;
     for (int nsub : odd_pieces(block, b->column.max_sub)) {
       if (launch_columns(b, nsub, dn, KernelEvents{}) != hipSuccess) return LBM_EHIP;
@@ -255,10 +265,15 @@ int launch_column_steps(lbm_batch* b, int64_t n) {
 
 // n steps of the other members, step by step.
 int launch_tile_steps(lbm_batch* b, int64_t n) {
-  const int nfin = (int)b->active.size() - b->ncolumn;
-  for (int64_t k = 0; nfin > 0 && k < n; ++k)
-    if (launch_tiles(b, KernelEvents{}) != hipSuccess || launch_finalizes(b) != hipSuccess)
+  const int count = (int)b->active.size() - b->ncolumn;
+  for (int64_t left = count ? n : 0; left > 0;) {
+    const int block = (int)std::min<int64_t>(left, kStepBlock);
+    for (int k = 0; k < block; ++k)
+      if (launch_tiles(b, k, KernelEvents{}) != hipSuccess) return LBM_EHIP;
+    if (launch_advance(b->d_descs, b->d_solves, count, block, b->stream) != hipSuccess)
       return LBM_EHIP;
+    left -= block;
+  }
   return LBM_OK;
 }
 

@@ -29,14 +29,21 @@
 // (the rules of the population kernel), read from the step's input state; at a
 // plate or a box face with the diffuse or the Maxwell wall those of the
 // diffuse emission (eq. DS) of the link's wall column, mixed with the specular
-// image for the Maxwell wall.  The finalize kernel sums the momentum exchange from the same
+// image for the Maxwell wall.  The force's workgroup sums the momentum exchange from the same
 // input state.
 #include <hip/hip_runtime.h>
 
 #include "device_util.hpp"
+#include "force.hpp"
 #include "lattice.hpp"
 #include "solver.hpp"
 #include "walls.hpp"
+
+// No implicit contraction in this file: every fused multiply-add is written as
+// one, so that a cell's bits do not depend on the unrolled copy, the tile
+// shape or the segment length that computes it, and the host may choose those
+// per launch.
+#pragma clang fp contract(off)
 
 namespace lbm {
 
@@ -341,7 +348,8 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
           H = fmadd(vn, c.cnt, -c.bt);
           K = c.ctt;
         }
-        add(s0 * G + s1 * H + s2 * K, s1 * G + s2 * H + s3 * K, s2 * G + s3 * H + s4 * K, vn);
+        add(fmadd(s0, G, fmadd(s1, H, s2 * K)), fmadd(s1, G, fmadd(s2, H, s3 * K)),
+            fmadd(s2, G, fmadd(s3, H, s4 * K)), vn);
         if (DSW && diffuse && d.sigma != 1.0) {
           // Maxwell wall: the specular share, the population of (t, -v_n) that
           // crossed the wall from the mirror cell's neighbour t cells back
@@ -505,8 +513,8 @@ struct TileCtx {
 };
 
 template <typename S>
-__device__ __forceinline__ TileCtx<S> tile_ctx(const SolveDesc& d) {
-  const int64_t n = kread(&d.state->step);
+__device__ __forceinline__ TileCtx<S> tile_ctx(const SolveDesc& d, int dn) {
+  const int64_t n = kread(&d.state->step) + dn;
   void* const b0 = kread(&d.mbuf[0]);
   void* const b1 = kread(&d.mbuf[1]);
   return {static_cast<const S*>(n & 1 ? b1 : b0), static_cast<S*>(n & 1 ? b0 : b1), n};
@@ -783,12 +791,12 @@ __device__ __forceinline__ void compute_tile(const SolveDesc& d, const TileCtx<S
     else
       inv_rho = S(1) / rho;
     bad |= in && !(rho > S(0) && rho < S(INFINITY));
-    const S uxx = jx * jx * inv_rho, uxy = jx * jy * inv_rho, uyy = jy * jy * inv_rho;
-    const S axx = m.v[3] - drho * th, ayy = m.v[5] - drho * th, axy = m.v[4];
-    const S bxx = axx - om * (axx - uxx);
-    const S bxy = axy - om * (axy - uxy);
-    const S byy = ayy - om * (ayy - uyy);
-    res[k][0] = drho - (bxx + byy) * cc.half_inv_theta;
+    const S ux = jx * inv_rho, uy = jy * inv_rho;
+    const S axx = fmadd(-drho, th, m.v[3]), ayy = fmadd(-drho, th, m.v[5]), axy = m.v[4];
+    const S bxx = fmadd(-om, fmadd(-jx, ux, axx), axx);
+    const S bxy = fmadd(-om, fmadd(-jx, uy, axy), axy);
+    const S byy = fmadd(-om, fmadd(-jy, uy, ayy), ayy);
+    res[k][0] = fmadd(-(bxx + byy), cc.half_inv_theta, drho);
     res[k][1] = jx * inv_th;
     res[k][2] = jy * inv_th;
     res[k][3] = bxx * h2;
@@ -862,6 +870,50 @@ __device__ __forceinline__ void stage_store(Pair<S>* C, const StageRegs<L, S, RB
   }
 }
 
+// LDS of a workgroup: a staged tile, or the force's sums.
+template <class L, typename S, int RB, bool DSW>
+union CoefLds {
+  struct {
+    // staged row r, pair j, column c at C[(3 r + j) HW + c]: the reads of a
+    // pair are 64-bit (128-bit) loads at consecutive lanes
+    Pair<S> C[CoefTile<L, RB>::HH * 3 * CoefTile<L, RB>::HW];
+    WallTable<S, DSW> tab;
+  } tile;
+  ForceLds force;
+};
+
+// Update of one tile by a workgroup.
+template <class L, typename S, int RB, bool DSW>
+__device__ __forceinline__ void tile_update(const SolveDesc& d, const TileCtx<S>& ctx, int tile,
+                                            const KernelLattice& lat, const CoefConst<S>& cc,
+                                            int tid, bool streaming,
+                                            CoefLds<L, S, RB, DSW>& lds) {
+  using T = CoefTile<L, RB>;
+  Pair<S>* const C = lds.tile.C;
+  WallTable<S, DSW>& tab = lds.tile.tab;
+  // wall drive of the step (for the links): a new table entry every step, so
+  // a cache miss; a vector load issued before the staging loads hides it
+  // behind them (a scalar load would share its counter with the LDS reads)
+  int nv = (int)ctx.n;
+  asm volatile("" : "+v"(nv));
+  const double U = as_global(d.drive)[nv].u;
+  if (WallBand<L>(d).meets((tile % d.tiles_x) * kCoefTileW, (tile / d.tiles_x) * T::TH, T::TH) &&
+      tid < 16)
+    fill_wall_table<L>(tab, lat, tid);
+  {
+    // all loads of a thread are issued before the first LDS store, so the
+    // block waits for one memory round trip, not one per staged cell
+    StageRegs<L, S, RB> g;
+    stage_load<L, S, RB>(d, ctx, tile, g, tid);
+    stage_store<L, S, RB>(C, g, tid);
+  }
+  __syncthreads();
+  S res[RB][6];
+  uint32_t valid = 0;
+  compute_tile<L, S, RB, DSW>(d, ctx, tile, C, tab, lat, cc, tid, res, valid, U);
+  store_tile<L, S, RB>(d, ctx, tile, tid, res, valid, streaming);
+}
+
 // DSW: with the diffuse-scattering wall (a separate instantiation, so that
 // the bounce-back kernel carries none of its code).  One workgroup per work
 // item.
@@ -869,82 +921,62 @@ template <class L, typename S, int RB, bool DSW>
 __global__ __launch_bounds__(64 * kCoefWaves) void coef_kernel(const SolveDesc* __restrict__ descs,
                                                    const WorkItem* __restrict__ work,
                                                    KernelLattice lat, CoefConst<S> cc,
-                                                   int streaming) {
-  using T = CoefTile<L, RB>;
-  // staged row r, pair j, column c at C[(3 r + j) HW + c]: the reads of a
-  // pair are 64-bit (128-bit) loads at consecutive lanes
-  __shared__ Pair<S> C[T::HH * 3 * T::HW];
-  __shared__ WallTable<S, DSW> tab;
+                                                   int streaming, int dn) {
+  __shared__ CoefLds<L, S, RB, DSW> lds;
   const WorkItem wi = kread_item(&work[blockIdx.x]);
-  if (wi.tile < 0) return;
+  if (wi.tile == kNoTile) return;
   const SolveDesc& d = descs[wi.solve];
-  const TileCtx<S> ctx = tile_ctx<S>(d);
-  // wall drive of the step (for the links): a new table entry every step, so
-  // a cache miss; a vector load issued before the staging loads hides it
-  // behind them (a scalar load would share its counter with the LDS reads)
-  int nv = (int)ctx.n;
-  asm volatile("" : "+v"(nv));
-  const double U = as_global(d.drive)[nv].u;
-  const int tid = (int)threadIdx.x;
-  if (WallBand<L>(d).meets((wi.tile % d.tiles_x) * kCoefTileW, (wi.tile / d.tiles_x) * T::TH,
-                           T::TH) &&
-      tid < 16)
-    fill_wall_table<L>(tab, lat, tid);
-  {
-    // all loads of a thread are issued before the first LDS store, so the
-    // block waits for one memory round trip, not one per staged cell
-    StageRegs<L, S, RB> g;
-    stage_load<L, S, RB>(d, ctx, wi.tile, g, tid);
-    stage_store<L, S, RB>(C, g, tid);
+  const TileCtx<S> ctx = tile_ctx<S>(d, dn);
+  if (wi.tile == kForceTile) {
+    wall_force<S>(d, true, ctx.n, lds.force);
+    return;
   }
-  __syncthreads();
-  S res[RB][6];
-  uint32_t valid = 0;
-  compute_tile<L, S, RB, DSW>(d, ctx, wi.tile, C, tab, lat, cc, tid, res, valid, U);
-  store_tile<L, S, RB>(d, ctx, wi.tile, tid, res, valid, streaming != 0);
+  tile_update<L, S, RB, DSW>(d, ctx, wi.tile, lat, cc, (int)threadIdx.x, streaming != 0, lds);
 }
 
 template <class L, typename S, int RB>
 static hipError_t launch_rb(bool ds, bool streaming, const SolveDesc* descs, const WorkItem* work,
-                            int nwork, const KernelLattice& lat, hipStream_t stream,
+                            int nwork, const KernelLattice& lat, int dn, hipStream_t stream,
                             const KernelEvents& ev) {
   const CoefConst<S> cc = coef_const<S>(lat);
   const dim3 grid(nwork), block(64 * kCoefWaves);
   const int st = streaming ? 1 : 0;
   if (ds)
-    launch_kernel(coef_kernel<L, S, RB, true>, grid, block, stream, ev, descs, work, lat, cc, st);
+    launch_kernel(coef_kernel<L, S, RB, true>, grid, block, stream, ev, descs, work, lat, cc, st,
+                  dn);
   else
-    launch_kernel(coef_kernel<L, S, RB, false>, grid, block, stream, ev, descs, work, lat, cc, st);
+    launch_kernel(coef_kernel<L, S, RB, false>, grid, block, stream, ev, descs, work, lat, cc, st,
+                  dn);
   return hipGetLastError();
 }
 
 template <class L, typename S>
 static hipError_t launch_coef_t(int k, bool ds, bool streaming, const SolveDesc* descs,
-                                const WorkItem* work, int nwork, const KernelLattice& lat,
+                                const WorkItem* work, int nwork, const KernelLattice& lat, int dn,
                                 hipStream_t stream, const KernelEvents& ev) {
   switch (k) {
     case 1:
-      return launch_rb<L, S, 1>(ds, streaming, descs, work, nwork, lat, stream, ev);
+      return launch_rb<L, S, 1>(ds, streaming, descs, work, nwork, lat, dn, stream, ev);
     case 2:
-      return launch_rb<L, S, 2>(ds, streaming, descs, work, nwork, lat, stream, ev);
+      return launch_rb<L, S, 2>(ds, streaming, descs, work, nwork, lat, dn, stream, ev);
     case 3:
-      return launch_rb<L, S, 3>(ds, streaming, descs, work, nwork, lat, stream, ev);
+      return launch_rb<L, S, 3>(ds, streaming, descs, work, nwork, lat, dn, stream, ev);
     default:
       return hipErrorInvalidValue;
   }
 }
 
 hipError_t launch_coef(int Q, bool f64, int k, bool ds, bool streaming, const SolveDesc* descs,
-                       const WorkItem* work, int nwork, const KernelLattice& lat,
+                       const WorkItem* work, int nwork, const KernelLattice& lat, int dn,
                        hipStream_t stream, KernelEvents ev) {
   if (nwork <= 0) return hipSuccess;
   if (Q == 9)
-    return f64 ? launch_coef_t<D2Q9, double>(k, ds, streaming, descs, work, nwork, lat, stream,
+    return f64 ? launch_coef_t<D2Q9, double>(k, ds, streaming, descs, work, nwork, lat, dn, stream,
                                              ev)
-               : launch_coef_t<D2Q9, float>(k, ds, streaming, descs, work, nwork, lat, stream,
+               : launch_coef_t<D2Q9, float>(k, ds, streaming, descs, work, nwork, lat, dn, stream,
                                             ev);
-  return f64 ? launch_coef_t<D2Q37, double>(k, ds, streaming, descs, work, nwork, lat, stream, ev)
-             : launch_coef_t<D2Q37, float>(k, ds, streaming, descs, work, nwork, lat, stream, ev);
+  return f64 ? launch_coef_t<D2Q37, double>(k, ds, streaming, descs, work, nwork, lat, dn, stream, ev)
+             : launch_coef_t<D2Q37, float>(k, ds, streaming, descs, work, nwork, lat, dn, stream, ev);
 }
 
 }  // namespace lbm

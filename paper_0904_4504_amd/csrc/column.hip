@@ -2,7 +2,7 @@
 //
 // A plate of a few columns (nx <= kColumnMaxNx, periodic in x) has too few
 // cells for a step to be anything but latency: a launch of the population
-// kernel and one of the finalize per step took 6-17 us for 1 k to 40 k cells
+// kernel and one for the force per step took 6-17 us for 1 k to 40 k cells
 // (D2Q9 FP64 4 x 256: 6.5 us, five D2Q37 FP32 4 x 2048: 10.3 us, D2Q37 FP64
 // 4 x 1531 with a diffuse wall: 16.6 us), nearly all of it launch, cold
 // caches and dependent round trips.  Here one workgroup owns `rows` lattice

@@ -11,17 +11,19 @@
 
 namespace lbm {
 
-// ds: some solve of the launch has a diffuse-scattering wall.
+// dn (here and below): steps enqueued since the last advance of the step
+// counters.  ds: some solve of the launch has a diffuse-scattering wall.
 hipError_t launch_step(int Q, bool f64, bool bgk, bool ds, int cpt, bool outm,
                        const SolveDesc* descs, const WorkItem* work, int nwork,
-                       const KernelLattice& lat, hipStream_t stream, KernelEvents ev = {});
+                       const KernelLattice& lat, int dn, hipStream_t stream,
+                       KernelEvents ev = {});
 // ds: some solve of the launch has a diffuse-scattering wall.  streaming:
 // the launch's state exceeds what stays in the last-level cache between
 // steps (its new coefficients then go out with nontemporal stores).
 hipError_t launch_coef(int Q, bool f64, int k, bool ds, bool streaming, const SolveDesc* descs,
-                       const WorkItem* work, int nwork, const KernelLattice& lat,
+                       const WorkItem* work, int nwork, const KernelLattice& lat, int dn,
                        hipStream_t stream, KernelEvents ev = {});
-// nsub steps of narrow lattices, dn steps after the counters' last advance.
+// nsub steps of narrow lattices.
 // work: (solve, tile of `rows` rows) items, or null for nwork tiles of solve 0.
 hipError_t launch_column(int Q, bool f64, bool bgk, bool ds, const ColumnShape& shape,
                          const SolveDesc* descs, const WorkItem* work, int nwork,
@@ -30,8 +32,6 @@ hipError_t launch_column(int Q, bool f64, bool bgk, bool ds, const ColumnShape& 
 // Advance the step counters of the listed solves.
 hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int count, int nsteps,
                           hipStream_t stream);
-hipError_t launch_finalize(bool f64, const SolveDesc* descs, const int32_t* solves, int nsolves,
-                           int mode, hipStream_t stream);
 
 constexpr uint64_t kAlign = 256;
 
@@ -55,10 +55,11 @@ struct Layout {
   uint64_t off_links = 0, off_fcells = 0, off_wcols = 0, off_wlinks = 0;
   uint64_t off_lweights = 0, off_cweights = 0;
   // coefficient representation (mom): six coefficient planes, updated in
-  // tiles of kCoefTileW columns x coef_tile_rows(coef_k) rows
+  // tiles of kCoefTileW columns x coef_tile_rows(K) rows
   bool mom = false;
   bool loadable = true;  // has the population buffer a populations load needs
-  int32_t coef_k = 0, tiles_x = 0, mntiles = 0;
+  int32_t coef_k = 0;  // tile asked for (0: the default's rank among batch members)
+  int32_t launch_k = 0;  // K of a launch over this solve alone
   int64_t mpitch = 0, mks = 0;  // coefficient buffers: row and plane strides (elements)
   uint64_t mbuf_bytes = 0, off_mwork = 0, off_mbuf[2] = {0, 0};
   int32_t nwork = 0, mnwork = 0;  // population-kernel and coefficient-kernel work items
@@ -76,8 +77,15 @@ void order_tiles(std::vector<WorkItem>* out, int32_t solve, int32_t ntiles, int3
 // the same length as order_tiles.
 void order_tiles_banded(std::vector<WorkItem>* out, int32_t solve, int32_t ntiles,
                         int32_t span);
-// Coefficient-kernel tiles of a solve with a wall link (mask over its tiles).
-std::vector<char> coef_wall_tiles(const lbm_params* p, const Layout& lay, int R);
+// Cells per thread of the coefficient kernel for a launch over `cells` cells:
+// the tile asked for, or (0) by the launch's size.
+int coef_k_for(uint32_t tile, bool f64, int64_t cells);
+// Tiles of a solve for K cells per thread, and the mask of those with a wall link.
+struct CoefGrid {
+  int32_t tiles_x = 0, ntiles = 0;
+};
+CoefGrid coef_grid(const lbm_params* p, int K);
+std::vector<char> coef_wall_tiles(const lbm_params* p, int K, int R);
 // The tiles of one coefficient solve: its wall tiles to `front` (they are the
 // slowest of a launch, so they start first), the rest to `rest` in the order
 // of order_tiles_banded (banded) or order_tiles with the wall tiles made
@@ -91,8 +99,8 @@ void order_coef_tiles(std::vector<WorkItem>* front, std::vector<WorkItem>* rest,
 // stream from HBM: the row-interleaved order (adjacent rows in flight on all
 // XCDs at once) and nontemporal stores.
 constexpr uint64_t kCachedStateBytes = (uint64_t)192 << 20;
-// Most column-kernel steps between two advances of the step counter.
-constexpr int kColumnBlock = 1024;
+// Most steps between two advances of the step counters.
+constexpr int kStepBlock = 1024;
 // Split of column-kernel launches: rows per workgroup and the most steps per
 // launch, for lattices of ny rows each and at most nx columns.
 struct ColumnPlan {
@@ -110,7 +118,7 @@ void join_front(std::vector<WorkItem>* front, const std::vector<WorkItem>& rest)
 
 struct lbm_solver;
 // One step of a single solver (population, population-to-coefficient or
-// coefficient kernel, then the finalize); defined in api.cpp.
+// coefficient kernel), its counter advanced; defined in api.cpp.
 int step_one(lbm_solver* s);
 // Steps of a single solver captured into one graph.
 constexpr int kGraphSteps = 32;

@@ -1,6 +1,5 @@
 // Lattice-BGK hot path for gfx950: fused pull-stream + regularized collision
-// with moving-wall bounce-back and FP64 momentum-exchange force, and the
-// per-step force finalisation with lock-in accumulation.
+// with moving-wall bounce-back; a workgroup per solve sums the wall force (wall_force).
 //
 // Method (Sec. 5): advection f_i^adv(x) = f_i(x - v_i) (eq. advection);
 // moments rho, rho u, Pi of f^adv (eq. MME_lbgk); H2 equilibrium (eq.
@@ -33,6 +32,7 @@
 #include <utility>
 
 #include "device_util.hpp"
+#include "force.hpp"
 #include "lattice.hpp"
 #include "solver.hpp"
 #include "walls.hpp"
@@ -43,7 +43,7 @@ namespace lbm {
 // cells of the domain edge or of the body: periodic wrap, bounce-back at the
 // moving wall / body (with the moving-wall term), stationary far wall or
 // rest-equilibrium far field (delta f = 0).  The wall force is computed from
-// the same input state by the finalize kernel.  DSW: the plate's moving wall
+// the same input state (wall_force).  DSW: the plate's moving wall
 // may be diffuse (else it is bounce-back).
 template <class L, typename S, bool DSW, int q>
 __device__ __forceinline__ S pull_edge(const SolveDesc& d, const S* __restrict__ fin, int x,
@@ -435,203 +435,39 @@ __device__ __forceinline__ void update_cell(const SolveDesc& d, const S* __restr
 template <class L, typename S, bool BGK, bool DSW, int BS, bool OUTM>
 __global__ __launch_bounds__(BS) void step_kernel(const SolveDesc* __restrict__ descs,
                                                   const WorkItem* __restrict__ work,
-                                                  KernelLattice lat) {
+                                                  KernelLattice lat, int dn) {
+  __shared__ ForceLds lds;
   // The host orders the work list so that workgroup b runs on XCD b % 8 with
   // whole lattice rows per XCD (see order_tiles); padding items are no-ops.
   const WorkItem wi = work[blockIdx.x];
-  if (wi.tile < 0) return;
+  if (wi.tile == kNoTile) return;
   const SolveDesc& d = descs[wi.solve];
-  const int64_t n = d.state->step;
+  const int64_t n = d.state->step + dn;
+  if (wi.tile == kForceTile) {
+    wall_force<S>(d, false, n, lds);
+    return;
+  }
   const S* __restrict__ fin = static_cast<const S*>(d.buf[n & 1]);
   S* __restrict__ fout = static_cast<S*>(OUTM ? d.mbuf[(n & 1) ^ 1] : d.buf[(n & 1) ^ 1]);
   update_cell<L, S, BGK, DSW, OUTM>(d, fin, fout, n, wi.tile * BS + (int)threadIdx.x, lat);
 }
 
-// One workgroup per solve.  Wall force of step n by momentum exchange (Sec.
-// 2 force F_f; eq. BB): every bounce-back link carries -v_i (f_opp(x_p) +
-// f_i^adv(x)) = -v_i (2 f_opp(x_p) + 2 w_i rho0 (v_i.U_w)/theta) (+ the rest
-// state), so F_n = F_static + K_ladd U_w(n) + sum over links of the reflected
-// populations of step n's input state, read here from the step's input buffer
-// (untouched by the step) and summed in a fixed order in FP64.  At a diffuse
-// wall (eq. DS) f_i^adv is the wall's emission, which depends on the same
-// input state only through the crossing mass of each column.  Then append
-// F_n to the history ring, accumulate the lock-in sums when n lies in the
-// window, and advance the step counter.
-// mode 0: the step read populations; 1: coefficients; 2: per solve,
-// coefficients if the solve keeps them (batches).
-template <typename S>
-__device__ void finalize_solve(const SolveDesc& d, int mode) {
-  SolveState* st = d.state;
-  const int64_t n = st->step;
-  const bool coeffs = mode == 1 || (mode == 2 && d.mbuf[0] != nullptr);
-  // the epilogue's loads (drive entry, lock-in sums), issued before the
-  // force sums so that their latency overlaps them
-  const bool in_window = n >= d.lockin_first && n < d.lockin_first + d.lockin_count;
-  Drive dr{};
-  double lk[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  if (threadIdx.x == 0) {
-    dr = d.drive[n];
-    if (in_window)
-      for (int k = 0; k < 6; ++k) lk[k] = st->lockin[k];
-  }
-  double fx = 0.0, fy = 0.0, fm = 0.0;
-  if (!coeffs && d.nwlinks > 0) {
-    // box with diffuse or Maxwell faces: every link's arrival as the step
-    // kernel formed it -- the column's diffuse emission from the column's
-    // crossing mass (first pass), mixed with the specular image; corner links
-    // bounce back -- and the momentum exchange -v_l (f_partner + f_arrival)
-    const S* __restrict__ f = static_cast<const S*>(n & 1 ? d.buf[1] : d.buf[0]);
-    __shared__ double cmass[kMaxWallCols];
-    for (int c = threadIdx.x; c < d.nwcols; c += kBlock) {
-      const WallCol col = d.wcols[c];
-      double m = 0.0;
-      for (int k = 0; k < col.count; ++k) m += (double)f[d.wlinks[col.first + k].off_partner];
-      cmass[c] = m;
-    }
-    __syncthreads();
-    const double U = d.drive[n].u;
-    const double ladd = d.ladd_scale * U;
-    for (int i = threadIdx.x; i < d.nwlinks; i += kBlock) {
-      const WallLink l = d.wlinks[i];
-      const double fp = (double)f[l.off_partner];
-      double a;
-      if (l.col < 0) {
-        a = fp + l.w * l.vx * ladd;
-      } else {
-        a = ds_box_arrival(d.wcols[l.col], d.rho0, U, cmass[l.col], l.w, l.vx, d.theta);
-        if (d.sigma != 1.0) {
-          const double sp = (double)f[l.off_spec] + (l.normal ? l.w * l.vx * ladd : 0.0);
-          a = d.sigma * a + (1.0 - d.sigma) * sp;
-        }
-      }
-      fx -= l.vx * (fp + a);
-      fy -= l.vy * (fp + a);
-    }
-  } else if (coeffs && d.nwlinks > 0) {
-    // the same two passes on the H2 coefficients of the input state: a
-    // population of velocity v at cell o is w_v (a0 + vx bx + vy by + vx^2 cxx
-    // + vx vy cxy + vy^2 cyy)(o)
-    const S* __restrict__ c = static_cast<const S*>(d.mbuf[n & 1]);
-    const int64_t ks = d.mks;
-    auto pop = [&](int64_t o, double w, double vx, double vy) {
-      return w * ((double)c[o] + vx * (double)c[ks + o] + vy * (double)c[2 * ks + o] +
-                  vx * vx * (double)c[3 * ks + o] + vx * vy * (double)c[4 * ks + o] +
-                  vy * vy * (double)c[5 * ks + o]);
-    };
-    __shared__ double cmass[kMaxWallCols];
-    for (int k = threadIdx.x; k < d.nwcols; k += kBlock) {
-      const WallCol& col = d.wcols[k];
-      double m = 0.0;
-      for (int r = 0; r < 3; ++r)
-        for (int j = 0; j < 6; ++j) m += col.mc[r][j] * (double)c[j * ks + col.cell[r]];
-      cmass[k] = m;
-    }
-    __syncthreads();
-    const double U = d.drive[n].u;
-    const double ladd = d.ladd_scale * U;
-    for (int i = threadIdx.x; i < d.nwlinks; i += kBlock) {
-      const WallLink l = d.wlinks[i];
-      const double fp = pop(l.cell_partner, l.w, -l.vx, -l.vy);
-      double a;
-      if (l.col < 0) {
-        a = fp + l.w * l.vx * ladd;
-      } else {
-        a = ds_box_arrival(d.wcols[l.col], d.rho0, U, cmass[l.col], l.w, l.vx, d.theta);
-        if (d.sigma != 1.0) {
-          const double sp = l.normal ? pop(l.cell_spec, l.w, -l.vx, l.vy) + l.w * l.vx * ladd
-                                     : pop(l.cell_spec, l.w, l.vx, -l.vy);
-          a = d.sigma * a + (1.0 - d.sigma) * sp;
-        }
-      }
-      fx -= l.vx * (fp + a);
-      fy -= l.vy * (fp + a);
-    }
-  } else if (coeffs) {
-    const S* __restrict__ c = static_cast<const S*>(d.mbuf[n & 1]);
-    const int64_t ks = d.mks;
-    for (int i = threadIdx.x; i < d.nfcells; i += kBlock) {
-      const ForceCell& cell = d.fcells[i];
-      const CellWeights& fc = d.cweights[cell.pat];
-#pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        const double v = (double)c[k * ks + cell.off];
-        fx += fc.wx[k] * v;
-        fy += fc.wy[k] * v;
-        fm += fc.wm[k] * v;
-      }
-    }
-  } else {
-    const S* __restrict__ f = static_cast<const S*>(n & 1 ? d.buf[1] : d.buf[0]);
-#pragma unroll 4
-    for (int i = threadIdx.x; i < d.nlinks; i += kBlock) {
-      const ForceLink& link = d.links[i];
-      const LinkWeights& l = d.lweights[link.pat];
-      const double v = (double)f[link.off];
-      fx += l.wx * v;
-      fy += l.wy * v;
-      fm += l.wm * v;
-    }
-  }
-  __shared__ double red[3][kBlock / 64];
-  fx = wave_sum(fx);
-  fy = wave_sum(fy);
-  fm = wave_sum(fm);
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    red[0][wave] = fx;
-    red[1][wave] = fy;
-    red[2][wave] = fm;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double sx = 0.0, sy = 0.0, sm = 0.0;
-#pragma unroll
-    for (int k = 0; k < kBlock / 64; ++k) {
-      sx += red[0][k];
-      sy += red[1][k];
-      sm += red[2][k];
-    }
-    fx = d.fstatic[0] + d.kladd[0] * dr.u + sx;
-    fy = d.fstatic[1] + d.kladd[1] * dr.u + sy;
-    if (d.wall == WALL_DS && d.geom == GEOM_PLATE) add_emission_force(wall_emission(d), dr.u, sm, &fx, &fy);
-    const int64_t h = n % d.hist_cap;
-    d.hist[2 * h] = fx;
-    d.hist[2 * h + 1] = fy;
-    if (in_window) {
-      st->lockin[0] = lk[0] + fx * dr.s;
-      st->lockin[1] = lk[1] + fx * dr.c;
-      st->lockin[2] = lk[2] + fx;
-      st->lockin[3] = lk[3] + fy * dr.s;
-      st->lockin[4] = lk[4] + fy * dr.c;
-      st->lockin[5] = lk[5] + fy;
-    }
-    st->step = n + 1;
-  }
-}
-
-template <typename S>
-__global__ __launch_bounds__(kBlock) void finalize_kernel(const SolveDesc* __restrict__ descs,
-                                                          const int32_t* __restrict__ solves,
-                                                          int mode) {
-  finalize_solve<S>(descs[solves[blockIdx.x]], mode);
-}
-
 template <class L, typename S, bool BGK, bool DSW>
 static hipError_t launch_step_t(int cpt, const SolveDesc* descs, const WorkItem* work, int nwork,
-                                const KernelLattice& lat, hipStream_t stream,
+                                const KernelLattice& lat, int dn, hipStream_t stream,
                                 const KernelEvents& ev) {
   switch (cpt) {
     case 1:
       launch_kernel(step_kernel<L, S, BGK, DSW, kBlock, false>, dim3(nwork), dim3(kBlock), stream,
-                    ev, descs, work, lat);
+                    ev, descs, work, lat, dn);
       break;
     case 2:
       launch_kernel(step_kernel<L, S, BGK, DSW, 2 * kBlock, false>, dim3(nwork),
-                    dim3(2 * kBlock), stream, ev, descs, work, lat);
+                    dim3(2 * kBlock), stream, ev, descs, work, lat, dn);
       break;
     case 4:
       launch_kernel(step_kernel<L, S, BGK, DSW, 4 * kBlock, false>, dim3(nwork),
-                    dim3(4 * kBlock), stream, ev, descs, work, lat);
+                    dim3(4 * kBlock), stream, ev, descs, work, lat, dn);
       break;
     default:
       return hipErrorInvalidValue;
@@ -641,47 +477,35 @@ static hipError_t launch_step_t(int cpt, const SolveDesc* descs, const WorkItem*
 
 template <class L, typename S>
 static hipError_t launch_step_l(bool bgk, bool ds, int cpt, bool outm, const SolveDesc* descs,
-                                const WorkItem* work, int nwork, const KernelLattice& lat,
+                                const WorkItem* work, int nwork, const KernelLattice& lat, int dn,
                                 hipStream_t stream, const KernelEvents& ev) {
   if (outm) {
     // one step of a solver kept in coefficients: any wall
     if (bgk || cpt != 1) return hipErrorInvalidValue;
     launch_kernel(step_kernel<L, S, false, true, kBlock, true>, dim3(nwork), dim3(kBlock), stream,
-                  ev, descs, work, lat);
+                  ev, descs, work, lat, dn);
     return hipGetLastError();
   }
   if (bgk)
-    return ds ? launch_step_t<L, S, true, true>(cpt, descs, work, nwork, lat, stream, ev)
-              : launch_step_t<L, S, true, false>(cpt, descs, work, nwork, lat, stream, ev);
-  return ds ? launch_step_t<L, S, false, true>(cpt, descs, work, nwork, lat, stream, ev)
-            : launch_step_t<L, S, false, false>(cpt, descs, work, nwork, lat, stream, ev);
+    return ds ? launch_step_t<L, S, true, true>(cpt, descs, work, nwork, lat, dn, stream, ev)
+              : launch_step_t<L, S, true, false>(cpt, descs, work, nwork, lat, dn, stream, ev);
+  return ds ? launch_step_t<L, S, false, true>(cpt, descs, work, nwork, lat, dn, stream, ev)
+            : launch_step_t<L, S, false, false>(cpt, descs, work, nwork, lat, dn, stream, ev);
 }
 
 hipError_t launch_step(int Q, bool f64, bool bgk, bool ds, int cpt, bool outm,
                        const SolveDesc* descs, const WorkItem* work, int nwork,
-                       const KernelLattice& lat, hipStream_t stream, KernelEvents ev) {
+                       const KernelLattice& lat, int dn, hipStream_t stream, KernelEvents ev) {
   if (nwork <= 0) return hipSuccess;
   if (Q == 9)
-    return f64 ? launch_step_l<D2Q9, double>(bgk, ds, cpt, outm, descs, work, nwork, lat, stream,
-                                             ev)
-               : launch_step_l<D2Q9, float>(bgk, ds, cpt, outm, descs, work, nwork, lat, stream,
-                                            ev);
-  return f64 ? launch_step_l<D2Q37, double>(bgk, ds, cpt, outm, descs, work, nwork, lat, stream,
-                                            ev)
-             : launch_step_l<D2Q37, float>(bgk, ds, cpt, outm, descs, work, nwork, lat, stream,
-                                           ev);
-}
-
-hipError_t launch_finalize(bool f64, const SolveDesc* descs, const int32_t* solves, int nsolves,
-                           int mode, hipStream_t stream) {
-  if (nsolves <= 0) return hipSuccess;
-  if (f64)
-    hipLaunchKernelGGL(finalize_kernel<double>, dim3(nsolves), dim3(kBlock), 0, stream, descs,
-                       solves, mode);
-  else
-    hipLaunchKernelGGL(finalize_kernel<float>, dim3(nsolves), dim3(kBlock), 0, stream, descs,
-                       solves, mode);
-  return hipGetLastError();
+    return f64 ? launch_step_l<D2Q9, double>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,
+                                             stream, ev)
+               : launch_step_l<D2Q9, float>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,
+                                            stream, ev);
+  return f64 ? launch_step_l<D2Q37, double>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,
+                                              stream, ev)
+             : launch_step_l<D2Q37, float>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,
+                                           stream, ev);
 }
 
 }  // namespace lbm

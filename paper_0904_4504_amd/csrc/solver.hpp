@@ -160,10 +160,12 @@ struct SolveDesc {
   const WallCol* wcols;      // [nwcols]
   const WallLink* wlinks;    // [nwlinks]
   int32_t nwcols, nwlinks;
-  double theta;              // lattice theta (the finalize's diffuse emission)
+  double theta;              // lattice theta (the force's diffuse emission)
 };
 
-// One entry of the launch work list: a tile of one solve.
+// One entry of the launch work list: a tile of one solve, nothing (kNoTile), or
+// the wall force of the solve (kForceTile).
+constexpr int32_t kNoTile = -1, kForceTile = -2;
 struct WorkItem {
   int32_t solve;
   int32_t tile;

@@ -49,3 +49,35 @@ def test_wall_edges(P, name, storage, wall, sigma):  # noqa: F811
     fscale = max(np.max(np.abs(ox)), np.max(np.abs(oy)))
     assert np.max(np.abs(fx - ox)) <= tol * fscale
     assert np.max(np.abs(fy - oy)) <= tol * fscale
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("wall", ["bb", "ds"])
+def test_launch_size_does_not_change_bits(P, storage, wall):  # noqa: F811
+    """A small box alone (one row per wavefront), with each explicit tile, and
+    beside a member large enough for the launch to take more rows: the same
+    forces and fields bit for bit."""
+    import torch
+    n = 40
+    small = W.Solve(Q=37, geometry=W.BOX, far=W.FAR_EQ, nx=90, ny=75, tau=0.8,
+                    omega=2 * math.pi / 40, box=(40, 30, 9, 11), nsteps=n, window_first=0,
+                    window_count=n, storage=storage, wall=wall)
+    large = W.Solve(Q=37, geometry=W.PLATE, far=W.FAR_EQ, nx=1000, ny=800, tau=0.7,
+                    omega=2 * math.pi / 40, nsteps=n, window_first=0, window_count=n,
+                    storage=storage)
+    out = []
+    for tile in (0, 1, 2, 3):
+        with P.Solver(P.params_from_solve(small, tile=tile)) as sv:
+            sv.step(n)
+            out.append((*sv.force_history(), sv.get_deviations()))
+    stream = torch.cuda.Stream()
+    with P.Solver(P.params_from_solve(small), stream=stream) as a, \
+            P.Solver(P.params_from_solve(large, loads=False), stream=stream) as b, \
+            P.Batch(stream) as batch:
+        batch.add(a)
+        batch.add(b)
+        batch.step(33)
+        batch.step(n - 33)
+        out.append((*a.force_history(), a.get_deviations()))
+    for o in out[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(o, out[0]))
