@@ -100,7 +100,7 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
       column_ny.push_back(s->p.ny);
     }
   if (b->column_nx) b->column = column_plan(b->Q, b->column_nx, column_ny);
-  uint64_t state[kGroups] = {};  // coefficient state bytes per group
+  uint64_t state[kGroups] = {};  // state bytes per group
   auto kind = [](const lbm_solver* s) {
     const Layout& lay = s->lay;
     return (lay.mom ? kTiles : lay.column ? kColumns : kPop) + (s->p.wall != LBM_WALL_BB);
@@ -108,7 +108,9 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   uint32_t tile = UINT32_MAX;
   int64_t coef_cells = 0;
   for (const lbm_solver* s : act)
-    if (s->lay.mom) {
+    if (!s->lay.mom) {
+      state[kind(s)] += 2 * s->lay.buf_bytes;
+    } else {
       state[kind(s)] += 2 * s->lay.mbuf_bytes;
       tile = std::min(tile, s->p.tile);
       coef_cells += (int64_t)s->p.nx * s->p.ny;
@@ -130,7 +132,7 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
                        g.tiles_x, state[k] <= kCachedStateBytes);
     } else {
       order_tiles(&group[k], (int32_t)i, lay.ntiles,
-                  (act[i]->p.nx + lay.cells_per_tile - 1) / lay.cells_per_tile);
+                  (lay.mw + lay.cells_per_tile - 1) / lay.cells_per_tile);
     }
   }
   b->ncolumn = (int)columns.size();
@@ -141,7 +143,7 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
       group[k].swap(front[k]);
     }
     b->ngroup[k] = (int)group[k].size();
-    b->streaming[k] = state[k] > kCachedStateBytes;
+    b->streaming[k] = state[k] > (k < kTiles ? kCachedPopBytes : kCachedStateBytes);
     work.insert(work.end(), group[k].begin(), group[k].end());
   }
   if (act.empty()) return LBM_OK;
@@ -214,7 +216,7 @@ hipError_t launch_tiles(lbm_batch* b, int dn, KernelEvents ev) {
     const bool ds = k & 1;
     const hipError_t e =
         k < kTiles ? launch_step(b->Q, f64, bgk, ds, b->cpt, false, b->d_descs, work, n, lat, dn,
-                                 b->stream, ev)
+                                 b->streaming[k], b->stream, ev)
                    : launch_coef(b->Q, f64, b->launch_k, ds, b->streaming[k], b->d_descs, work, n,
                                  lat, dn, b->stream, ev);
     if (e != hipSuccess) return e;

@@ -15,7 +15,7 @@ namespace lbm {
 // counters.  ds: some solve of the launch has a diffuse-scattering wall.
 hipError_t launch_step(int Q, bool f64, bool bgk, bool ds, int cpt, bool outm,
                        const SolveDesc* descs, const WorkItem* work, int nwork,
-                       const KernelLattice& lat, int dn, hipStream_t stream,
+                       const KernelLattice& lat, int dn, bool streaming, hipStream_t stream,
                        KernelEvents ev = {});
 // ds: some solve of the launch has a diffuse-scattering wall.  streaming:
 // the launch's state exceeds what stays in the last-level cache between
@@ -51,6 +51,7 @@ struct Layout {
   bool column = false;  // stepped by the column kernel
   int64_t pitch = 0, qs = 0, ys = 0, buf_elems = 0;
   int32_t ntiles = 0, cells_per_tile = kBlock, cpt = 1;
+  int32_t mw = 0;  // population kernel: cells per row of its tiles
   int32_t nlinks = 0, nfcells = 0, nwcols = 0, nwlinks = 0, nlweights = 0, ncweights = 0;
   uint64_t off_links = 0, off_fcells = 0, off_wcols = 0, off_wlinks = 0;
   uint64_t off_lweights = 0, off_cweights = 0;
@@ -99,6 +100,11 @@ void order_coef_tiles(std::vector<WorkItem>* front, std::vector<WorkItem>* rest,
 // stream from HBM: the row-interleaved order (adjacent rows in flight on all
 // XCDs at once) and nontemporal stores.
 constexpr uint64_t kCachedStateBytes = (uint64_t)192 << 20;
+// The same line for the stores of the population kernel (two populations
+// buffers of all the launch's members; stores plain against nontemporal: 209 MB
+// 32.2 against 40.3 us per step, 310 MB 57.1 against 57.3, 931 MB 167 against
+// 160).
+constexpr uint64_t kCachedPopBytes = (uint64_t)256 << 20;
 // Most steps between two advances of the step counters.
 constexpr int kStepBlock = 1024;
 // Split of column-kernel launches: rows per workgroup and the most steps per

@@ -280,13 +280,15 @@ __device__ __forceinline__ double box_cross_mass(const SolveDesc& d, const S* __
 template <class L, typename S, bool BGK, bool DSW, bool OUTM>
 __device__ __forceinline__ void update_cell(const SolveDesc& d, const S* __restrict__ fin,
                                             S* __restrict__ fout, int64_t n, int c,
-                                            const KernelLattice& lat) {
+                                            const KernelLattice& lat, bool streaming) {
   constexpr int Q = L::Q, R = L::R;
   const int nx = d.nx, ny = d.ny;
   const int64_t qs = d.qs, ys = d.ys;
-  const bool active = c < d.ncells;
-  const int y = active ? c / nx : 0;
-  const int x = active ? c - y * nx : 0;
+  // cell c of rows of d.mw cells (those past the lattice's columns idle)
+  const int cy = c / d.mw, cx = c - cy * d.mw;
+  const bool active = cy < ny && cx < nx;
+  const int y = active ? cy : 0;
+  const int x = active ? cx : 0;
   const bool is_box = d.geom == GEOM_BOX;
   const bool solid = is_box && x >= d.bx0 && x < d.bx1 && y >= d.by0 && y < d.by1;
   bool interior = x >= R && x < nx - R && y >= R && y < ny - R;
@@ -407,8 +409,7 @@ __device__ __forceinline__ void update_cell(const SolveDesc& d, const S* __restr
         if constexpr (vx != 0) p += S(vx) * bx + S(vx * vx) * cxx;
         if constexpr (vy != 0) p += S(vy) * by + S(vy * vy) * cyy;
         if constexpr (vx * vy != 0) p += S(vx * vy) * cxy;
-        // output is not re-read in this step: stream it past the caches
-        __builtin_nontemporal_store((S)lat.w[L::orbit[q]] * p, &fout[q * qs + idx]);
+        f[q] = (S)lat.w[L::orbit[q]] * p;
       });
     }
   } else {
@@ -416,7 +417,7 @@ __device__ __forceinline__ void update_cell(const SolveDesc& d, const S* __restr
     const S a0 = drho - (uxx + uyy) * (S(0.5) * inv_th);
     const S bx = jx * inv_th, by = jy * inv_th;
     const S cxx = uxx * h2, cxy = uxy * (S(2) * h2), cyy = uyy * h2;
-    if (fluid) static_for<0, Q>([&](auto qc) {
+    static_for<0, Q>([&](auto qc) {
       constexpr int q = decltype(qc)::value;
       constexpr int vx = L::vx[q], vy = L::vy[q];
       S p = a0;
@@ -424,18 +425,36 @@ __device__ __forceinline__ void update_cell(const SolveDesc& d, const S* __restr
       if constexpr (vy != 0) p += S(vy) * by + S(vy * vy) * cyy;
       if constexpr (vx * vy != 0) p += S(vx * vy) * cxy;
       const S feq = (S)lat.w[L::orbit[q]] * p;
-      __builtin_nontemporal_store(f[q] + om * (feq - f[q]), &fout[q * qs + idx]);
+      f[q] = f[q] + om * (feq - f[q]);
     });
+  }
+  if constexpr (!OUTM) {
+    // a state that stays in the last-level cache between steps is stored
+    // through it, a streaming one past the caches (kCachedPopBytes)
+    if (fluid) {
+      if (streaming)
+        static_for<0, Q>([&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          __builtin_nontemporal_store(f[q], &fout[q * qs + idx]);
+        });
+      else
+        static_for<0, Q>([&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          // (empty, but keeps the compiler from merging the two forms)
+          asm volatile("" ::: "memory");
+          fout[q * qs + idx] = f[q];
+        });
+    }
   }
 }
 
-// One workgroup of BS threads per tile of BS consecutive cells (row-major),
-// one cell per thread.  The diffuse wall is a separate instantiation (DSW), so
+// One workgroup of BS threads per tile of BS consecutive cells (row-major, rows
+// of d.mw cells), one cell per thread.  The diffuse wall is a separate instantiation (DSW), so
 // that the bounce-back kernel carries none of its code and registers.
 template <class L, typename S, bool BGK, bool DSW, int BS, bool OUTM>
 __global__ __launch_bounds__(BS) void step_kernel(const SolveDesc* __restrict__ descs,
                                                   const WorkItem* __restrict__ work,
-                                                  KernelLattice lat, int dn) {
+                                                  KernelLattice lat, int dn, int streaming) {
   __shared__ ForceLds lds;
   // The host orders the work list so that workgroup b runs on XCD b % 8 with
   // whole lattice rows per XCD (see order_tiles); padding items are no-ops.
@@ -449,25 +468,27 @@ __global__ __launch_bounds__(BS) void step_kernel(const SolveDesc* __restrict__ 
   }
   const S* __restrict__ fin = static_cast<const S*>(d.buf[n & 1]);
   S* __restrict__ fout = static_cast<S*>(OUTM ? d.mbuf[(n & 1) ^ 1] : d.buf[(n & 1) ^ 1]);
-  update_cell<L, S, BGK, DSW, OUTM>(d, fin, fout, n, wi.tile * BS + (int)threadIdx.x, lat);
+  update_cell<L, S, BGK, DSW, OUTM>(d, fin, fout, n, wi.tile * BS + (int)threadIdx.x, lat,
+                                    streaming != 0);
 }
 
 template <class L, typename S, bool BGK, bool DSW>
 static hipError_t launch_step_t(int cpt, const SolveDesc* descs, const WorkItem* work, int nwork,
-                                const KernelLattice& lat, int dn, hipStream_t stream,
+                                const KernelLattice& lat, int dn, bool streaming,
+                                hipStream_t stream,
                                 const KernelEvents& ev) {
   switch (cpt) {
     case 1:
       launch_kernel(step_kernel<L, S, BGK, DSW, kBlock, false>, dim3(nwork), dim3(kBlock), stream,
-                    ev, descs, work, lat, dn);
+                    ev, descs, work, lat, dn, (int)streaming);
       break;
     case 2:
       launch_kernel(step_kernel<L, S, BGK, DSW, 2 * kBlock, false>, dim3(nwork),
-                    dim3(2 * kBlock), stream, ev, descs, work, lat, dn);
+                    dim3(2 * kBlock), stream, ev, descs, work, lat, dn, (int)streaming);
       break;
     case 4:
       launch_kernel(step_kernel<L, S, BGK, DSW, 4 * kBlock, false>, dim3(nwork),
-                    dim3(4 * kBlock), stream, ev, descs, work, lat, dn);
+                    dim3(4 * kBlock), stream, ev, descs, work, lat, dn, (int)streaming);
       break;
     default:
       return hipErrorInvalidValue;
@@ -478,34 +499,39 @@ static hipError_t launch_step_t(int cpt, const SolveDesc* descs, const WorkItem*
 template <class L, typename S>
 static hipError_t launch_step_l(bool bgk, bool ds, int cpt, bool outm, const SolveDesc* descs,
                                 const WorkItem* work, int nwork, const KernelLattice& lat, int dn,
-                                hipStream_t stream, const KernelEvents& ev) {
+                                bool streaming, hipStream_t stream, const KernelEvents& ev) {
   if (outm) {
     // one step of a solver kept in coefficients: any wall
     if (bgk || cpt != 1) return hipErrorInvalidValue;
     launch_kernel(step_kernel<L, S, false, true, kBlock, true>, dim3(nwork), dim3(kBlock), stream,
-                  ev, descs, work, lat, dn);
+                  ev, descs, work, lat, dn, (int)streaming);
     return hipGetLastError();
   }
   if (bgk)
-    return ds ? launch_step_t<L, S, true, true>(cpt, descs, work, nwork, lat, dn, stream, ev)
-              : launch_step_t<L, S, true, false>(cpt, descs, work, nwork, lat, dn, stream, ev);
-  return ds ? launch_step_t<L, S, false, true>(cpt, descs, work, nwork, lat, dn, stream, ev)
-            : launch_step_t<L, S, false, false>(cpt, descs, work, nwork, lat, dn, stream, ev);
+    return ds ? launch_step_t<L, S, true, true>(cpt, descs, work, nwork, lat, dn, streaming,
+                                                stream, ev)
+              : launch_step_t<L, S, true, false>(cpt, descs, work, nwork, lat, dn, streaming,
+                                                 stream, ev);
+  return ds ? launch_step_t<L, S, false, true>(cpt, descs, work, nwork, lat, dn, streaming,
+                                               stream, ev)
+            : launch_step_t<L, S, false, false>(cpt, descs, work, nwork, lat, dn, streaming,
+                                                stream, ev);
 }
 
 hipError_t launch_step(int Q, bool f64, bool bgk, bool ds, int cpt, bool outm,
                        const SolveDesc* descs, const WorkItem* work, int nwork,
-                       const KernelLattice& lat, int dn, hipStream_t stream, KernelEvents ev) {
+                       const KernelLattice& lat, int dn, bool streaming,
+                                hipStream_t stream, KernelEvents ev) {
   if (nwork <= 0) return hipSuccess;
   if (Q == 9)
     return f64 ? launch_step_l<D2Q9, double>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,
-                                             stream, ev)
+                                             streaming, stream, ev)
                : launch_step_l<D2Q9, float>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,
-                                            stream, ev);
+                                            streaming, stream, ev);
   return f64 ? launch_step_l<D2Q37, double>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,
-                                              stream, ev)
+                                              streaming, stream, ev)
              : launch_step_l<D2Q37, float>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,
-                                           stream, ev);
+                                           streaming, stream, ev);
 }
 
 }  // namespace lbm

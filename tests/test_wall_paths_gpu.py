@@ -81,3 +81,30 @@ def test_launch_size_does_not_change_bits(P, storage, wall):  # noqa: F811
         out.append((*a.force_history(), a.get_deviations()))
     for o in out[1:]:
         assert all(np.array_equal(x, y) for x, y in zip(o, out[0]))
+
+
+@pytest.mark.parametrize("nx", [64, 102, 103, 128, 161])
+@pytest.mark.parametrize("geom,wall", [(W.BOX, "bb"), (W.PLATE, "ds"), (W.PERIODIC, "bb")])
+def test_population_rows(P, nx, geom, wall):  # noqa: F811
+    """Populations at widths on both sides of the line where the kernel's tiles
+    cover rows padded to whole wavefronts: 12 FP64 steps against the long-double
+    oracle within 1e-12, the same bits with every tile."""
+    n, ny = 12, 29
+    s = W.Solve(Q=37, geometry=geom, far=W.FAR_WALL if geom == W.PLATE else W.FAR_EQ, nx=nx,
+                ny=ny, tau=0.9, omega=2 * math.pi / 32,
+                box=(25, 9, 12, 8) if geom == W.BOX else (0, 0, 0, 0), nsteps=n,
+                window_first=0, window_count=n, storage="f64", collision="bgk", wall=wall)
+    v, w, th = P.lattice(37)
+    f0 = _f0(s, w, seed=5, amp=1e-3)
+    fx, fy, z, f = _gpu(P, s, f0, state=True, repr_=1)
+    ox, oy, of = O.run(_oracle_params(s), n, f0=f0, want_state=True, variant="ld")
+    x0, y0, lx, ly = s.box
+    mask = np.ones((ny, nx))
+    mask[y0:y0 + ly, x0:x0 + lx] = 0
+    rest = w[:, None, None]
+    assert np.max(np.abs((f - of) * mask)) <= \
+        1e-12 * np.max(np.abs((of - rest) * mask)) + 2 * np.spacing(np.max(w))
+    assert np.max(np.abs(fx - ox)) <= 1e-12 * max(np.max(np.abs(ox)), np.max(np.abs(oy)), 1e-3)
+    for tile in (2, 4):
+        gx, gy, _, g = _gpu(P, s, f0, state=True, repr_=1, tile=tile)
+        assert np.array_equal(g, f) and np.array_equal(gx, fx) and np.array_equal(gy, fy)
