@@ -6,8 +6,10 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -951,15 +953,58 @@ int step_one(lbm_solver* s) {
 
 namespace {
 
-int sync_and_check(lbm_solver* s) {
-  if (hipStreamSynchronize(s->stream) != hipSuccess) return LBM_EHIP;
-  if (!s->sticky_unstable) {
-    int32_t flag = 0;
-    if (hipMemcpy(&flag, &s->desc.state->unstable, sizeof(flag), hipMemcpyDeviceToHost) !=
-        hipSuccess)
-      return LBM_EHIP;
-    s->sticky_unstable = flag != 0;
+// fn(y0, y1) over the rows [0, ny), by up to 8 threads where the `row` values
+// per row make that worth their start.
+template <class F>
+void host_rows(int ny, size_t row, F&& fn) {
+  const size_t most = std::min<size_t>(8, std::max(1u, std::thread::hardware_concurrency()));
+  const int n = (int)std::min<size_t>({most, (size_t)ny, 1 + row * ny / (1 << 18)});
+  std::vector<std::thread> team;
+  int y = 0;
+  try {
+    team.reserve((size_t)n);
+    for (int i = 0; i + 1 < n; ++i) {
+      const int y1 = (int)((int64_t)ny * (i + 1) / n);
+      team.emplace_back([&fn, y, y1] { fn(y, y1); });
+      y = y1;
+    }
+  } catch (...) {
+    // fewer threads than wanted: the rest of the rows here
   }
+  fn(y, ny);
+  for (std::thread& t : team) t.join();
+}
+
+// Wait for the solver's work and read its flag, and the lock-in sums and
+// `count` force samples from step `first` into `force` (pairs) if wanted.
+int sync_and_check(lbm_solver* s, double lockin[6] = nullptr, int64_t first = 0,
+                   int64_t count = 0, double* force = nullptr) {
+  int32_t flag = 0;
+  const int small = (int)std::min<int64_t>(count, kReadoutSamples);
+  int rc = read_out(s->d_desc, s->device, s->stream, first, small, &flag, lockin, force);
+  int64_t done = small;
+  if (rc == LBM_ENOMEM) {
+    // no pinned memory: a wait and copies
+    SolveState st;
+    if (hipStreamSynchronize(s->stream) != hipSuccess ||
+        hipMemcpy(&st, s->desc.state, sizeof(st), hipMemcpyDeviceToHost) != hipSuccess)
+      return LBM_EHIP;
+    flag = st.unstable;
+    if (lockin) std::memcpy(lockin, st.lockin, sizeof(st.lockin));
+    done = 0;
+    rc = LBM_OK;
+  }
+  if (rc) return rc;
+  const int64_t cap = s->lay.hist_cap;
+  while (done < count) {
+    const int64_t h = (first + done) % cap;
+    const int64_t run = std::min(count - done, cap - h);
+    if (hipMemcpy(force + 2 * done, s->desc.hist + 2 * h, sizeof(double) * 2 * run,
+                  hipMemcpyDeviceToHost) != hipSuccess)
+      return LBM_EHIP;
+    done += run;
+  }
+  if (flag) s->sticky_unstable = true;
   return s->sticky_unstable ? LBM_EUNSTABLE : LBM_OK;
 }
 
@@ -1066,18 +1111,9 @@ int lbm_force_history(lbm_solver* s, int64_t first, int64_t count, double* fx, d
   const int64_t cap = s->lay.hist_cap;
   if (first + count > s->steps || first < std::max(s->hist_from, s->steps - std::min(s->steps, cap)))
     return LBM_ERANGE;
-  int rc = sync_and_check(s);
-  if (rc && rc != LBM_EUNSTABLE) return rc;
   std::vector<double> tmp((size_t)count * 2);
-  int64_t done = 0;
-  while (done < count) {
-    const int64_t h = (first + done) % cap;
-    const int64_t run = std::min(count - done, cap - h);
-    if (hipMemcpy(tmp.data() + 2 * done, s->desc.hist + 2 * h, sizeof(double) * 2 * run,
-                  hipMemcpyDeviceToHost) != hipSuccess)
-      return LBM_EHIP;
-    done += run;
-  }
+  const int rc = sync_and_check(s, nullptr, first, count, tmp.data());
+  if (rc && rc != LBM_EUNSTABLE) return rc;
   for (int64_t i = 0; i < count; ++i) {
     if (fx) fx[i] = tmp[2 * i];
     if (fy) fy[i] = tmp[2 * i + 1];
@@ -1087,12 +1123,8 @@ int lbm_force_history(lbm_solver* s, int64_t first, int64_t count, double* fx, d
 
 int lbm_lockin(lbm_solver* s, double sums[6], int64_t* nsamples) {
   if (!s || !sums) return LBM_EINVAL;
-  int rc = sync_and_check(s);
+  const int rc = sync_and_check(s, sums);
   if (rc && rc != LBM_EUNSTABLE) return rc;
-  SolveState st;
-  if (hipMemcpy(&st, s->desc.state, sizeof(st), hipMemcpyDeviceToHost) != hipSuccess)
-    return LBM_EHIP;
-  for (int k = 0; k < 6; ++k) sums[k] = st.lockin[k];
   if (nsamples)
     *nsamples = std::max<int64_t>(
         0, std::min(s->steps, s->p.lockin_first + s->p.lockin_count) - s->p.lockin_first);
@@ -1154,29 +1186,35 @@ int copy_out(lbm_solver* s, double* host, uint64_t n, bool with_rest) {
   const bool coeffs = s->lay.mom && !s->pop_pending;
   const uint64_t bytes = coeffs ? s->lay.mbuf_bytes : s->lay.buf_bytes;
   const void* src = coeffs ? s->desc.mbuf[s->steps & 1] : s->bufs[s->steps & 1];
-  std::vector<char> stage(bytes);
-  if (hipMemcpy(stage.data(), src, bytes, hipMemcpyDeviceToHost) != hipSuccess) return LBM_EHIP;
-  auto at = [&](int64_t i) {
-    return f64 ? reinterpret_cast<const double*>(stage.data())[i]
-               : (double)reinterpret_cast<const float*>(stage.data())[i];
-  };
-  for (int q = 0; q < Q; ++q) {
-    const double w = L.lw.w_orbit[L.orbit[q]];
-    const double wr = with_rest ? w * p.rho0 : 0.0;
-    const double vx = L.vx[q], vy = L.vy[q];
-    for (int y = 0; y < p.ny; ++y)
-      for (int x = 0; x < p.nx; ++x) {
-        double dv;
+  std::unique_ptr<char[]> stage(new (std::nothrow) char[bytes]);
+  if (!stage) return LBM_ENOMEM;
+  if (hipMemcpy(stage.get(), src, bytes, hipMemcpyDeviceToHost) != hipSuccess) return LBM_EHIP;
+  auto rows = [&](const auto* buf, int y0, int y1) {
+    for (int y = y0; y < y1; ++y)
+      for (int q = 0; q < Q; ++q) {
+        const double w = L.lw.w_orbit[L.orbit[q]];
+        const double wr = with_rest ? w * p.rho0 : 0.0;
+        double* out = host + ((size_t)q * p.ny + y) * p.nx;
         if (coeffs) {
-          const int64_t g = y * s->lay.mpitch + x, ks = s->lay.mks;
-          dv = w * (at(g) + vx * at(ks + g) + vy * at(2 * ks + g) + vx * vx * at(3 * ks + g) +
-                    vx * vy * at(4 * ks + g) + vy * vy * at(5 * ks + g));
+          const double vx = L.vx[q], vy = L.vy[q];
+          const double xx = vx * vx, xy = vx * vy, yy = vy * vy;
+          const int64_t ks = s->lay.mks;
+          const auto* c = buf + y * s->lay.mpitch;
+          for (int x = 0; x < p.nx; ++x)
+            out[x] = wr + w * ((double)c[x] + vx * (double)c[ks + x] + vy * (double)c[2 * ks + x] +
+                               xx * (double)c[3 * ks + x] + xy * (double)c[4 * ks + x] +
+                               yy * (double)c[5 * ks + x]);
         } else {
-          dv = at(q * s->lay.qs + y * s->lay.ys + x);
+          const auto* f = buf + q * s->lay.qs + y * s->lay.ys;
+          for (int x = 0; x < p.nx; ++x) out[x] = wr + (double)f[x];
         }
-        host[((size_t)q * p.ny + y) * p.nx + x] = in_body(&p, x, y) ? 0.0 : wr + dv;
+        if (in_body(&p, p.box_x0, y)) std::fill_n(out + p.box_x0, p.box_lx, 0.0);
       }
-  }
+  };
+  host_rows(p.ny, (size_t)Q * p.nx, [&](int y0, int y1) {
+    if (f64) rows(reinterpret_cast<const double*>(stage.get()), y0, y1);
+    else rows(reinterpret_cast<const float*>(stage.get()), y0, y1);
+  });
   return LBM_OK;
 }
 
@@ -1190,18 +1228,28 @@ int copy_in(lbm_solver* s, const double* host, uint64_t n, bool with_rest) {
   if (!s->lay.loadable) return LBM_EINVAL;  // no population buffer to load into
   if (hipStreamSynchronize(s->stream) != hipSuccess) return LBM_EHIP;
   const bool f64 = p.storage == LBM_STORE_F64;
-  std::vector<char> stage(s->lay.buf_bytes, 0);
-  for (int q = 0; q < Q; ++q) {
-    const double wr = with_rest ? s->lat.lw.w_orbit[s->lat.orbit[q]] * p.rho0 : 0.0;
-    for (int y = 0; y < p.ny; ++y)
-      for (int x = 0; x < p.nx; ++x) {
-        const int64_t dst = q * s->lay.qs + y * s->lay.ys + x;
-        const double dv = in_body(&p, x, y) ? 0.0 : host[((size_t)q * p.ny + y) * p.nx + x] - wr;
-        if (f64) reinterpret_cast<double*>(stage.data())[dst] = dv;
-        else reinterpret_cast<float*>(stage.data())[dst] = (float)dv;
+  std::unique_ptr<char[]> stage(new (std::nothrow) char[s->lay.buf_bytes]);
+  if (!stage) return LBM_ENOMEM;
+  // elements after a row of a population: the row's padding, or the gap
+  // between two planes (zeros)
+  const int64_t qs = s->lay.qs, ys = s->lay.ys;
+  auto rows = [&](auto* buf, int y0, int y1) {
+    for (int y = y0; y < y1; ++y)
+      for (int q = 0; q < Q; ++q) {
+        const double wr = with_rest ? s->lat.lw.w_orbit[s->lat.orbit[q]] * p.rho0 : 0.0;
+        const double* in = host + ((size_t)q * p.ny + y) * p.nx;
+        auto* out = buf + q * qs + y * ys;
+        for (int x = 0; x < p.nx; ++x) out[x] = in[x] - wr;
+        if (in_body(&p, p.box_x0, y)) std::fill_n(out + p.box_x0, p.box_lx, 0);
+        const int64_t gap = ys > qs ? s->lay.pitch - p.nx : y + 1 == p.ny ? qs - p.ny * ys : 0;
+        std::fill_n(out + p.nx, gap, 0);
       }
-  }
-  if (hipMemcpy(s->bufs[s->steps & 1], stage.data(), s->lay.buf_bytes,
+  };
+  host_rows(p.ny, (size_t)Q * p.nx, [&](int y0, int y1) {
+    if (f64) rows(reinterpret_cast<double*>(stage.get()), y0, y1);
+    else rows(reinterpret_cast<float*>(stage.get()), y0, y1);
+  });
+  if (hipMemcpy(s->bufs[s->steps & 1], stage.get(), s->lay.buf_bytes,
                 hipMemcpyHostToDevice) != hipSuccess)
     return LBM_EHIP;
   if (s->lay.mom) s->pop_pending = true;

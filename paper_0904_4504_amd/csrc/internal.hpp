@@ -33,6 +33,19 @@ hipError_t launch_column(int Q, bool f64, bool bgk, bool ds, const ColumnShape& 
 hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int count, int nsteps,
                           hipStream_t stream);
 
+// What a read-out brings to the host, in pinned memory.
+constexpr int kReadoutSamples = 4096;
+struct Readout {
+  int32_t unstable, pad;
+  double lockin[6];
+  double force[kReadoutSamples][2];
+};
+// Wait for the stream and read a solver's flag, lock-in sums and `count` force
+// samples from step `first` (null: not wanted).  LBM_ENOMEM: no pinned memory
+// (nothing was enqueued or waited for).
+int read_out(const SolveDesc* desc, int device, hipStream_t stream, int64_t first, int count,
+             int32_t* unstable, double lockin[6], double* force);
+
 constexpr uint64_t kAlign = 256;
 
 inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
