@@ -161,38 +161,55 @@ constexpr bool source_used(int vx, int iy) {
   return false;
 }
 
-// Weight of the velocities with components (+-a, +-b), as an orbit index, or
-// -1: the lattice's weights by |vx| and |vy|.
-template <class L>
-struct WeightMap {
-  int8_t orbit[4][4];
-  constexpr WeightMap() : orbit() {
-    for (int a = 0; a < 4; ++a)
-      for (int b = 0; b < 4; ++b) {
-        const int q = a <= L::R && b <= L::R ? find_velocity<L>(a, b) : -1;
-        orbit[a][b] = (int8_t)(q >= 0 ? L::orbit[q] : -1);
-      }
-  }
-};
-template <class L>
-__device__ constexpr WeightMap<L> kWeightMap{};
-
-// The weights by |vx| and |vy| (zero where the lattice has no such velocity),
-// in the storage precision and, for the diffuse wall, in FP64; in LDS, so that
-// the lanes of a wavefront can look up different ones.
+// Wall constants of a tile, in LDS, so that the lanes of a wavefront can look
+// up different ones.  w: the weights by |vx| and |vy| (zero where the lattice
+// has no such velocity).  s[n - 1][lo][hi][b]: the sum of w t^b over the
+// velocities of normal speed n and tangential speed -lo <= t <= hi, b = 0..4;
+// sd: the first three in FP64, for the diffuse wall.
 template <typename S, bool DSW>
 struct WallTable {
   S w[4][4];
-  double wd[DSW ? 4 : 1][4];
+  S s[3][4][4][5];
+  double sd[DSW ? 3 : 1][4][4][3];
 };
 
+// Entries of thread i < 48: selected from the kernel's arguments, without a
+// load (a table of orbits looked up in memory put two dependent cache misses
+// in front of the staging loads).
 template <class L, typename S, bool DSW>
-__device__ __forceinline__ void fill_wall_table(WallTable<S, DSW>& t, const KernelLattice& lat,
+__device__ __forceinline__ void fill_wall_table(WallTable<S, DSW>& tab, const KernelLattice& lat,
                                                 int i) {
-  const int o = kWeightMap<L>.orbit[i >> 2][i & 3];
-  const double w = o < 0 ? 0.0 : lat.w[o];
-  t.w[i >> 2][i & 3] = (S)w;
-  if constexpr (DSW) t.wd[i >> 2][i & 3] = w;
+  constexpr int R = L::R;
+  const int n = (i >> 4) + 1, lo = i >> 2 & 3, hi = i & 3;
+  double w = 0, wn[4] = {0, 0, 0, 0};
+  static_for<0, R + 1>([&](auto ac) __attribute__((always_inline)) {
+    static_for<0, R + 1>([&](auto bc) __attribute__((always_inline)) {
+      constexpr int a = decltype(ac)::value, b = decltype(bc)::value;
+      constexpr int q = find_velocity<L>(a, b);
+      if constexpr (q >= 0) {
+        const double v = lat.w[L::orbit[q]];
+        w = i == 4 * a + b ? v : w;
+        if constexpr (a > 0) wn[b] = n == a ? v : wn[b];
+      }
+    });
+  });
+  if (i < 16) tab.w[i >> 2][i & 3] = (S)w;
+  double m[5] = {wn[0], 0, 0, 0, 0};
+#pragma unroll
+  for (int t = 1; t <= R; ++t) {
+    const double u = t <= hi ? wn[t] : 0.0, v = t <= lo ? wn[t] : 0.0;
+    const double e = u + v, o = u - v, tt = t * t;
+    m[0] += e;
+    m[1] = fmadd((double)t, o, m[1]);
+    m[2] = fmadd(tt, e, m[2]);
+    m[3] = fmadd(t * tt, o, m[3]);
+    m[4] = fmadd(tt * tt, e, m[4]);
+  }
+#pragma unroll
+  for (int b = 0; b < 5; ++b) tab.s[n - 1][lo][hi][b] = (S)m[b];
+  if constexpr (DSW)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) tab.sd[n - 1][lo][hi][b] = m[b];
 }
 
 // Moments of the arrivals from the walls at fluid cell (x, y): each link
@@ -216,6 +233,17 @@ __device__ __forceinline__ void fill_wall_table(WallTable<S, DSW>& t, const Kern
 // 14.3 and 23.3 us, over a 256 x 256 plate 9.9 and 15.0 us, without walls
 // 7.8 us.
 //
+// What is left is a serial chain on the few wavefronts with wall cells, so it
+// is kept short: the S_b come from a table by n and the range of t, filled by
+// 48 threads while the staging loads are under way (summed by each lane from
+// the weights they were seven look-ups and five chains of seven additions per
+// mirror cell and as many again in FP64 for the crossing mass), the reads of
+// a mirror cell, or of a few specular sources, are in flight together, and
+// the column constants arrive behind the crossing mass.  One row per
+// wavefront, box of 256 x 256, bounce-back / diffuse: FP32 8.8 -> 8.0 / 12.5
+// -> 10.0 us per step, FP64 9.9 -> 9.0 / - -> 10.5 (4.8 and 5.8 us without
+// walls).
+//
 // Every cell read here (mirror cells, the specular sources and the crossing
 // rows of the diffuse wall) lies within R - 1 cells of (x, y) along each axis
 // (specular: R tangentially, inside the halo), so inside the staged tile: the
@@ -228,6 +256,9 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
   constexpr int R = L::R;
   const lptr<const Pair<S>> T = (lptr<const Pair<S>>)C;
   Mom<S> m{{S(0), S(0), S(0), S(0), S(0), S(0)}};
+  struct WallEmit {
+    double Mr, Z1, Z2, L1;  // of a WallCol, or of a plate (ds)
+  };
   // coefficients of cell (cx, cy) by normal axis: a0, b_t, b_n, c_tt, c_nt, c_nn
   struct Cell {
     S a0, bt, bn, ctt, cnt, cnn;
@@ -271,68 +302,60 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
       }
       const int k = sg * ((ax ? x : y) - w0);
       if (k >= R) continue;
-      // tangential velocities t with a source behind the wall: tlo <= t <= thi
-      const int tlo = is_box ? (ax ? y - d.by1 : x - d.bx1) + 1 : -R;
-      const int thi = is_box ? (ax ? y - d.by0 : x - d.bx0) : R;
+      // tangential velocities t with a source behind the wall: -lo <= t <= hi
+      int lo = R, hi = R;
+      if (is_box) {
+        lo = min(R, (ax ? d.by1 - y : d.bx1 - x) - 1);
+        hi = min(R, ax ? y - d.by0 : x - d.bx0);
+      }
       const S lad = pass ? S(0) : ladd;
       const bool diffuse = DSW && d.wall == WALL_DS && pass == 0;
       // diffuse emission w (ea + eb (e1 v_x + e2 v_x^2)) of the cell's column
       double ea = 0, eb = 0, e1 = 0, e2 = 0;
       if (diffuse) {
-        double Mr, Zu, Lu;  // mass emitted per unit density: Mr + Zu
+        WallEmit em{d.ds[0], 0, d.ds[1], 0};
         if (is_box) {
           const int face = ax ? (sg < 0 ? 2 : 3) : (sg < 0 ? 0 : 1);
           const WallCol& wc = d.wcols[box_column(d, face, x, y)];
-          Mr = wc.Mr;
-          Zu = wc.Z1 * U + wc.Z2 * U * U;
-          Lu = wc.L1 * U;
-        } else {
-          Mr = d.ds[0];
-          Zu = d.ds[1] * U * U;
-          Lu = 0;
+          em = {wc.Mr, wc.Z1, wc.Z2, wc.L1};
         }
         // deviation of the mass crossing the wall in this column: the
-        // bounce-back partners of all its links
+        // bounce-back partners of all its links (while em arrives)
         double cm = 0;
-#pragma unroll 1
+        const double sgn = sg;
+#pragma unroll
         for (int r = 0; r < R; ++r) {
           const int pc = w0 + sg * r;
           const Cell c = cell(ax ? pc : x, ax ? y : pc, ax);
-#pragma unroll 1
-          for (int n = r + 1; n <= R; ++n) {
-            double s0 = 0, s1 = 0, s2 = 0;
+          const double a0 = c.a0, bn = sgn * (double)c.bn, cnn = c.cnn, bt = c.bt, ctt = c.ctt;
+          const double cnt = sgn * (double)c.cnt;
 #pragma unroll
-            for (int t = -R; t <= R; ++t) {
-              const double w = t >= tlo && t <= thi ? tab.wd[n][t < 0 ? -t : t] : 0.0;
-              s0 += w;
-              s1 += w * t;
-              s2 += w * (t * t);
-            }
-            const double vn = sg * n;
-            cm += s0 * ((double)c.a0 - vn * (double)c.bn + vn * vn * (double)c.cnn) +
-                  s1 * (vn * (double)c.cnt - (double)c.bt) + s2 * (double)c.ctt;
+          for (int n = r + 1; n <= R; ++n) {
+            const double* sd;
+            if constexpr (sizeof(S) == 8)
+              sd = tab.s[n - 1][lo][hi];
+            else
+              sd = tab.sd[DSW ? n - 1 : 0][lo][hi];
+            cm = fmadd(sd[0], fmadd((double)n, fmadd((double)n, cnn, -bn), a0), cm);
+            cm = fmadd(sd[1], fmadd((double)n, cnt, -bt), cm);
+            cm = fmadd(sd[2], ctt, cm);
           }
+          asm volatile("" : "+v"(cm)::"memory");  // the reads of one cell in flight
         }
-        const double z = Mr + Zu, e0 = -U * U / (2 * theta);
-        e1 = U / theta;
-        e2 = U * U / (2 * theta * theta);
-        eb = d.sigma * (d.rho0 * (Mr + Lu) + cm) / z;
-        ea = d.sigma * (d.rho0 * (Lu - Zu) + cm) / z + eb * e0;
+        // mass emitted per unit density: Mr + Zu
+        const double Zu = fmadd(em.Z2, U, em.Z1) * U, Lu = em.L1 * U;
+        const double it = 1.0 / theta, sz = d.sigma / (em.Mr + Zu), e0 = -0.5 * U * U * it;
+        e1 = U * it;
+        e2 = 0.5 * e1 * e1;
+        eb = sz * fmadd(d.rho0, em.Mr + Lu, cm);
+        ea = fmadd(eb, e0, sz * fmadd(d.rho0, Lu - Zu, cm));
       }
 #pragma unroll 1
       for (int r = 0; r < R - k; ++r) {
         const int n = k + 1 + r;
         const S vn = (S)(sg * n);
-        S s0 = 0, s1 = 0, s2 = 0, s3 = 0, s4 = 0;
-#pragma unroll
-        for (int t = -R; t <= R; ++t) {
-          const S w = t >= tlo && t <= thi ? tab.w[n][t < 0 ? -t : t] : S(0);
-          s0 += w;
-          s1 = fmadd(S(t), w, s1);
-          s2 = fmadd(S(t * t), w, s2);
-          s3 = fmadd(S(t * t * t), w, s3);
-          s4 = fmadd(S(t * t * t * t), w, s4);
-        }
+        const S* const st = tab.s[n - 1][lo][hi];
+        const S s0 = st[0], s1 = st[1], s2 = st[2], s3 = st[3], s4 = st[4];
         const int pc = w0 + sg * r;
         S G, H, K;
         if (diffuse) {
@@ -355,17 +378,23 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
           // crossed the wall from the mirror cell's neighbour t cells back
           // (plus the moving-wall term on the faces normal to the motion)
           const S ws = (S)(1.0 - d.sigma);
-#pragma unroll 1
+          S f0 = 0, f1 = 0, f2 = 0;
+#pragma unroll
           for (int t = -R; t <= R; ++t) {
-            const S w = t >= tlo && t <= thi ? ws * tab.w[n][t < 0 ? -t : t] : S(0);
-            if (w == S(0)) continue;
+            const S w = t >= -lo && t <= hi ? ws * tab.w[n][t < 0 ? -t : t] : S(0);
             Cell c = cell(ax ? pc : x - t, ax ? y - t : pc, ax);
             c.bn -= ax ? lad : S(0);
             const S ts = (S)t;
-            const S f = w * (c.a0 + ts * (c.bt + ts * c.ctt - vn * c.cnt) +
-                             vn * (vn * c.cnn - c.bn));
-            add(f, ts * f, ts * ts * f, vn);
+            const S g = w * fmadd(ts, fmadd(ts, c.ctt, fmadd(-vn, c.cnt, c.bt)),
+                                  fmadd(vn, fmadd(vn, c.cnn, -c.bn), c.a0));
+            const S f = w == S(0) ? S(0) : g;
+            f0 += f;
+            f1 = fmadd(ts, f, f1);
+            f2 = fmadd(ts * ts, f, f2);
+            // the reads of a few cells in flight, not of all
+            if (sizeof(S) == 8 || t % 2 == 0) asm volatile("" : "+v"(f0), "+v"(f1), "+v"(f2)::"memory");
           }
+          add(f0, f1, f2, vn);
         }
       }
     }
@@ -897,14 +926,14 @@ __device__ __forceinline__ void tile_update(const SolveDesc& d, const TileCtx<S>
   int nv = (int)ctx.n;
   asm volatile("" : "+v"(nv));
   const double U = as_global(d.drive)[nv].u;
-  if (WallBand<L>(d).meets((tile % d.tiles_x) * kCoefTileW, (tile / d.tiles_x) * T::TH, T::TH) &&
-      tid < 16)
-    fill_wall_table<L>(tab, lat, tid);
   {
     // all loads of a thread are issued before the first LDS store, so the
     // block waits for one memory round trip, not one per staged cell
     StageRegs<L, S, RB> g;
     stage_load<L, S, RB>(d, ctx, tile, g, tid);
+    if (tid < 48 &&
+        WallBand<L>(d).meets((tile % d.tiles_x) * kCoefTileW, (tile / d.tiles_x) * T::TH, T::TH))
+      fill_wall_table<L>(tab, lat, tid);
     stage_store<L, S, RB>(C, g, tid);
   }
   __syncthreads();
