@@ -331,12 +331,62 @@ bool diffuse_box(const lbm_params* p) {
   return p->geometry == LBM_GEOM_BOX && p->wall != LBM_WALL_BB;
 }
 
+// The mirror cells of a coefficient state with their force weights; cells with
+// equal weights (compared bit for bit) share a pattern.
+struct CellTable {
+  const Layout& lay;
+  ForceTables* t;
+  int x0 = 0, y0 = 0, w = 0;    // the cells within R of the moving wall
+  std::vector<int32_t> index;   // of those cells: position in t->cells, or -1
+  std::vector<CellWeights> cw;  // the weights of t->cells
+
+  CellTable(const lbm_params* p, int R, const Layout& layout, ForceTables* tables)
+      : lay(layout), t(tables), w(p->nx) {
+    int h = R;
+    if (p->geometry == LBM_GEOM_BOX) {
+      x0 = p->box_x0 - R;
+      y0 = p->box_y0 - R;
+      w = p->box_lx + 2 * R;
+      h = p->box_ly + 2 * R;
+    }
+    if (lay.mom && p->geometry != LBM_GEOM_PERIODIC) index.assign((size_t)w * h, -1);
+  }
+  CellWeights& at(int px, int py) {
+    int32_t& pos = index[(size_t)(py - y0) * w + (px - x0)];
+    if (pos >= 0) return cw[(size_t)pos];
+    ForceCell fc{};
+    fc.off = (int64_t)py * lay.mpitch + px;
+    pos = (int32_t)t->cells.size();
+    t->cells.push_back(fc);
+    cw.push_back(CellWeights{});
+    return cw.back();
+  }
+  void assign_patterns() {
+    std::unordered_map<std::string, int32_t> pats;
+    for (size_t i = 0; i < t->cells.size(); ++i)
+      t->cells[i].pat = pattern(pats, t->cweights, cw[i]);
+  }
+  template <class P, class V, class W>
+  static int32_t pattern(P& pats, V& table, const W& wts) {
+    const std::string key(reinterpret_cast<const char*>(&wts), sizeof(wts));
+    auto it = pats.find(key);
+    if (it != pats.end()) return it->second;
+    const int32_t k = (int32_t)table.size();
+    table.push_back(wts);
+    pats.emplace(key, k);
+    return k;
+  }
+};
+
 // Tables of a box with diffuse or Maxwell faces: its links face column by
 // face column (faces below, above the body by arrival x, left, right of it
 // by arrival y; in a column by arrival cell and direction), then the corner
 // links; per column the lattice sums of its links (long double).  The force
 // is -sum v_l (f_partner + f_arrival) over every link: the rest-state parts
-// give fstatic, the rest is formed per link by wall_force.
+// give fstatic, the moving-wall terms of the corner links and of the specular
+// share at the x faces give kladd.  The rest is formed per link (population
+// state); of a coefficient state all but the columns' emission is linear in
+// the cells' coefficients and becomes weights per cell, as for bounce-back.
 void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& lay,
                        ForceTables* t) {
   const int R = L.R;
@@ -354,7 +404,20 @@ void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& 
     if (iny && !inx) return x < x0 ? 2 : 3;
     return -1;
   };
-  long double sx = 0, sy = 0;
+  const long double spec = 1.0L - (p->wall == LBM_WALL_MAXWELL ? (long double)p->accommodation : 1.0L);
+  long double sx = 0, sy = 0, kx = 0, ky = 0;
+  CellTable cells(p, L.R, lay, t);
+  // -scale v_l times the population of velocity (ux, uy) and weight w at a cell
+  auto add_pop = [&](int cx, int cy, long double scale, long double w, int vx, int vy, int ux,
+                     int uy) {
+    CellWeights& fc = cells.at(cx, cy);
+    const long double g[6] = {1, (long double)ux, (long double)uy, (long double)ux * ux,
+                              (long double)ux * uy, (long double)uy * uy};
+    for (int k = 0; k < 6; ++k) {
+      fc.wx[k] += (double)(-scale * vx * w * g[k]);
+      fc.wy[k] += (double)(-scale * vy * w * g[k]);
+    }
+  };
   // crossing-mass weights of the current column over its cells' coefficients
   long double mc[3][6];
   // the links of a fluid cell, in direction order
@@ -368,19 +431,23 @@ void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& 
       const long double w = L.lw.w_orbit_ld[L.orbit[q]];
       WallLink l{};
       l.off_partner = L.opp[q] * lay.qs + py * lay.ys + px;
-      l.cell_partner = (int64_t)py * lay.mpitch + px;
       l.col = col;
       l.w = (double)w;
       l.vx = vx;
       l.vy = vy;
       const int face = face_of(x, y);
-      l.normal = face >= 2;
-      if (face == 0 || face == 1) {
-        l.off_spec = find(vx, -vy) * lay.qs + py * lay.ys + sxs;
-        l.cell_spec = (int64_t)py * lay.mpitch + sxs;
-      } else if (face >= 2) {
-        l.off_spec = find(-vx, vy) * lay.qs + sys * lay.ys + px;
-        l.cell_spec = (int64_t)sys * lay.mpitch + px;
+      // where and with which velocity the specular source crossed
+      const bool xface = face >= 2;
+      const int ux = xface ? -vx : vx, uy = xface ? vy : -vy;
+      const int cx = xface ? px : sxs, cy = xface ? sys : py;
+      if (face >= 0) l.off_spec = find(ux, uy) * lay.qs + cy * lay.ys + cx;
+      // a corner link's arrival is its partner again
+      if (lay.mom) add_pop(px, py, face < 0 ? 2.0L : 1.0L, w, vx, vy, -vx, -vy);
+      if (lay.mom && face >= 0 && spec != 0) add_pop(cx, cy, spec, w, vx, vy, ux, uy);
+      if (face < 0 || xface) {
+        const long double share = face < 0 ? 1.0L : spec;
+        kx -= share * vx * w * 2.0L * p->rho0 * vx / th;
+        ky -= share * vy * w * 2.0L * p->rho0 * vx / th;
       }
       if (col >= 0) {
         // the partner's distance from the face (it lies in the link's column)
@@ -419,6 +486,7 @@ void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& 
       for (int j = 0; j < 6; ++j) wc.mc[k][j] = (double)mc[k][j];
     wc.count = (int32_t)t->wlinks.size() - wc.first;
     long double mr = 0, z1 = 0, z2 = 0, l1 = 0;
+    long double ex[3] = {0, 0, 0}, ey[3] = {0, 0, 0};
     for (int i = wc.first; i < wc.first + wc.count; ++i) {
       const WallLink& l = t->wlinks[(size_t)i];
       const long double w = L.lw.w_orbit_ld[L.orbit[find((int)l.vx, (int)l.vy)]];
@@ -427,6 +495,15 @@ void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& 
       z1 += w * vx / th;
       z2 += w * (vx * vx / (2 * th * th) - 1 / (2 * th));
       l1 += 2 * w * vx / th;
+      for (int k = 0; k < 3; ++k) {
+        const long double pw = k == 0 ? w : k == 1 ? w * vx : w * vx * vx;
+        ex[k] += pw * vx;
+        ey[k] += pw * (long double)l.vy;
+      }
+    }
+    for (int k = 0; k < 3; ++k) {
+      wc.ex[k] = (double)ex[k];
+      wc.ey[k] = (double)ey[k];
     }
     wc.Mr = (double)mr;
     wc.Z1 = (double)z1;
@@ -437,8 +514,11 @@ void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& 
   for (int y = y0 - R; y < y1 + R; ++y)
     for (int x = x0 - R; x < x1 + R; ++x)
       if (!in_body(p, x, y) && face_of(x, y) < 0) add_cell(x, y, -1);
+  cells.assign_patterns();
   t->fstatic[0] = (double)sx;
   t->fstatic[1] = (double)sy;
+  t->kladd[0] = (double)kx;
+  t->kladd[1] = (double)ky;
 }
 
 void build_force_tables(const lbm_params* p, const HostLattice& L, const Layout& lay,
@@ -455,30 +535,8 @@ void build_force_tables(const lbm_params* p, const HostLattice& L, const Layout&
   const bool diffuse = p->wall == LBM_WALL_DS || p->wall == LBM_WALL_MAXWELL;
   const long double sigma = p->wall == LBM_WALL_MAXWELL ? (long double)p->accommodation : 1.0L;
   const long double mwx = diffuse ? sigma : 2.0L, mwy = diffuse ? 2.0L - sigma : 2.0L;
-  std::unordered_map<int64_t, size_t> index;  // mirror cell -> position in t->cells
-  std::vector<CellWeights> cw;                 // the weights of t->cells
-  auto cell_for = [&](int px, int py) -> CellWeights& {
-    const int64_t key = (int64_t)py * p->nx + px;
-    auto it = index.find(key);
-    if (it != index.end()) return cw[it->second];
-    ForceCell fc{};
-    fc.off = (int64_t)py * lay.mpitch + px;
-    index.emplace(key, t->cells.size());
-    t->cells.push_back(fc);
-    cw.push_back(CellWeights{});
-    return cw.back();
-  };
-  // one pattern per distinct set of weights (compared bit for bit)
-  std::unordered_map<std::string, int32_t> lpat, cpat;
-  auto pattern = [](auto& pats, auto& table, const auto& wts) {
-    const std::string key(reinterpret_cast<const char*>(&wts), sizeof(wts));
-    auto it = pats.find(key);
-    if (it != pats.end()) return it->second;
-    const int32_t k = (int32_t)table.size();
-    table.push_back(wts);
-    pats.emplace(key, k);
-    return k;
-  };
+  CellTable cells(p, L.R, lay, t);
+  std::unordered_map<std::string, int32_t> lpat;
   int x0 = 0, x1 = 0, y0 = 0, y1 = 0;
   if (p->geometry == LBM_GEOM_PLATE) {
     x0 = 0; x1 = p->nx; y0 = 0; y1 = std::min(L.R, p->ny);
@@ -504,9 +562,9 @@ void build_force_tables(const lbm_params* p, const HostLattice& L, const Layout&
         const LinkWeights lwt{(double)(-mwx * vx), (double)(-mwy * vy), diffuse ? 1.0 : 0.0,
                               0.0};
         t->links.push_back(ForceLink{L.opp[q] * lay.qs + py * lay.ys + px,
-                                     pattern(lpat, t->lweights, lwt), 0});
+                                     CellTable::pattern(lpat, t->lweights, lwt), 0});
         if (lay.mom) {
-          CellWeights& fc = cell_for(px, py);
+          CellWeights& fc = cells.at(px, py);
           // basis of the opposite direction -v at the mirror cell
           const long double g[6] = {1, -(long double)vx, -(long double)vy,
                                     (long double)vx * vx, (long double)vx * vy,
@@ -519,7 +577,7 @@ void build_force_tables(const lbm_params* p, const HostLattice& L, const Layout&
         }
       }
     }
-  for (size_t i = 0; i < t->cells.size(); ++i) t->cells[i].pat = pattern(cpat, t->cweights, cw[i]);
+  cells.assign_patterns();
   t->fstatic[0] = (double)sx;
   t->fstatic[1] = (double)sy;
   t->kladd[0] = (double)kx;

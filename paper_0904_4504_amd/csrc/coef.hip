@@ -957,7 +957,7 @@ __global__ __launch_bounds__(64 * kCoefWaves) void coef_kernel(const SolveDesc* 
   const SolveDesc& d = descs[wi.solve];
   const TileCtx<S> ctx = tile_ctx<S>(d, dn);
   if (wi.tile == kForceTile) {
-    wall_force<S>(d, true, ctx.n, lds.force);
+    wall_force<S, DSW>(d, true, ctx.n, lds.force);
     return;
   }
   tile_update<L, S, RB, DSW>(d, ctx, wi.tile, lat, cc, (int)threadIdx.x, streaming != 0, lds);

@@ -463,7 +463,7 @@ __global__ __launch_bounds__(BS) void step_kernel(const SolveDesc* __restrict__ 
   const SolveDesc& d = descs[wi.solve];
   const int64_t n = d.state->step + dn;
   if (wi.tile == kForceTile) {
-    wall_force<S>(d, false, n, lds);
+    wall_force<S, DSW>(d, false, n, lds);
     return;
   }
   const S* __restrict__ fin = static_cast<const S*>(d.buf[n & 1]);
