@@ -239,10 +239,14 @@ __device__ __forceinline__ void fill_wall_table(WallTable<S, DSW>& tab, const Ke
 // the weights they were seven look-ups and five chains of seven additions per
 // mirror cell and as many again in FP64 for the crossing mass), the reads of
 // a mirror cell, or of a few specular sources, are in flight together, and
-// the column constants arrive behind the crossing mass.  One row per
-// wavefront, box of 256 x 256, bounce-back / diffuse: FP32 8.8 -> 8.0 / 12.5
-// -> 10.0 us per step, FP64 9.9 -> 9.0 / - -> 10.5 (4.8 and 5.8 us without
-// walls).
+// the column constants arrive behind the crossing mass.  The corner links of
+// a cell are one unrolled pass of selects (in a loop over pairs of speeds, up
+// to nine round trips to LDS, they were the longest chain of a bounce-back
+// box).  One row per wavefront, box of 256 x 256, bounce-back / diffuse /
+// Maxwell, us per step: FP32 8.8 -> 6.9 / 12.5 -> 8.4 / - -> 11.9, FP64 9.9 ->
+// 7.8 / - -> 9.1 / - -> 13.4 (5.0 and 6.2 without walls).  The specular share
+// is the rest of the Maxwell wall: its 21 sources unrolled over t; rolled
+// over t, the two signs together, 15.3.
 //
 // Every cell read here (mirror cells, the specular sources and the crossing
 // rows of the diffuse wall) lies within R - 1 cells of (x, y) along each axis
@@ -255,6 +259,10 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
                                                const WallTable<S, DSW>& tab, double theta) {
   constexpr int R = L::R;
   const lptr<const Pair<S>> T = (lptr<const Pair<S>>)C;
+  // (values: the fences below would have them loaded again)
+  const int bx0 = d.bx0, bx1 = d.bx1, by0 = d.by0, by1 = d.by1, nyl = d.ny;
+  const bool two_walls = d.geom == GEOM_PLATE && d.far == FAR_WALL, ds_wall = d.wall == WALL_DS;
+  const double sigma = d.sigma, rho0 = d.rho0;
   Mom<S> m{{S(0), S(0), S(0), S(0), S(0), S(0)}};
   struct WallEmit {
     double Mr, Z1, Z2, L1;  // of a WallCol, or of a plate (ds)
@@ -266,12 +274,15 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
   auto cell = [&](int cx, int cy, bool nx_axis) __attribute__((always_inline)) -> Cell {
     const int i = 3 * (cy - oy) * HW + (cx - ox);
     const Pair<S> p0 = T[i], p1 = T[i + HW], p2 = T[i + 2 * HW];
-    return nx_axis ? Cell{p0.x, p1.x, p0.y, p2.y, p2.x, p1.y}
-                   : Cell{p0.x, p0.y, p1.x, p1.y, p2.x, p2.y};
+    // (selects per field: a choice of whole cells becomes a branch, and with it
+    // a wait for every cell by itself)
+    const S bt = nx_axis ? p1.x : p0.y, bn = nx_axis ? p0.y : p1.x;
+    const S ctt = nx_axis ? p2.y : p1.y, cnn = nx_axis ? p1.y : p2.y;
+    return Cell{p0.x, bt, bn, ctt, p2.x, cnn};
   };
   const bool is_box = d.geom == GEOM_BOX;
-  const bool inx = !is_box || (x >= d.bx0 && x < d.bx1);
-  const bool iny = is_box && y >= d.by0 && y < d.by1;
+  const bool inx = !is_box || (x >= bx0 && x < bx1);
+  const bool iny = is_box && y >= by0 && y < by1;
   // moments along the normal and the tangential axis
   Mom<S> a{{S(0), S(0), S(0), S(0), S(0), S(0)}};  // drho, j_t, j_n, P_tt, P_nt, P_nn
   auto add = [&](S t0, S t1, S t2, S vn) __attribute__((always_inline)) {
@@ -285,31 +296,31 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
   const bool ax = iny;  // normal along x: the faces left and right of the body
   if (inx || iny) {
     // a plate's cell may be in reach of both its walls
-    const int npass = d.geom == GEOM_PLATE && d.far == FAR_WALL ? 2 : 1;
+    const int npass = two_walls ? 2 : 1;
 #pragma unroll 1
     for (int pass = 0; pass < npass; ++pass) {
       // first fluid cell along the normal, and the sign of the arrivals' v_n
       int w0, sg;
       if (!is_box) {
-        w0 = pass ? d.ny - 1 : 0;
+        w0 = pass ? nyl - 1 : 0;
         sg = pass ? -1 : 1;
       } else if (ax) {
-        w0 = x < d.bx0 ? d.bx0 - 1 : d.bx1;
-        sg = x < d.bx0 ? -1 : 1;
+        w0 = x < bx0 ? bx0 - 1 : bx1;
+        sg = x < bx0 ? -1 : 1;
       } else {
-        w0 = y < d.by0 ? d.by0 - 1 : d.by1;
-        sg = y < d.by0 ? -1 : 1;
+        w0 = y < by0 ? by0 - 1 : by1;
+        sg = y < by0 ? -1 : 1;
       }
       const int k = sg * ((ax ? x : y) - w0);
       if (k >= R) continue;
       // tangential velocities t with a source behind the wall: -lo <= t <= hi
       int lo = R, hi = R;
       if (is_box) {
-        lo = min(R, (ax ? d.by1 - y : d.bx1 - x) - 1);
-        hi = min(R, ax ? y - d.by0 : x - d.bx0);
+        lo = min(R, (ax ? by1 - y : bx1 - x) - 1);
+        hi = min(R, ax ? y - by0 : x - bx0);
       }
       const S lad = pass ? S(0) : ladd;
-      const bool diffuse = DSW && d.wall == WALL_DS && pass == 0;
+      const bool diffuse = DSW && ds_wall && pass == 0;
       // diffuse emission w (ea + eb (e1 v_x + e2 v_x^2)) of the cell's column
       double ea = 0, eb = 0, e1 = 0, e2 = 0;
       if (diffuse) {
@@ -344,11 +355,11 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
         }
         // mass emitted per unit density: Mr + Zu
         const double Zu = fmadd(em.Z2, U, em.Z1) * U, Lu = em.L1 * U;
-        const double it = 1.0 / theta, sz = d.sigma / (em.Mr + Zu), e0 = -0.5 * U * U * it;
+        const double it = 1.0 / theta, sz = sigma / (em.Mr + Zu), e0 = -0.5 * U * U * it;
         e1 = U * it;
         e2 = 0.5 * e1 * e1;
-        eb = sz * fmadd(d.rho0, em.Mr + Lu, cm);
-        ea = fmadd(eb, e0, sz * fmadd(d.rho0, Lu - Zu, cm));
+        eb = sz * fmadd(rho0, em.Mr + Lu, cm);
+        ea = fmadd(eb, e0, sz * fmadd(rho0, Lu - Zu, cm));
       }
 #pragma unroll 1
       for (int r = 0; r < R - k; ++r) {
@@ -373,15 +384,17 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
         }
         add(fmadd(s0, G, fmadd(s1, H, s2 * K)), fmadd(s1, G, fmadd(s2, H, s3 * K)),
             fmadd(s2, G, fmadd(s3, H, s4 * K)), vn);
-        if (DSW && diffuse && d.sigma != 1.0) {
+        if (DSW && diffuse && sigma != 1.0) {
           // Maxwell wall: the specular share, the population of (t, -v_n) that
           // crossed the wall from the mirror cell's neighbour t cells back
           // (plus the moving-wall term on the faces normal to the motion)
-          const S ws = (S)(1.0 - d.sigma);
-          S f0 = 0, f1 = 0, f2 = 0;
+          const S ws = (S)(1.0 - sigma);
+          S f0 = 0, f1 = 0, f2 = 0, wt[R + 1];
+#pragma unroll
+          for (int t = 0; t <= R; ++t) wt[t] = ws * tab.w[n][t];
 #pragma unroll
           for (int t = -R; t <= R; ++t) {
-            const S w = t >= -lo && t <= hi ? ws * tab.w[n][t < 0 ? -t : t] : S(0);
+            const S w = t >= -lo && t <= hi ? wt[t < 0 ? -t : t] : S(0);
             Cell c = cell(ax ? pc : x - t, ax ? y - t : pc, ax);
             c.bn -= ax ? lad : S(0);
             const S ts = (S)t;
@@ -400,23 +413,28 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
     }
   } else {
     // corner links: |v_x| >= i and |v_y| >= j, one mirror cell each
-    const bool lo_x = x < d.bx0, lo_y = y < d.by0;
-    const int i = lo_x ? d.bx0 - x : x - d.bx1 + 1, j = lo_y ? d.by0 - y : y - d.by1 + 1;
-#pragma unroll 1
-    for (int b = j; b <= R; ++b)
-#pragma unroll 1
-      for (int c0 = i; c0 <= R; ++c0) {
-        const S w = tab.w[c0][b];
-        if (w == S(0)) continue;
-        const int px = lo_x ? d.bx0 - 1 - (c0 - i) : d.bx1 + (c0 - i);
-        const int py = lo_y ? d.by0 - 1 - (b - j) : d.by1 + (b - j);
-        Cell c = cell(px, py, false);
-        c.bt -= ladd;
-        const S vx = (S)(lo_x ? -c0 : c0), vy = (S)(lo_y ? -b : b);
-        const S f = w * (c.a0 + vx * (vx * c.ctt + vy * c.cnt - c.bt) +
-                         vy * (vy * c.cnn - c.bn));
-        add(f, vx * f, vx * vx * f, vy);
-      }
+    const bool lo_x = x < bx0, lo_y = y < by0;
+    const int i = lo_x ? bx0 - x : x - bx1 + 1, j = lo_y ? by0 - y : y - by1 + 1;
+    const int wx = lo_x ? bx0 - 1 : bx1, wy = lo_y ? by0 - 1 : by1;
+    const int sx = lo_x ? -1 : 1, sy = lo_y ? -1 : 1;
+    static_for<1, R + 1>([&](auto bc) __attribute__((always_inline)) {
+      static_for<1, R + 1>([&](auto ac) __attribute__((always_inline)) {
+        constexpr int va = decltype(ac)::value, vb = decltype(bc)::value;
+        if constexpr (find_velocity<L>(va, vb) >= 0) {
+          const bool on = va >= i && vb >= j;
+          Cell c = cell(on ? wx + sx * (va - i) : x, on ? wy + sy * (vb - j) : y, false);
+          c.bt -= ladd;
+          const S vx = (S)(sx * va), vy = (S)(sy * vb);
+          const S g = tab.w[va][vb] *
+                      fmadd(vx, fmadd(vx, c.ctt, fmadd(vy, c.cnt, -c.bt)),
+                            fmadd(vy, fmadd(vy, c.cnn, -c.bn), c.a0));
+          const S f = on ? g : S(0);
+          add(f, vx * f, vx * vx * f, vy);
+        }
+      });
+      // the reads of one row of velocities in flight
+      row_fence(a);
+    });
   }
   m.v[0] = a.v[0];
   m.v[1] = ax ? a.v[2] : a.v[1];
