@@ -176,6 +176,9 @@ namespace lbm {
 // Create a solver in caller-owned device memory (dev_buf, bytes) or, with
 // dev_buf null, in memory the library allocates.  graphs: lbm_step may
 // capture and replay HIP graphs (off: every step launches directly).
+// lbm_required_bytes; fine (if asked for): how much of it goes beyond the state,
+// the tables and the work lists of the default tiles, at most.
+int required_bytes(const lbm_params* p, uint64_t* bytes, uint64_t* fine);
 int create_solver(const lbm_params* p, void* stream, void* dev_buf, uint64_t bytes, bool graphs,
                   lbm_solver** out);
 // Mark the static scratch array of `device` free again (lbm_destroy of a

@@ -10,6 +10,7 @@
 // caller's buffer, so it runs the same kernels on the same layout.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "internal.hpp"
@@ -17,8 +18,12 @@
 namespace {
 
 constexpr uint64_t kScratchBytes = LBM_STATIC_SCRATCH_BYTES;
+// The limit is on the state, its tables and the work lists of the default
+// tiles; what finer tiles add to the lists (8 bytes per tile of 64 x 4 cells)
+// and the force cells of diffuse boxes lies behind.
+constexpr uint64_t kScratchSlack = 256 << 10;
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSlack];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
@@ -35,10 +40,10 @@ void lbm::release_scratch(int device) {
 extern "C" int lbm_create_static(const lbm_params* p, void* hip_stream, lbm_solver** out) {
   if (!out) return LBM_EINVAL;
   *out = nullptr;
-  uint64_t need = 0;
-  int rc = lbm_required_bytes(p, &need);
+  uint64_t need = 0, fine = 0;
+  int rc = lbm::required_bytes(p, &need, &fine);
   if (rc) return rc;
-  if (need > kScratchBytes) return LBM_ESCRATCH;
+  if (need > kScratchBytes + std::min(fine, kScratchSlack)) return LBM_ESCRATCH;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return LBM_EHIP;
   if (dev < 0 || dev >= kMaxDevices) return LBM_EINVAL;
@@ -52,7 +57,7 @@ extern "C" int lbm_create_static(const lbm_params* p, void* hip_stream, lbm_solv
     }
     g_ptr[dev] = ptr;
   }
-  rc = lbm::create_solver(p, hip_stream, g_ptr[dev], kScratchBytes, false, out);
+  rc = lbm::create_solver(p, hip_stream, g_ptr[dev], sizeof(scratch), false, out);
   if (rc) return rc;
   (*out)->in_scratch = true;
   g_busy[dev] = true;
