@@ -41,16 +41,17 @@ void order_tiles(std::vector<WorkItem>* out, int32_t solve, int32_t ntiles, int3
 
 // Small launches take one row per wavefront: few workgroups per compute unit,
 // so a step is the chain of one wavefront, which K rows make K times as long
-// (a 256 x 256 box, K = 1, 2, 3: FP32 8.8, 11.6, 14.6 us per step, FP64 9.9,
-// 13.4, 17.3).  Large ones share the halo and the source cells among more rows.
-// The lines: FP32 768 x 768 13.7, 14.1, 15.2, 1024 x 1024 21.5, 18.3, 18.2,
-// 1400 x 1400 33.0, 27.0, 25.6; FP64 512 x 512 12.9, 14.5, 17.2, 768 x 768
-// 21.9, 20.5, 21.5, 1400 x 1400 53.6, 45.6, 51.0 (K = 3 leaves two workgroups
-// per compute unit by LDS).  A cell's bits do not depend on K.
+// (a 256 x 256 box, K = 1, 2, 3: FP32 6.9, 9.1, 10.8 us per step, FP64 7.9,
+// 10.4, 12.8).  Large ones share the halo and the source cells among more rows.
+// The lines: FP32 640 x 640 10.6, 10.7, 12.3, 768 x 768 13.0, 11.8, 12.4,
+// 848 x 848 16.0, 14.9, 13.7, 1024 x 1024 20.3, 17.7, 17.9, 1400 x 1400 32.5,
+// 26.6, 25.7; FP64 512 x 512 12.5, 12.3, 13.5, 640 x 640 17.4, 17.2, 17.6,
+// 768 x 768 21.8, 20.1, 21.0, 1400 x 1400 54.3, 46.3, 48.6 (K = 3 leaves two
+// workgroups per compute unit by LDS).  A cell's bits do not depend on K.
 int coef_k_for(uint32_t tile, bool f64, int64_t cells) {
   if (tile) return (int)tile;
   if (f64) return cells <= 400000 ? 1 : 2;
-  return cells <= 720000 ? 1 : kCoefKDefault;
+  return cells <= 420000 ? 1 : cells <= 650000 ? 2 : kCoefKDefault;
 }
 
 CoefGrid coef_grid(const lbm_params* p, int K) {
@@ -758,7 +759,6 @@ int init_solver(lbm_solver* s) {
   d.lockin_count = p->lockin_count;
   d.nx = p->nx;
   d.ny = p->ny;
-  d.ncells = p->nx * p->ny;
   d.mw = lay.mw;
   d.geom = (int32_t)p->geometry;
   d.far = (int32_t)p->far;
@@ -1068,6 +1068,35 @@ int sync_and_check(lbm_solver* s, double lockin[6] = nullptr, int64_t first = 0,
 
 }  // namespace
 
+namespace lbm {
+
+int required_bytes(const lbm_params* p, uint64_t* bytes, uint64_t* fine) {
+  if (!bytes) return LBM_EINVAL;
+  HostLattice lat;
+  int rc = validate(p, &lat);
+  if (rc) return rc;
+  Layout lay;
+  make_layout(p, lat, &lay);
+  *bytes = lay.total;
+  if (!fine) return LBM_OK;
+  // the same lists over plain cells and with the default K, wall tiles aside
+  const int64_t cells = (int64_t)p->nx * p->ny, per = lay.cells_per_tile;
+  int64_t items = lay.nwork - ordered_length((cells + per - 1) / per, (p->nx + per - 1) / per);
+  if (lay.mom) {
+    const CoefGrid g = coef_grid(p, lay.coef_k);
+    items += lay.mnwork - ordered_length(g.ntiles, g.tiles_x);
+  }
+  const int64_t tables =
+      diffuse_box(p) && lay.mom
+          ? (int64_t)sizeof(ForceCell) * lay.nfcells + (int64_t)sizeof(CellWeights) * lay.ncweights
+          : 0;
+  // (a kAlign for the rounding of each)
+  *fine = (uint64_t)std::max<int64_t>(0, items * (int64_t)sizeof(WorkItem) + tables) + 4 * kAlign;
+  return LBM_OK;
+}
+
+}  // namespace lbm
+
 extern "C" {
 
 int lbm_params_init(lbm_params* p) {
@@ -1098,14 +1127,7 @@ int lbm_lattice(int Q, int32_t* vx, int32_t* vy, double* w, double* theta) {
 }
 
 int lbm_required_bytes(const lbm_params* p, uint64_t* bytes) {
-  if (!bytes) return LBM_EINVAL;
-  HostLattice lat;
-  int rc = validate(p, &lat);
-  if (rc) return rc;
-  Layout lay;
-  make_layout(p, lat, &lay);
-  *bytes = lay.total;
-  return LBM_OK;
+  return lbm::required_bytes(p, bytes, nullptr);
 }
 
 int lbm_create(const lbm_params* p, void* hip_stream, lbm_solver** out) {

@@ -141,7 +141,7 @@ struct SolveDesc {
   int64_t max_steps;
   int64_t hist_cap;
   int64_t lockin_first, lockin_count;
-  int32_t nx, ny, ncells;          // ncells = nx * ny
+  int32_t nx, ny;
   int32_t mw;                      // population kernel: cells per row of its tiles
   int32_t geom, far;
   int32_t bx0, by0, bx1, by1;      // solid cells [bx0,bx1) x [by0,by1) (box only)
