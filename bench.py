@@ -11,8 +11,8 @@ update in FP32): 13.5 GB of state, 53 times the 256 MB last-level cache, so
 every step streams it from HBM.  One step = one stream-collide launch over
 the tiles of all 256 lattices (pull advection of the 37 populations from the
 coefficients, bounce-back with the moving-wall term, moments, H2
-equilibrium, regularized collision) plus one launch that computes each
-solve's FP64 momentum-exchange force, appends it to the history and
+equilibrium, regularized collision), in which one workgroup per solve
+computes the FP64 momentum-exchange force, appends it to the history and
 accumulates the lock-in sums.  The state is created and warmed up on the
 device before the timed steps.
 
@@ -55,6 +55,8 @@ KERNELS = {
     1: ("lbm::step_kernel<D2Q37, float, false, false, 256, false>", "kernels.hip"),
     2: ("lbm::coef_kernel<D2Q37, float, {rb}, false>", "coef.hip"),
 }
+# the plates of a few columns: several steps per launch, one when it is timed
+COLUMN_KERNEL = "lbm::column_kernel<D2Q37, float, false, false>"
 # committed rocprofv3 counters per (representation, workload)
 COUNTERS = {
     (1, "beam_box"): "step_kernel_beam_box_counters.json",
@@ -73,8 +75,8 @@ COEF_K_DEFAULT = 3  # the library's tile when none is given
 # 256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2.4 GHz
 FP32_VALU_PEAK_TFLOPS = 78.6
 # host sources that shape what a kernel's counters measure besides its own
-# file: the work order, tile sizes and layout
-ORDER_SOURCES = ("api.cpp", "batch.cpp", "internal.hpp", "solver.hpp")
+# file: the work order, tile sizes and layout, and the wall force
+ORDER_SOURCES = ("api.cpp", "batch.cpp", "internal.hpp", "solver.hpp", "force.hpp")
 
 
 def sources_hash(src):
@@ -409,6 +411,8 @@ def main():
            "algorithmic_bytes_per_launch": launch_bytes, "traffic": traffic,
            "device_bytes": state_bytes, "state_streams_from": resident}
     kernel = KERNELS[repr_][0].format(rb=tile or COEF_K_DEFAULT)
+    if a.workload == "plate_sweep":
+        kernel = COLUMN_KERNEL
     roofline = dict(hbm, bound="hbm")
     if repr_ != 1:
         # coefficients: 48 B and 401-469 flop per update (8.4-9.8 flop/B), at or
