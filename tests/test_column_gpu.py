@@ -54,3 +54,46 @@ def test_column_kernel(P, nx, ny, Q, geom, far, wall, sigma, coll):  # noqa: F81
             scale = max(np.max(np.abs(ox)), np.max(np.abs(oy)))
             assert np.max(np.abs(fx - ox)) <= tol * scale
             assert np.max(np.abs(fy - oy)) <= tol * scale
+
+
+@pytest.mark.parametrize("own_stream", [True, False])
+@pytest.mark.parametrize("graphs", [32, 0])
+def test_columns_beside_tiles(P, own_stream, graphs):  # noqa: F811
+    """Narrow plates in a batch with a box and a population member (their
+    launches run beside the others'): reads between calls, members that leave
+    and a member that ends early see the same bits as each solve alone."""
+    import torch
+    n = 150
+    kw = dict(Q=37, tau=0.9, omega=2 * math.pi / 40, window_first=5)
+    solves = [
+        W.Solve(geometry=W.PLATE, far=W.FAR_WALL, nx=4, ny=700, nsteps=n, window_count=n - 9, **kw),
+        W.Solve(geometry=W.BOX, far=W.FAR_EQ, nx=90, ny=75, box=(40, 30, 9, 11), nsteps=n,
+                window_count=n - 9, **kw),
+        W.Solve(geometry=W.PLATE, far=W.FAR_EQ, nx=7, ny=64, nsteps=n - 40, window_count=n - 60,
+                wall="ds", **kw),
+        W.Solve(geometry=W.PLATE, far=W.FAR_EQ, nx=40, ny=64, nsteps=n, window_count=n - 9, **kw),
+    ]
+    alone = []
+    for s in solves:
+        with P.Solver(P.params_from_solve(s)) as sv:
+            sv.step(s.nsteps)
+            alone.append((*sv.force_history(), sv.get_deviations(), sv.lockin()[0]))
+    stream = torch.cuda.Stream() if own_stream else torch.cuda.default_stream()
+    members = [P.Solver(P.params_from_solve(s), stream=stream) for s in solves]
+    with P.Batch(stream) as batch:
+        batch.set_graphs(graphs)
+        for m in members:
+            batch.add(m)
+        for k in (1, 64, 33):
+            batch.step(k)
+            for m, a in zip(members, alone):
+                fx, fy = m.force_history(m.steps_done - 1, 1)
+                assert (fx[0], fy[0]) == (a[0][m.steps_done - 1], a[1][m.steps_done - 1])
+        batch.remove(members[1])
+        members[1].step(n - 98)
+        batch.step(n - 98)
+        for m, a in zip(members, alone):
+            got = (*m.force_history(), m.get_deviations(), m.lockin()[0])
+            assert all(np.array_equal(x, y) for x, y in zip(got, a))
+    for m in members:
+        m.close()
