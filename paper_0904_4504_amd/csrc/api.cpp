@@ -412,11 +412,11 @@ void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& 
   auto add_pop = [&](int cx, int cy, long double scale, long double w, int vx, int vy, int ux,
                      int uy) {
     CellWeights& fc = cells.at(cx, cy);
-    const long double g[6] = {1, (long double)ux, (long double)uy, (long double)ux * ux,
-                              (long double)ux * uy, (long double)uy * uy};
+    const double sw = (double)(-scale * w);
+    const int g[6] = {1, ux, uy, ux * ux, ux * uy, uy * uy};
     for (int k = 0; k < 6; ++k) {
-      fc.wx[k] += (double)(-scale * vx * w * g[k]);
-      fc.wy[k] += (double)(-scale * vy * w * g[k]);
+      fc.wx[k] += sw * (vx * g[k]);
+      fc.wy[k] += sw * (vy * g[k]);
     }
   };
   // crossing-mass weights of the current column over its cells' coefficients
@@ -607,7 +607,8 @@ void build_force_tables(const lbm_params* p, const HostLattice& L, const Layout&
   }
 }
 
-void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay) {
+// The layout, and the force tables whose sizes it holds.
+void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay, ForceTables* tables) {
   const uint64_t es = p->storage == LBM_STORE_F64 ? 8 : 4;
   if (p->nx >= 64) {
     // row-interleaved: the Q rows of lattice row y are contiguous, so the Q
@@ -682,7 +683,7 @@ void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay) {
     lay->off_mwork = take(sizeof(WorkItem) * (uint64_t)lay->mnwork);
   }
   lay->off_solves = take(sizeof(int32_t));
-  ForceTables ft;
+  ForceTables& ft = *tables;
   build_force_tables(p, L, *lay, &ft);
   lay->nlinks = (int32_t)ft.links.size();
   lay->nfcells = (int32_t)ft.cells.size();
@@ -722,12 +723,10 @@ void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay) {
 
 namespace {
 
-int init_solver(lbm_solver* s) {
+int init_solver(lbm_solver* s, const ForceTables& ft) {
   const lbm_params* p = &s->p;
   const Layout& lay = s->lay;
   char* b = s->base;
-  ForceTables ft;
-  build_force_tables(p, s->lat, lay, &ft);
 
   SolveDesc& d = s->desc;
   std::memset(&d, 0, sizeof(d));
@@ -887,7 +886,8 @@ int lbm::create_solver(const lbm_params* p, void* stream, void* dev_buf, uint64_
     return rc;
   }
   s->p = *p;
-  make_layout(p, s->lat, &s->lay);
+  ForceTables tables;
+  make_layout(p, s->lat, &s->lay, &tables);
   s->stream = static_cast<hipStream_t>(stream);
   if (hipGetDevice(&s->device) != hipSuccess) {
     delete s;
@@ -912,7 +912,7 @@ int lbm::create_solver(const lbm_params* p, void* stream, void* dev_buf, uint64_
   s->graphs_ok = graphs;
   if (s->lay.column)
     s->column = column_plan((int)p->lattice, p->nx, {p->ny});
-  rc = init_solver(s);
+  rc = init_solver(s, tables);
   if (rc) {
     if (s->owned) (void)hipFree(s->base);
     delete s;
@@ -1076,7 +1076,8 @@ int required_bytes(const lbm_params* p, uint64_t* bytes, uint64_t* fine) {
   int rc = validate(p, &lat);
   if (rc) return rc;
   Layout lay;
-  make_layout(p, lat, &lay);
+  ForceTables tables;
+  make_layout(p, lat, &lay, &tables);
   *bytes = lay.total;
   if (!fine) return LBM_OK;
   // the same lists over plain cells and with the default K, wall tiles aside
@@ -1086,12 +1087,13 @@ int required_bytes(const lbm_params* p, uint64_t* bytes, uint64_t* fine) {
     const CoefGrid g = coef_grid(p, lay.coef_k);
     items += lay.mnwork - ordered_length(g.ntiles, g.tiles_x);
   }
-  const int64_t tables =
+  const int64_t force_cells =
       diffuse_box(p) && lay.mom
           ? (int64_t)sizeof(ForceCell) * lay.nfcells + (int64_t)sizeof(CellWeights) * lay.ncweights
           : 0;
   // (a kAlign for the rounding of each)
-  *fine = (uint64_t)std::max<int64_t>(0, items * (int64_t)sizeof(WorkItem) + tables) + 4 * kAlign;
+  *fine = (uint64_t)std::max<int64_t>(0, items * (int64_t)sizeof(WorkItem) + force_cells) +
+          4 * kAlign;
   return LBM_OK;
 }
 
