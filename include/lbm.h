@@ -195,7 +195,8 @@ int lbm_create_in(const lbm_params* p, void* hip_stream, void* dev_buf, uint64_t
  * earlier solver left in the array does not matter.  One such solver per
  * device at a time: while it lives (until lbm_destroy), another
  * lbm_create_static on that device returns LBM_ESCRATCH, as do parameters
- * whose lbm_required_bytes exceeds LBM_STATIC_SCRATCH_BYTES.  Launches of two
+ * whose lbm_required_bytes exceeds LBM_STATIC_SCRATCH_BYTES (the work list of
+ * a small lattice's finer tiles, a few KiB, not counted).  Launches of two
  * processes' static solvers on one device do not share the array (each
  * process has its own copy); work enqueued on the array by a destroyed solver
  * has completed (lbm_destroy waits). */
@@ -289,7 +290,9 @@ int lbm_destroy(lbm_solver* s);
  * A batch advances many solvers -- uneven lattices with the same lattice,
  * storage and collision, created on the batch's stream -- with one fused
  * launch per step and kind of member that updates all their tiles and reduces
- * their wall forces (narrow plates: one launch per several steps).  Each member runs the
+ * their wall forces (narrow plates: one launch per several steps, on a stream
+ * of the batch's own beside the other members' launches; later work on `hip_stream`
+ * waits for it).  Each member runs the
  * kernel it runs when stepped alone, so its results are bit-identical alone
  * and in any mix.  Members may join and leave between steps
  * (continuous batching); a member stops when it reaches its max_steps.
