@@ -25,7 +25,7 @@
 // the row behind the wall that their arrival pulls from (bounce-back with the
 // moving-wall term of the next step, or the specular share of the Maxwell
 // wall; zero for the rest-equilibrium far field), so the pull is one rule for
-// every cell.  The diffuse emission is added to the arrivals of the wall rows.
+// every cell.  Rows past the region's ends are left out (row_behind_moving).  The diffuse emission is added to the arrivals of the wall rows.
 // A cell's arithmetic does not depend on the split into workgroups or
 // launches, so any sequence of calls gives the same bits.
 //
@@ -223,8 +223,12 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
     sx -= sx >= nx ? nx : 0;
     base[k] = mine ? sx * ys + row : R;
   }
-  // rows whose populations cross a wall
+  // rows whose populations cross a wall, and the element of the column of
+  // offset 0 that their reflections go to, relative to the column's base
   const bool low = mine && !yper && y < R, high = mine && !yper && y >= ny - R;
+  const int behind_low = low ? row_behind_moving(row, y, region) : -1;
+  const int behind_high = high ? row_behind_far(row, ny - 1 - y, region) : -1;
+  const int to_low = behind_low - row, to_high = behind_high - row;
   // write the cell's populations, and those that cross a wall to where their
   // arrivals in the step with wall velocity U pull from
   auto put = [&](double U) __attribute__((always_inline)) {
@@ -241,39 +245,39 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
           if constexpr (L::vy[q] < 0)
             if (y < -L::vy[q]) {
               cm += (double)f[q];
-              pop[own - 1 - 2 * y + to * cap] = ws * f[q];
+              if (behind_low >= 0) pop[own + to_low + to * cap] = ws * f[q];
             }
         });
         cross[y * kColumnMaxNx + x] = cm;
-      } else {
+      } else if (behind_low >= 0) {
         const double ladd = ladd_scale * U;
         static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
           constexpr int q = decltype(qc)::value;  // the arrival
           constexpr int vx = L::vx[q], vy = L::vy[q], o = opposite<L>(q);
           if constexpr (vy > 0)
             if (y < vy)
-              pop[base[R + vx] - 1 - 2 * y + q * cap] =
+              pop[base[R + vx] + to_low + q * cap] =
                   f[o] + (S)(lat.w[L::orbit[q]] * vx * ladd);
         });
       }
     }
-    if (high && !far_eq) {
+    if (behind_high >= 0 && !far_eq) {
       const int k = ny - 1 - y;
       static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
         constexpr int q = decltype(qc)::value;
         constexpr int vx = L::vx[q], vy = L::vy[q], o = opposite<L>(q);
         if constexpr (vy < 0)
-          if (k < -vy) pop[base[R + vx] + 1 + 2 * k + q * cap] = f[o];
+          if (k < -vy) pop[base[R + vx] + to_high + q * cap] = f[o];
       });
     }
   };
-  if (high && far_eq) {
+  if (behind_high >= 0 && far_eq) {
     const int k = ny - 1 - y;
     static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
       constexpr int q = decltype(qc)::value;
       constexpr int vx = L::vx[q], vy = L::vy[q];
       if constexpr (vy < 0)
-        if (k < -vy) pop[base[R + vx] + 1 + 2 * k + q * cap] = S(0);
+        if (k < -vy) pop[base[R + vx] + to_high + q * cap] = S(0);
     });
   }
   if (mine) put(d.drive[n0].u);

@@ -36,6 +36,20 @@ __host__ __device__ constexpr int column_stride(int region, int nx, int es) {
   const int ys = region + (mod + want - region % mod) % mod;
   return ys * nx <= kColumnCells ? ys : region;
 }
+// Row of a tile's region behind a wall that the reflection of a population
+// crossing it goes to, for a cell in region row `row`, `away` rows from the
+// wall (moving wall below, far wall above); -1: outside the region.  A tile whose
+// region just reaches a wall has cells whose reflections land past its ends:
+// nothing that is still exact pulls from there, and the element belongs to the
+// next lattice column or the next velocity's plane.
+__host__ __device__ constexpr int row_behind_moving(int row, int away, int region) {
+  const int g = row - 1 - 2 * away;
+  return g >= 0 && g < region ? g : -1;
+}
+__host__ __device__ constexpr int row_behind_far(int row, int away, int region) {
+  const int g = row + 1 + 2 * away;
+  return g >= 0 && g < region ? g : -1;
+}
 // Shape of a column-kernel launch: rows per workgroup, steps per launch (odd),
 // threads for the widest lattice of the launch.
 struct ColumnShape {

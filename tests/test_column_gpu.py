@@ -56,6 +56,72 @@ def test_column_kernel(P, nx, ny, Q, geom, far, wall, sigma, coll):  # noqa: F81
             assert np.max(np.abs(fy - oy)) <= tol * scale
 
 
+# lattices so long that a workgroup's rows fill the LDS planes, some tiles'
+# regions just reaching a wall
+FULL = [(37, 16, 2309), (37, 16, 2310), (37, 8, 3339), (37, 7, 2307), (9, 16, 2309)]
+
+
+@pytest.mark.parametrize("far,wall,sigma", [(W.FAR_WALL, "bb", 1.0), (W.FAR_EQ, "bb", 1.0),
+                                            (W.FAR_WALL, "ds", 1.0), (W.FAR_EQ, "maxwell", 0.35)])
+@pytest.mark.parametrize("Q,nx,ny", FULL)
+def test_full_planes(P, Q, nx, ny, far, wall, sigma):  # noqa: F811
+    """14 steps of full planes in one call, and the same bits from one step per
+    call; FP64 against the long-double oracle within 1e-12."""
+    n = 14
+    print(f"case {nx}x{ny} Q{Q} {far} {wall}", flush=True)
+    v, w, th = P.lattice(Q)
+    for storage in ("f64", "f32dev"):
+        s = W.Solve(Q=Q, geometry=W.PLATE, far=far, nx=nx, ny=ny, tau=0.9,
+                    omega=2 * math.pi / 40, nsteps=n, window_first=2, window_count=n - 4,
+                    storage=storage, wall=wall, accommodation=sigma)
+        f0 = _f0(s, w, seed=13, amp=1e-3)
+        out = []
+        for split in ([n], [1] * n):
+            with P.Solver(P.params_from_solve(s)) as sv:
+                sv.set_populations(f0)
+                for k in split:
+                    sv.step(k)
+                out.append((*sv.force_history(), sv.get_deviations(), sv.lockin()[0]))
+        assert all(np.array_equal(a, b) for a, b in zip(*out))
+        if storage == "f64":
+            ox, oy, of = O.run(_oracle_params(s), n, f0=f0, want_state=True, variant="ld")
+            dev = of - w[:, None, None] * s.rho0
+            assert np.max(np.abs(out[0][2] - dev)) <= \
+                1e-12 * np.max(np.abs(dev)) + 2 * np.spacing(np.max(w))
+            scale = max(np.max(np.abs(ox)), np.max(np.abs(oy)))
+            assert np.max(np.abs(out[0][0] - ox)) <= 1e-12 * scale
+            assert np.max(np.abs(out[0][1] - oy)) <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("nx,lengths", [(8, [3101] * 8), (16, [700, 1311, 902]),
+                                        (4, [5832, 6795, 1186, 6816, 4385])])
+def test_batch_of_long_plates(P, nx, lengths):  # noqa: F811
+    """Plates whose total length makes the workgroups of their launch take more
+    rows than each plate's own: the bits of every plate alone."""
+    import torch
+    n = 21
+    solves = [W.Solve(Q=37, geometry=W.PLATE, far=(W.FAR_WALL, W.FAR_EQ)[i % 2], nx=nx, ny=ny,
+                      tau=0.8, omega=2 * math.pi / 40, nsteps=n, window_first=0, window_count=n)
+              for i, ny in enumerate(lengths)]
+    alone = []
+    for s in solves:
+        with P.Solver(P.params_from_solve(s)) as sv:
+            for _ in range(n):
+                sv.step(1)
+            alone.append((*sv.force_history(), sv.get_deviations()))
+    stream = torch.cuda.Stream()
+    members = [P.Solver(P.params_from_solve(s), stream=stream) for s in solves]
+    with P.Batch(stream) as batch:
+        for m in members:
+            batch.add(m)
+        batch.step(n)
+        for m, a in zip(members, alone):
+            got = (*m.force_history(), m.get_deviations())
+            assert all(np.array_equal(x, y) for x, y in zip(got, a))
+    for m in members:
+        m.close()
+
+
 @pytest.mark.parametrize("own_stream", [True, False])
 @pytest.mark.parametrize("graphs", [32, 0])
 def test_columns_beside_tiles(P, own_stream, graphs):  # noqa: F811
