@@ -392,9 +392,12 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
     }
   }
   if (force) {
-    // the forces of the steps, written by lane 63 above
-    for (int i = lane; i < 2 * nsub; i += 64)
-      d.hist[2 * ((n0 + (i >> 1)) % d.hist_cap) + (i & 1)] = hist[i];
+    // the forces of the steps, written by lane 63 above; of a ring shorter than
+    // the launch the last hist_cap only, so that each slot is written once
+    const int64_t cap_h = d.hist_cap;
+    const int s0 = nsub > cap_h ? nsub - (int)cap_h : 0;
+    for (int i = 2 * s0 + lane; i < 2 * nsub; i += 64)
+      d.hist[2 * ((n0 + (i >> 1)) % cap_h) + (i & 1)] = hist[i];
     if (lane == 63)
       for (int k = 0; k < 6; ++k) d.state->lockin[k] = lk[k];
   }

@@ -122,6 +122,25 @@ def test_batch_of_long_plates(P, nx, lengths):  # noqa: F811
         m.close()
 
 
+@pytest.mark.parametrize("capacity", [1, 2, 5])
+@pytest.mark.parametrize("Q", [9, 37])
+def test_short_force_ring(P, Q, capacity):  # noqa: F811
+    """A force ring shorter than the steps of one launch holds the newest
+    samples after every call."""
+    n = 97
+    s = W.Solve(Q=Q, geometry=W.PLATE, far=W.FAR_EQ, nx=4, ny=40, tau=0.9,
+                omega=2 * math.pi / 40, nsteps=n, window_first=0, window_count=n)
+    with P.Solver(P.params_from_solve(s)) as sv:
+        sv.step(n)
+        fx, fy = sv.force_history()
+    with P.Solver(P.params_from_solve(s, history_capacity=capacity)) as sv:
+        for k in (31, 3, 2, 61):
+            sv.step(k)
+            at, m = sv.steps_done, min(capacity, sv.steps_done)
+            gx, gy = sv.force_history(at - m, m)
+            assert np.array_equal(gx, fx[at - m:at]) and np.array_equal(gy, fy[at - m:at])
+
+
 @pytest.mark.parametrize("own_stream", [True, False])
 @pytest.mark.parametrize("graphs", [32, 0])
 def test_columns_beside_tiles(P, own_stream, graphs):  # noqa: F811
