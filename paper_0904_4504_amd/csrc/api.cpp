@@ -131,28 +131,72 @@ ColumnShape column_shape(int Q, int nx, int rows, int nsub) {
   return sh;
 }
 
-// Steps per launch: a step's share of the launch (about 4 us) falls as 1/T, the
-// halo it updates (R rows per step left) grows as R (T - 1) / 2 rows per side;
-// D2Q37 is flat from 9 to 15 (a 4 x 2048 plate: 1.67 us per step at 5, 1.47 at
-// 11), D2Q9 from 15 to 31 (4 x 256 FP64: 1.32 us at 5, 0.90 at 31).
-// Rows per workgroup: the fewest with which the launch's workgroups get a
-// compute unit each (five 4 x 2048 plates, 256 CUs: 4.2 us per step at 24
-// rows, 430 workgroups; 2.7 at 41 to 48), 8 at least (below, the halo is most
-// of the work: 0.89 us at 4 to 8 for 4 x 256).
-ColumnPlan column_plan(int Q, int nx, const std::vector<int>& ny) {
-  const int R = Q == 9 ? D2Q9::R : D2Q37::R;
-  const int most = Q == 9 ? kColumnMaxSub : 11, least_rows = 8;
-  ColumnPlan plan;
-  // the halo leaves room for the least rows; wide lattices take fewer steps
-  for (int t = 1; t <= most; t += 2)
-    if ((least_rows + 2 * R * t) * nx <= kColumnCells) plan.max_sub = t;
-  const int fit = kColumnCells / nx;
-  for (plan.rows = least_rows;; ++plan.rows) {
-    int64_t groups = 0;
-    for (int n : ny) groups += (n + plan.rows - 1) / plan.rows;
-    if (groups <= 256 || plan.rows + 1 + 2 * R * std::min(plan.max_sub, 9) > fit) break;
+// Lanes per LDS bank, on average over the parts of a wavefront that are served
+// together, when it reads one element per cell of rows of nx columns.
+static double bank_load(int nx, int ys, int es) {
+  const int part = es == 8 ? 16 : 32;  // lanes served together, and banks
+  int sum = 0;
+  for (int l0 = 0; l0 < 64; l0 += part) {
+    int hits[32] = {}, most = 0;
+    for (int l = l0; l < l0 + part; ++l)
+      most = std::max(most, ++hits[(l % nx * ys + l / nx) % part]);
+    sum += most;
   }
-  while (plan.max_sub > 1 && plan.rows + 2 * R * plan.max_sub > fit) plan.max_sub -= 2;
+  return (double)sum / (64 / part);
+}
+
+// A step's share of a launch (about 4 us) falls as 1/T, the halo it updates
+// grows as R (T - 1) / 2 rows per side.
+// While the workgroups all run at once (one per compute unit, two of D2Q9's FP32
+// ones): the fewest rows for that, 8 at least (below, the halo is most of the
+// work), and the most steps that fit, up to 11 (D2Q37; 4 x 2048 FP32, us per step
+// in calls of 1024: 1.89 at 5, 1.62 at 9, 1.56 at 11, 1.67 at 13) or 27 (D2Q9;
+// 4 x 256, FP32 / FP64: 0.77 / 0.82 at 15, 0.70 / 0.75 at 23, 0.69 / 0.76 at 27,
+// 0.78 / 0.87 at 31).
+// Longer lattices and batches, or widths that leave one step only: what costs
+// least, in updates of a row: the rounds of workgroups (two of D2Q9 at once) times
+// what one does per step -- the loads and stores of its region (a row 3 or 5
+// updates, FP32 or FP64; fitted) once in T steps, the updates, a tenth more for
+// every further lane per bank, and the barriers, 100 cells' updates -- and the
+// launch, 1300 (D2Q9) or 500 cells' updates.
+// D2Q37 FP32, us per step, against the most steps that leave 8 rows of a full
+// plane: 7 x 16384 6.0 and 21.8 (64 rows per column, a row's lanes all on one
+// bank), 8 x 16384 6.9 and 10.0, 61 plates of 8 x 2048 62 and 83 (FP64 98 and 119).
+ColumnPlan column_plan(int Q, bool f64, int nx, const std::vector<int>& ny) {
+  const int R = Q == 9 ? D2Q9::R : D2Q37::R;
+  const int most = Q == 9 ? kColumnMaxSub : 11, fit = kColumnCells / nx, es = f64 ? 8 : 4;
+  auto groups = [&](int rows) {
+    int64_t g = 0;
+    for (int n : ny) g += (n + rows - 1) / rows;
+    return g;
+  };
+  ColumnPlan plan;
+  plan.rows = 8;
+  const int abreast = Q == 9 ? 512 : 256;
+  while (plan.rows < fit && groups(plan.rows) > (f64 ? 256 : abreast)) ++plan.rows;
+  plan.max_sub = most;
+  auto banks = [&](int region) { return bank_load(nx, column_stride(region, nx, es), es); };
+  while (plan.max_sub > 1) {
+    const int region = plan.rows + 2 * R * plan.max_sub;
+    if (region <= fit && banks(region) <= 4) return plan;
+    plan.max_sub -= 2;
+  }
+  double least = INFINITY;
+  for (int t = 1; t <= most; t += 2)
+    for (int rows = 4; rows + 2 * R * t <= fit; ++rows) {
+      const int region = rows + 2 * R * t;
+      if (banks(region) > 4) continue;
+      const double work = (f64 ? 5.0 : 3.0) * region / t +
+                          (rows + R * (t - 1)) * (0.9 + 0.1 * banks(region)) + 100.0 / nx;
+      const double rounds = (double)groups(rows) / abreast;
+      const double cost = (rounds < 4 ? std::ceil(rounds) : rounds + 0.5) * work +
+                          (Q == 9 ? 1300.0 : 500.0) / (nx * t);
+      if (cost < least) {
+        least = cost;
+        plan.rows = rows;
+        plan.max_sub = t;
+      }
+    }
   return plan;
 }
 
@@ -215,9 +259,15 @@ bool uses_coefficients(const lbm_params* p) {
 }
 
 // Stepped by the column kernel: plates and periodic lattices of a few columns
-// kept as populations (see column.hip).
+// kept as populations (see column.hip).  14 to 16 columns of D2Q37 leave room for
+// 3 steps per launch and about as much halo as rows, so long ones go to the
+// population kernel (16 columns, us per step, column / population kernel: 4096
+// rows FP32 6.2 / 7.5, FP64 9.6 / 10.9, 8192 rows 11.8 / 9.1, 19.2 / 14.4).  The choice
+// is by the lattice alone, since its bits follow from it: batches of many short
+// ones take longer (31 plates of 16 x 2048 FP32 82 / 65, FP64 124 / 114; alone 4.1 / 6.8).
 bool uses_columns(const lbm_params* p) {
-  return !uses_coefficients(p) && p->geometry != LBM_GEOM_BOX && p->nx <= kColumnMaxNx;
+  if (uses_coefficients(p) || p->geometry == LBM_GEOM_BOX || p->nx > kColumnMaxNx) return false;
+  return p->lattice == 9 || p->nx < 14 || (int64_t)p->nx * p->ny <= kColumnWideCells;
 }
 
 int validate(const lbm_params* p, HostLattice* lat) {
@@ -911,7 +961,7 @@ int lbm::create_solver(const lbm_params* p, void* stream, void* dev_buf, uint64_
   }
   s->graphs_ok = graphs;
   if (s->lay.column)
-    s->column = column_plan((int)p->lattice, p->nx, {p->ny});
+    s->column = column_plan((int)p->lattice, p->storage == LBM_STORE_F64, p->nx, {p->ny});
   rc = init_solver(s, tables);
   if (rc) {
     if (s->owned) (void)hipFree(s->base);

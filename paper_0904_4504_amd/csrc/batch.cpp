@@ -118,7 +118,8 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
       b->column_nx = std::max(b->column_nx, s->p.nx);
       column_ny.push_back(s->p.ny);
     }
-  if (b->column_nx) b->column = column_plan(b->Q, b->column_nx, column_ny);
+  if (b->column_nx)
+    b->column = column_plan(b->Q, b->storage == LBM_STORE_F64, b->column_nx, column_ny);
   uint64_t state[kGroups] = {};  // state bytes per group
   auto kind = [](const lbm_solver* s) {
     const Layout& lay = s->lay;

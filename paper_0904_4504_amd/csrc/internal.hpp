@@ -125,7 +125,7 @@ constexpr int kStepBlock = 1024;
 struct ColumnPlan {
   int rows = 0, max_sub = 1;
 };
-ColumnPlan column_plan(int Q, int nx, const std::vector<int>& ny);
+ColumnPlan column_plan(int Q, bool f64, int nx, const std::vector<int>& ny);
 ColumnShape column_shape(int Q, int nx, int rows, int nsub);
 // n as a sum of odd numbers of at most max_sub (odd): the steps per launch of
 // a call of n steps.

@@ -72,15 +72,22 @@ static void check() {
     // every plan of lattices of this width: it depends on their lengths only
     // through the workgroups they take
     std::set<std::pair<int, int>> plans;
-    for (int groups = 1; groups < 70; ++groups) {
-      const ColumnPlan one = column_plan(Q, nx, {groups * 40});
-      plans.insert({one.rows, one.max_sub});
-      const ColumnPlan many = column_plan(Q, nx, std::vector<int>(groups, 4096));
-      plans.insert({many.rows, many.max_sub});
-    }
-    for (int ny = 2000; ny < 20000; ny += 61) {
-      const ColumnPlan p = column_plan(Q, nx, {ny});
-      plans.insert({p.rows, p.max_sub});
+    for (bool f64 : {false, true}) {
+      auto add = [&](const std::vector<int>& ny) {
+        const ColumnPlan p = column_plan(Q, f64, nx, ny);
+        if (p.rows < 1 || p.max_sub < 1 || (p.rows + 2 * R * p.max_sub) * nx > kColumnCells)
+          fail("plan", Q, nx, p.rows, p.max_sub, ny[0], (int)ny.size());
+        // a row's cells on a bank each, or nearly
+        if (nx > 4 && column_stride(p.rows + 2 * R * p.max_sub, nx, f64 ? 8 : 4) % (f64 ? 16 : 32) == 0)
+          fail("columns on one bank", Q, nx, p.rows, p.max_sub, ny[0], (int)ny.size());
+        plans.insert({p.rows, p.max_sub});
+      };
+      for (int groups = 1; groups < 70; ++groups) {
+        add({groups * 40});
+        add(std::vector<int>(groups, 4096));
+      }
+      for (int ny = 2000; ny < 20000; ny += 151) add({ny});
+      for (int ny = 20000; ny < 4000000; ny += ny / 7) add({ny});
     }
     for (const auto& [rows, most] : plans) {
       std::set<int> subs;

@@ -122,6 +122,27 @@ def test_batch_of_long_plates(P, nx, lengths):  # noqa: F811
         m.close()
 
 
+@pytest.mark.parametrize("nx,ny", [(16, 6250), (16, 6251), (14, 7142), (14, 7143), (13, 7700)])
+def test_wide_line(P, nx, ny):  # noqa: F811
+    """Lengths on both sides of the line where D2Q37 lattices of 14 to 16 columns
+    leave the column kernel: 5 FP64 steps against the long-double oracle."""
+    n = 5
+    s = W.Solve(Q=37, geometry=W.PLATE, far=W.FAR_WALL, nx=nx, ny=ny, tau=0.9, storage="f64",
+                omega=2 * math.pi / 40, nsteps=n, window_first=0, window_count=n)
+    v, w, th = P.lattice(37)
+    f0 = _f0(s, w, seed=17, amp=1e-3)
+    with P.Solver(P.params_from_solve(s)) as sv:
+        sv.set_populations(f0)
+        sv.step(n)
+        fx, fy = sv.force_history()
+        dev = sv.get_deviations()
+    ox, oy, of = O.run(_oracle_params(s), n, f0=f0, want_state=True, variant="ld")
+    want = of - w[:, None, None] * s.rho0
+    assert np.max(np.abs(dev - want)) <= 1e-12 * np.max(np.abs(want)) + 2 * np.spacing(np.max(w))
+    scale = max(np.max(np.abs(ox)), np.max(np.abs(oy)))
+    assert np.max(np.abs(fx - ox)) <= 1e-12 * scale and np.max(np.abs(fy - oy)) <= 1e-12 * scale
+
+
 @pytest.mark.parametrize("capacity", [1, 2, 5])
 @pytest.mark.parametrize("Q", [9, 37])
 def test_short_force_ring(P, Q, capacity):  # noqa: F811
