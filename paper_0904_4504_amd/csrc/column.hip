@@ -23,9 +23,11 @@
 //
 // Walls: the populations that cross a wall are written a second time, into
 // the row behind the wall that their arrival pulls from (bounce-back with the
-// moving-wall term of the next step, or the specular share of the Maxwell
+// moving-wall term of the next step, or the specular image of the Maxwell
 // wall; zero for the rest-equilibrium far field), so the pull is one rule for
-// every cell.  Rows past the region's ends are left out (row_behind_moving).  The diffuse emission is added to the arrivals of the wall rows.
+// every cell.  Rows past the region's ends are left out (row_behind_moving).  At
+// a diffuse or Maxwell wall the arrivals of the wall rows mix it with the
+// emission, in FP64.
 // A cell's arithmetic does not depend on the split into workgroups or
 // launches, so any sequence of calls gives the same bits.
 //
@@ -194,7 +196,8 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
   const int64_t win0 = d.lockin_first - n0, win1 = win0 + d.lockin_count;
   const bool far_eq = d.far == FAR_EQ, diffuse = DSW && d.wall == WALL_DS;
   const WallEmission emission = wall_emission(d);
-  const S rho0 = (S)rho0d, ws = (S)(1.0 - sigma);
+  const bool specular = sigma != 1.0;
+  const S rho0 = (S)rho0d;
   const double inv_thd = 1.0 / lat.theta;
   const S th = (S)lat.theta, inv_th = (S)(1.0 / lat.theta);
   const S h2 = (S)(0.5 / (lat.theta * lat.theta));
@@ -245,7 +248,7 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
           if constexpr (L::vy[q] < 0)
             if (y < -L::vy[q]) {
               cm += (double)f[q];
-              if (behind_low >= 0) pop[own + to_low + to * cap] = ws * f[q];
+              if (behind_low >= 0 && specular) pop[own + to_low + to * cap] = f[q];
             }
         });
         cross[y * kColumnMaxNx + x] = cm;
@@ -340,7 +343,8 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
       });
       if (DSW && diffuse && low) {
         // the emission w (ea + eb (e1 vx + e2 vx^2)) of the cell's column (see
-        // ds_arrival)
+        // ds_arrival), mixed in FP64 with the specular image pulled from behind
+        // the wall, rounded once
         const double U = drive[s].u;
         double cm = 0.0;
 #pragma unroll
@@ -353,8 +357,9 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
           constexpr int q = decltype(qc)::value;
           constexpr int vx = L::vx[q], vy = L::vy[q];
           if constexpr (vy > 0) {
-            const S e = (S)(lat.w[L::orbit[q]] * (ea + eb * (vx * (e1 + vx * e2))));
-            f[q] += y < vy ? e : S(0);
+            double e = lat.w[L::orbit[q]] * (ea + eb * (vx * (e1 + vx * e2)));
+            if (specular) e += (1.0 - sigma) * (double)f[q];
+            f[q] = y < vy ? (S)e : f[q];
           }
         });
       }
