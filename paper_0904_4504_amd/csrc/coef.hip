@@ -165,12 +165,13 @@ constexpr bool source_used(int vx, int iy) {
 // up different ones.  w: the weights by |vx| and |vy| (zero where the lattice
 // has no such velocity).  s[n - 1][lo][hi][b]: the sum of w t^b over the
 // velocities of normal speed n and tangential speed -lo <= t <= hi, b = 0..4;
-// sd: the first three in FP64, for the diffuse wall.
+// wd, sd: the same in FP64, for the diffuse wall.
 template <typename S, bool DSW>
 struct WallTable {
   S w[4][4];
   S s[3][4][4][5];
-  double sd[DSW ? 3 : 1][4][4][3];
+  double wd[DSW ? 4 : 1][4];
+  double sd[DSW ? 3 : 1][4][4][5];
 };
 
 // Entries of thread i < 48: selected from the kernel's arguments, without a
@@ -193,7 +194,10 @@ __device__ __forceinline__ void fill_wall_table(WallTable<S, DSW>& tab, const Ke
       }
     });
   });
-  if (i < 16) tab.w[i >> 2][i & 3] = (S)w;
+  if (i < 16) {
+    tab.w[i >> 2][i & 3] = (S)w;
+    if constexpr (DSW) tab.wd[i >> 2][i & 3] = w;
+  }
   double m[5] = {wn[0], 0, 0, 0, 0};
 #pragma unroll
   for (int t = 1; t <= R; ++t) {
@@ -209,7 +213,7 @@ __device__ __forceinline__ void fill_wall_table(WallTable<S, DSW>& tab, const Ke
   for (int b = 0; b < 5; ++b) tab.s[n - 1][lo][hi][b] = (S)m[b];
   if constexpr (DSW)
 #pragma unroll
-    for (int b = 0; b < 3; ++b) tab.sd[n - 1][lo][hi][b] = m[b];
+    for (int b = 0; b < 5; ++b) tab.sd[n - 1][lo][hi][b] = m[b];
 }
 
 // Moments of the arrivals from the walls at fluid cell (x, y): each link
@@ -238,15 +242,20 @@ __device__ __forceinline__ void fill_wall_table(WallTable<S, DSW>& tab, const Ke
 // 48 threads while the staging loads are under way (summed by each lane from
 // the weights they were seven look-ups and five chains of seven additions per
 // mirror cell and as many again in FP64 for the crossing mass), the reads of
-// a mirror cell, or of a few specular sources, are in flight together, and
+// a mirror cell, or of two specular sources, are in flight together, and
 // the column constants arrive behind the crossing mass.  The corner links of
 // a cell are one unrolled pass of selects (in a loop over pairs of speeds, up
 // to nine round trips to LDS, they were the longest chain of a bounce-back
 // box).  One row per wavefront, box of 256 x 256, bounce-back / diffuse /
-// Maxwell, us per step: FP32 8.8 -> 6.9 / 12.5 -> 8.4 / - -> 11.9, FP64 9.9 ->
-// 7.8 / - -> 9.1 / - -> 13.4 (5.0 and 6.2 without walls).  The specular share
+// Maxwell, us per step: FP32 8.8 -> 6.7 / 12.5 -> 8.2 / - -> 12.6, FP64 9.9 ->
+// 7.7 / - -> 9.0 / - -> 12.4 (5.0 and 6.2 without walls).  The specular share
 // is the rest of the Maxwell wall: its 21 sources unrolled over t; rolled
 // over t, the two signs together, 15.3.
+//
+// What a diffuse or Maxwell wall sends back is FP64 whatever the storage,
+// emission, specular share and mixing, and a mirror cell's sums are rounded
+// to S once (FP32 with sums and share in FP32: diffuse 8.1, Maxwell 11.6 us;
+// registers and wavefronts per SIMD are the same).
 //
 // Every cell read here (mirror cells, the specular sources and the crossing
 // rows of the diffuse wall) lies within R - 1 cells of (x, y) along each axis
@@ -342,11 +351,7 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
           const double cnt = sgn * (double)c.cnt;
 #pragma unroll
           for (int n = r + 1; n <= R; ++n) {
-            const double* sd;
-            if constexpr (sizeof(S) == 8)
-              sd = tab.s[n - 1][lo][hi];
-            else
-              sd = tab.sd[DSW ? n - 1 : 0][lo][hi];
+            const double* const sd = tab.sd[DSW ? n - 1 : 0][lo][hi];
             cm = fmadd(sd[0], fmadd((double)n, fmadd((double)n, cnn, -bn), a0), cm);
             cm = fmadd(sd[1], fmadd((double)n, cnt, -bt), cm);
             cm = fmadd(sd[2], ctt, cm);
@@ -365,49 +370,60 @@ __device__ __forceinline__ Mom<S> wall_moments(const SolveDesc& d, const Pair<S>
       for (int r = 0; r < R - k; ++r) {
         const int n = k + 1 + r;
         const S vn = (S)(sg * n);
-        const S* const st = tab.s[n - 1][lo][hi];
-        const S s0 = st[0], s1 = st[1], s2 = st[2], s3 = st[3], s4 = st[4];
         const int pc = w0 + sg * r;
-        S G, H, K;
         if (diffuse) {
-          G = (S)(ax ? ea + eb * (e1 * (sg * n) + e2 * (n * n)) : ea);
-          H = (S)(ax ? 0.0 : eb * e1);
-          K = (S)(ax ? 0.0 : eb * e2);
+          // in FP64, the emission and its mixing with the specular image, and
+          // rounded once
+          const double vd = sg * n;
+          double f0 = 0, f1 = 0, f2 = 0;
+          if (DSW && sigma != 1.0) {
+            // Maxwell wall: the specular share, the population of (t, -v_n) that
+            // crossed the wall from the mirror cell's neighbour t cells back
+            // (plus the moving-wall term on the faces normal to the motion)
+            const double ws = 1.0 - sigma, ladn = ax ? d.ladd_scale * U : 0.0;
+            const double* const wt = tab.wd[DSW ? n : 0];
+            auto source = [&](int t) __attribute__((always_inline)) {
+              return cell(ax ? pc : x - t, ax ? y - t : pc, ax);
+            };
+            Cell next = source(-R);
+#pragma unroll
+            for (int t = -R; t <= R; ++t) {
+              // the reads of the next source in flight, not of all
+              const Cell c = next;
+              if (t < R) next = source(t + 1);
+              const double ts = t, bn = (double)c.bn - ladn;
+              const double g =
+                  fmadd(ts, fmadd(ts, (double)c.ctt, fmadd(-vd, (double)c.cnt, (double)c.bt)),
+                        fmadd(vd, fmadd(vd, (double)c.cnn, -bn), (double)c.a0));
+              const double f = t >= -lo && t <= hi ? wt[t < 0 ? -t : t] * g : 0.0;
+              f0 += f;
+              f1 = fmadd(ts, f, f1);
+              f2 = fmadd(ts * ts, f, f2);
+              asm volatile("" : "+v"(f0), "+v"(f1), "+v"(f2)::"memory");
+            }
+            f0 *= ws;
+            f1 *= ws;
+            f2 *= ws;
+          }
+          const double* const sd = tab.sd[DSW ? n - 1 : 0][lo][hi];
+          const double s0 = sd[0], s1 = sd[1], s2 = sd[2], s3 = sd[3], s4 = sd[4];
+          const double G = ax ? fmadd(eb, vd * fmadd(vd, e2, e1), ea) : ea;
+          const double H = ax ? 0.0 : eb * e1, K = ax ? 0.0 : eb * e2;
+          f0 = fmadd(s0, G, fmadd(s1, H, fmadd(s2, K, f0)));
+          f1 = fmadd(s1, G, fmadd(s2, H, fmadd(s3, K, f1)));
+          f2 = fmadd(s2, G, fmadd(s3, H, fmadd(s4, K, f2)));
+          add((S)f0, (S)f1, (S)f2, vn);
         } else {
+          const S* const st = tab.s[n - 1][lo][hi];
+          const S s0 = st[0], s1 = st[1], s2 = st[2], s3 = st[3], s4 = st[4];
           Cell c = cell(ax ? pc : x, ax ? y : pc, ax);
           // the moving-wall term acts like a shift of bx by its amplitude
           c.bn -= ax ? lad : S(0);
           c.bt -= ax ? S(0) : lad;
-          G = fmadd(vn, fmadd(vn, c.cnn, -c.bn), c.a0);
-          H = fmadd(vn, c.cnt, -c.bt);
-          K = c.ctt;
-        }
-        add(fmadd(s0, G, fmadd(s1, H, s2 * K)), fmadd(s1, G, fmadd(s2, H, s3 * K)),
-            fmadd(s2, G, fmadd(s3, H, s4 * K)), vn);
-        if (DSW && diffuse && sigma != 1.0) {
-          // Maxwell wall: the specular share, the population of (t, -v_n) that
-          // crossed the wall from the mirror cell's neighbour t cells back
-          // (plus the moving-wall term on the faces normal to the motion)
-          const S ws = (S)(1.0 - sigma);
-          S f0 = 0, f1 = 0, f2 = 0, wt[R + 1];
-#pragma unroll
-          for (int t = 0; t <= R; ++t) wt[t] = ws * tab.w[n][t];
-#pragma unroll
-          for (int t = -R; t <= R; ++t) {
-            const S w = t >= -lo && t <= hi ? wt[t < 0 ? -t : t] : S(0);
-            Cell c = cell(ax ? pc : x - t, ax ? y - t : pc, ax);
-            c.bn -= ax ? lad : S(0);
-            const S ts = (S)t;
-            const S g = w * fmadd(ts, fmadd(ts, c.ctt, fmadd(-vn, c.cnt, c.bt)),
-                                  fmadd(vn, fmadd(vn, c.cnn, -c.bn), c.a0));
-            const S f = w == S(0) ? S(0) : g;
-            f0 += f;
-            f1 = fmadd(ts, f, f1);
-            f2 = fmadd(ts * ts, f, f2);
-            // the reads of a few cells in flight, not of all
-            if (sizeof(S) == 8 || t % 2 == 0) asm volatile("" : "+v"(f0), "+v"(f1), "+v"(f2)::"memory");
-          }
-          add(f0, f1, f2, vn);
+          const S G = fmadd(vn, fmadd(vn, c.cnn, -c.bn), c.a0);
+          const S H = fmadd(vn, c.cnt, -c.bt), K = c.ctt;
+          add(fmadd(s0, G, fmadd(s1, H, s2 * K)), fmadd(s1, G, fmadd(s2, H, s3 * K)),
+              fmadd(s2, G, fmadd(s3, H, s4 * K)), vn);
         }
       }
     }

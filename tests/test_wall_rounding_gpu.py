@@ -57,3 +57,86 @@ def test_narrow_plate(P, Q, wall):  # noqa: F811
             assert np.all(np.abs(out[q, y] - exact) <= 0.5 * ulp * (1 + 1e-6) + 1e-18)
             n += nx
     assert n > 0
+
+
+def _face_sums(v, w, n, sg, ax, lo, hi):
+    """Velocities of normal speed n towards the fluid and their tangential part,
+    those with a source behind the wall."""
+    for q, (vx, vy) in enumerate(v.tolist()):
+        vn, t = (vx, vy) if ax else (vy, vx)
+        if vn == sg * n and -lo <= t <= hi:
+            yield w[q], vx, vy
+
+
+@pytest.mark.parametrize("wall", ["ds", "maxwell"])
+@pytest.mark.parametrize("Q", [9, 37])
+@pytest.mark.parametrize("geom", [W.PLATE, W.BOX])
+def test_coefficients(P, geom, Q, wall):  # noqa: F811
+    """First step from rest of a coefficient state.  The cells R - 1 cells from a face
+    get one set of arrivals (normal speed R) and nothing from the stream: their
+    mass and momentum sums, rounded to FP32 once, then the FP32 scaling to
+    the coefficients j / theta, to the last FP32 bit."""
+    sigma = SIGMA if wall == "maxwell" else 1.0
+    v, w, th = P.lattice(Q)
+    v = np.asarray(v)
+    R = int(v.max())
+    nx, ny, box = (70, 12, (0, 0, 0, 0)) if geom == W.PLATE else (80, 50, (30, 20, 12, 9))
+    x0, y0, lx, ly = box
+    x1, y1 = x0 + lx, y0 + ly
+    f32 = np.float32
+    ith = f32(1.0 / th)
+    checked = 0
+    for k in range(24):
+        s = W.Solve(Q=Q, geometry=geom, far=W.FAR_WALL if geom == W.PLATE else W.FAR_EQ, nx=nx,
+                    ny=ny, tau=1.3, omega=math.pi, u0=1e-3 * 1.37 ** k / 10, box=box, nsteps=1,
+                    window_first=0, window_count=0, storage="f32dev", wall=wall,
+                    accommodation=sigma)
+        with P.Solver(P.params_from_solve(s, representation=2)) as sv:
+            sv.step(1)
+            dev = sv.get_deviations()
+        U = s.u0 * math.sin(s.omega * 0.5)
+        ladd = 2 * s.rho0 / th * U
+        # coefficients (by)(bx) back from the populations of speed 1
+        def coef(axis):
+            a = [q for q, p in enumerate(v.tolist()) if p == ([1, 0] if axis == 0 else [0, 1])][0]
+            b = [q for q, p in enumerate(v.tolist()) if p == ([-1, 0] if axis == 0 else [0, -1])][0]
+            return ((dev[a] - dev[b]) / (2 * w[a])).astype(f32)
+        bx, by = coef(0), coef(1)
+        if geom == W.PLATE:
+            cells = [(0, x, R - 1, False, 1, R, R) for x in (0, 1, 33, nx - 1)]
+        else:
+            cells = [(0, x, y0 - R, False, -1, min(R, x1 - x - 1), min(R, x - x0))
+                     for x in range(x0 + R, x1 - R)]
+            cells += [(1, x, y1 + R - 1, False, 1, min(R, x1 - x - 1), min(R, x - x0))
+                      for x in range(x0 + R, x1 - R)]
+            cells += [(2, x0 - R, y, True, -1, min(R, y1 - y - 1), min(R, y - y0))
+                      for y in range(y0 + R, y1 - R)]
+            cells += [(3, x1 + R - 1, y, True, 1, min(R, y1 - y - 1), min(R, y - y0))
+                      for y in range(y0 + R, y1 - R)]
+        for face, x, y, ax, sg, lo, hi in cells:
+            # the column's constants over all its links
+            Mr = Z1 = Z2 = L1 = 0.0
+            for n in range(1, R + 1):
+                for wq, vx, vy in _face_sums(v, w, n, sg, ax, lo, hi):
+                    Mr += n * wq
+                    if geom == W.BOX:
+                        Z1 += n * wq * vx / th
+                        L1 += n * 2 * wq * vx / th
+                    Z2 += n * wq * (vx * vx / (2 * th * th) - 1 / (2 * th))
+            jn = jt = m0 = size = 0.0
+            for wq, vx, vy in _face_sums(v, w, R, sg, ax, lo, hi):
+                arr = sigma * _emission(U, s.rho0, 0.0, wq, vx, th, Mr, Z1, Z2, L1)
+                if ax:
+                    arr += (1 - sigma) * wq * vx * ladd
+                m0 += arr
+                size += abs(arr)
+                jt += arr * (vy if ax else vx)
+            jn = f32(sg * R) * f32(m0)
+            want_n, want_t = f32(jn * ith), f32(f32(jt) * ith)
+            got_n, got_t = (bx[y, x], by[y, x]) if ax else (by[y, x], bx[y, x])
+            # (a sum that cancels is the rounding error of its FP64 terms)
+            eps = 16 * np.spacing(size) * R / th
+            assert abs(float(got_n) - float(want_n)) <= eps, (k, face, x, y, got_n, want_n)
+            assert abs(float(got_t) - float(want_t)) <= eps, (k, face, x, y, got_t, want_t)
+            checked += 1
+    assert checked >= 24 * 4
