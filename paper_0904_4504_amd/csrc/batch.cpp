@@ -105,7 +105,7 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   if (!b->dirty && act == b->active) return LBM_OK;
   drop_graph(b);
   b->active = act;
-  b->dirty = false;
+  b->dirty = true;  // until the device has the whole set
   std::vector<SolveDesc> descs;
   // first every member's force item and (coefficient groups) its wall tiles,
   // the slowest tiles of the launch, then the rest
@@ -166,7 +166,10 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
     b->streaming[k] = state[k] > (k < kTiles ? kCachedPopBytes : kCachedStateBytes);
     work.insert(work.end(), group[k].begin(), group[k].end());
   }
-  if (act.empty()) return LBM_OK;
+  if (act.empty()) {
+    b->dirty = false;
+    return LBM_OK;
+  }
   if (b->ncolumn && b->ncolumn < (int)act.size()) (void)side_stream(b);
   if (hipStreamSynchronize(b->stream) != hipSuccess) return LBM_EHIP;
   int rc;
@@ -180,6 +183,7 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
       hipMemcpy(b->d_solves, solves.data(), sizeof(int32_t) * solves.size(),
                 hipMemcpyHostToDevice) != hipSuccess)
     return LBM_EHIP;
+  b->dirty = false;
   return LBM_OK;
 }
 

@@ -1,0 +1,193 @@
+// The library's host side (api.cpp, batch.cpp, lattice.cpp) on a HIP runtime of
+// plain host memory whose launches only record which steps they would do: see
+// test_host_bookkeeping_cpu.py.  A launch, an allocation or a copy can be made
+// to fail.  argv[1]: the check to run.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <set>
+#include <string>
+#include <vector>
+
+#include "internal.hpp"
+
+using namespace lbm;
+
+#define CHECK(c)                                              \
+  do {                                                        \
+    if (!(c)) {                                               \
+      std::printf("line %d: %s\n", __LINE__, #c);             \
+      std::exit(1);                                           \
+    }                                                         \
+  } while (0)
+
+// ------------------------------------------------------------ the runtime
+static int g_fail_launch = -1, g_fail_malloc = -1;  // calls until one fails
+static std::vector<std::string> g_log;              // launches and events, in order
+static int g_coef_k = 0;                            // K of the last coefficient launch
+
+static bool fails(int& counter) { return counter >= 0 && counter-- == 0; }
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  if (fails(g_fail_malloc)) return hipErrorOutOfMemory;
+  *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
+  return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
+  std::memset(d, v, n);
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t*) { return hipErrorNotSupported; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+  return hipErrorNotSupported;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  *s = reinterpret_cast<hipStream_t>(new int);
+  return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t s) { delete reinterpret_cast<int*>(s); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(new int); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<int*>(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { g_log.push_back("record"); return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) {
+  g_log.push_back("wait");
+  return hipSuccess;
+}
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1; return hipSuccess; }
+}
+
+// ------------------------------------------------------------- the kernels
+// steps that a solve has done, by its state block; each must come once, in order
+static std::map<const SolveState*, int64_t> g_done;
+
+static hipError_t run(const char* name, const SolveDesc* descs, const WorkItem* work, int nwork,
+                      int dn, int nsub) {
+  g_log.push_back(name);
+  if (fails(g_fail_launch)) return hipErrorLaunchFailure;
+  std::set<int> solves;
+  for (int i = 0; i < nwork; ++i)
+    if (!work || work[i].tile != kNoTile) solves.insert(work ? work[i].solve : 0);
+  for (int i : solves) {
+    const SolveState* st = descs[i].state;
+    CHECK(st->step + dn == g_done[st]);
+    g_done[st] += nsub;
+  }
+  return hipSuccess;
+}
+
+namespace lbm {
+hipError_t launch_step(int, bool, bool, bool, int, bool, const SolveDesc* descs,
+                       const WorkItem* work, int nwork, const KernelLattice&, int dn, bool,
+                       hipStream_t, KernelEvents) {
+  return run("step", descs, work, nwork, dn, 1);
+}
+hipError_t launch_coef(int, bool, int k, bool, bool, const SolveDesc* descs, const WorkItem* work,
+                       int nwork, const KernelLattice&, int dn, hipStream_t, KernelEvents) {
+  g_coef_k = k;
+  return run("coef", descs, work, nwork, dn, 1);
+}
+hipError_t launch_column(int, bool, bool, bool, const ColumnShape& sh, const SolveDesc* descs,
+                         const WorkItem* work, int nwork, const KernelLattice&, int dn, hipStream_t,
+                         KernelEvents) {
+  return run("column", descs, work, nwork, dn, sh.nsub);
+}
+hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int count, int nsteps,
+                          hipStream_t) {
+  if (count <= 0 || nsteps <= 0) return hipSuccess;
+  g_log.push_back("advance");
+  for (int i = 0; i < count; ++i) descs[solves[i]].state->step += nsteps;
+  return hipSuccess;
+}
+int read_out(const SolveDesc*, int, hipStream_t, int64_t, int, int32_t*, double*, double*) {
+  return LBM_ENOMEM;
+}
+void release_scratch(int) {}
+}  // namespace lbm
+
+// -------------------------------------------------------------- the checks
+static lbm_params params(int geom, int nx, int ny, int wall, int64_t steps) {
+  lbm_params p;
+  CHECK(lbm_params_init(&p) == LBM_OK);
+  p.lattice = 37;
+  p.storage = LBM_STORE_F32_DEV;
+  p.collision = LBM_COLL_REGULARIZED;
+  p.geometry = geom;
+  p.far = geom == LBM_GEOM_BOX ? LBM_FAR_EQ : LBM_FAR_WALL;
+  p.wall = wall;
+  p.accommodation = 1.0;
+  p.nx = nx;
+  p.ny = ny;
+  if (geom == LBM_GEOM_BOX) {
+    p.box_x0 = nx / 2;
+    p.box_y0 = ny / 2;
+    p.box_lx = p.box_ly = 5;
+  }
+  p.tau = 0.9;
+  p.omega = 0.1;
+  p.u0 = 1e-3;
+  p.rho0 = 1;
+  p.max_steps = steps;
+  return p;
+}
+
+static lbm_solver* solver(const lbm_params& p) {
+  lbm_solver* s = nullptr;
+  CHECK(lbm_create(&p, nullptr, &s) == LBM_OK);
+  return s;
+}
+
+// members of every kind of launch
+static std::vector<lbm_solver*> members(int64_t steps) {
+  return {solver(params(LBM_GEOM_PLATE, 4, 100, LBM_WALL_BB, steps)),
+          solver(params(LBM_GEOM_BOX, 80, 70, LBM_WALL_BB, steps)),
+          solver(params(LBM_GEOM_PLATE, 5, 60, LBM_WALL_DS, steps)),
+          solver(params(LBM_GEOM_BOX, 40, 40, LBM_WALL_DS, steps)),
+          solver(params(LBM_GEOM_PLATE, 70, 30, LBM_WALL_DS, steps)),
+          solver(params(LBM_GEOM_BOX, 40, 44, LBM_WALL_BB, steps))};
+}
+
+// A launch set that could not be built is built by the next call.
+static void check_refresh() {
+  for (int n = 0; n < 3; ++n) {
+    auto ms = members(50);
+    lbm_batch* b = nullptr;
+    CHECK(lbm_batch_create(nullptr, &b) == LBM_OK);
+    for (lbm_solver* s : ms) CHECK(lbm_batch_add(b, s) == LBM_OK);
+    g_fail_malloc = n;
+    CHECK(lbm_batch_step(b, 3) == LBM_ENOMEM);
+    g_fail_malloc = -1;
+    CHECK(lbm_batch_step(b, 3) == LBM_OK);
+    for (lbm_solver* s : ms) CHECK(s->steps == 3 && g_done[s->desc.state] == 3);
+    lbm_batch_destroy(b);
+    for (lbm_solver* s : ms) lbm_destroy(s);
+    g_done.clear();
+  }
+}
+
+int main(int argc, char** argv) {
+  const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh}};
+  CHECK(argc == 2 && checks.count(argv[1]));
+  checks.at(argv[1])();
+  std::printf("ok\n");
+  return 0;
+}
