@@ -990,7 +990,7 @@ int launch_one_step(lbm_solver* s, int dn) {
   } else if (s->pop_pending) {
     e = launch_step(Q, f64, false, ds, 1, true, s->d_desc, s->d_work, s->lay.nwork, s->klat, dn,
                     false, s->stream);
-    s->pop_pending = false;
+    if (e == hipSuccess) s->pop_pending = false;
   } else {
     e = launch_coef(Q, f64, s->lay.launch_k, ds, 2 * s->lay.mbuf_bytes > kCachedStateBytes,
                     s->d_desc, s->d_mwork, s->lay.mnwork, s->klat, dn, s->stream);
@@ -998,28 +998,32 @@ int launch_one_step(lbm_solver* s, int dn) {
   return e == hipSuccess ? LBM_OK : LBM_EHIP;
 }
 
-// Enqueue the launches of n steps (no host bookkeeping).
-int launch_steps(lbm_solver* s, int64_t n) {
+// Enqueue the launches of n steps; *done: how many were (less than n after a
+// failure), the device's counter advanced by as many.
+int launch_steps(lbm_solver* s, int64_t n, int64_t* done) {
   const bool f64 = s->p.storage == LBM_STORE_F64;
   const int Q = (int)s->p.lattice, rows = s->column.rows;
-  while (n > 0) {
+  *done = 0;
+  while (*done < n) {
     // one advance of the step counter for all the launches of a block
-    const int block = (int)std::min<int64_t>(n, kStepBlock);
-    for (int k = 0; !s->lay.column && k < block; ++k) {
-      const int rc = launch_one_step(s, k);
-      if (rc) return rc;
-    }
-    int dn = 0;
-    for (int nsub : odd_pieces(s->lay.column ? block : 0, s->column.max_sub)) {
-      if (launch_column(Q, f64, s->p.collision == LBM_COLL_BGK, s->p.wall != LBM_WALL_BB,
-                        column_shape(Q, s->p.nx, rows, nsub), s->d_desc, nullptr,
-                        (s->p.ny + rows - 1) / rows, s->klat, dn, s->stream) != hipSuccess)
-        return LBM_EHIP;
-      dn += nsub;
-    }
-    if (launch_advance(s->d_desc, s->d_solves, 1, block, s->stream) != hipSuccess)
-      return LBM_EHIP;
-    n -= block;
+    const int block = (int)std::min<int64_t>(n - *done, kStepBlock);
+    int rc = LBM_OK, k = 0;
+    if (!s->lay.column)
+      for (; k < block && !(rc = launch_one_step(s, k)); ++k) {
+      }
+    else
+      for (int nsub : odd_pieces(block, s->column.max_sub)) {
+        if (launch_column(Q, f64, s->p.collision == LBM_COLL_BGK, s->p.wall != LBM_WALL_BB,
+                          column_shape(Q, s->p.nx, rows, nsub), s->d_desc, nullptr,
+                          (s->p.ny + rows - 1) / rows, s->klat, k, s->stream) != hipSuccess) {
+          rc = LBM_EHIP;
+          break;
+        }
+        k += nsub;
+      }
+    if (launch_advance(s->d_desc, s->d_solves, 1, k, s->stream) != hipSuccess) return LBM_EHIP;
+    *done += k;
+    if (rc) return rc;
   }
   return LBM_OK;
 }
@@ -1033,7 +1037,8 @@ bool capture_steps(lbm_solver* s) {
     (void)hipGetLastError();
     return false;
   }
-  const bool ok = launch_steps(s, kGraphSteps) == LBM_OK;
+  int64_t done;
+  const bool ok = launch_steps(s, kGraphSteps, &done) == LBM_OK;
   if (hipStreamEndCapture(s->stream, &g) != hipSuccess || !ok) {
     (void)hipGetLastError();
     if (g) (void)hipGraphDestroy(g);
@@ -1053,10 +1058,10 @@ bool capture_steps(lbm_solver* s) {
 }  // namespace
 
 int step_one(lbm_solver* s) {
-  const int rc = launch_steps(s, 1);
-  if (rc) return rc;
-  ++s->steps;
-  return LBM_OK;
+  int64_t done;
+  const int rc = launch_steps(s, 1, &done);
+  s->steps += done;
+  return rc;
 }
 
 namespace {
@@ -1214,9 +1219,10 @@ int lbm_step(lbm_solver* s, int64_t nsteps) {
     s->steps += kGraphSteps;
   }
   if (k < nsteps) {
-    const int rc = launch_steps(s, nsteps - k);
-    if (rc) return rc;
-    s->steps += nsteps - k;
+    int64_t done;
+    const int rc = launch_steps(s, nsteps - k, &done);
+    s->steps += done;
+    return rc;
   }
   return LBM_OK;
 }

@@ -36,9 +36,10 @@ struct lbm_batch {
   // (bounce-back wall, diffuse wall), coefficient kernel, column
   // kernel (the same); every member runs the kernel it runs alone
   int ngroup[kGroups] = {};
+  int first[kGroups + 1] = {};  // the groups' ranges in the solve list
   ColumnPlan column;      // of the column-kernel members
   int column_nx = 0;      // their widest lattice
-  int ncolumn = 0;        // how many (the last of the launch set's solve list)
+  int ncolumn = 0;        // how many
   // where other members step too, the column launches go on a stream of their
   // own between these events on the batch's stream
   hipStream_t side = nullptr;
@@ -100,6 +101,12 @@ bool side_stream(lbm_batch* b) {
   return b->join != nullptr;
 }
 
+// The kind of launch that steps a member.
+int kind(const lbm_solver* s) {
+  const Layout& lay = s->lay;
+  return (lay.mom ? kTiles : lay.column ? kColumns : kPop) + (s->p.wall != LBM_WALL_BB);
+}
+
 // Rebuild the device launch set from the given members.
 int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   if (!b->dirty && act == b->active) return LBM_OK;
@@ -110,7 +117,7 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   // first every member's force item and (coefficient groups) its wall tiles,
   // the slowest tiles of the launch, then the rest
   std::vector<WorkItem> group[kGroups], front[kGroups], work;
-  std::vector<int32_t> solves, columns;
+  std::vector<int32_t> solves;
   std::vector<int> column_ny;
   b->column_nx = 0;
   for (lbm_solver* s : act)
@@ -121,10 +128,6 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   if (b->column_nx)
     b->column = column_plan(b->Q, b->storage == LBM_STORE_F64, b->column_nx, column_ny);
   uint64_t state[kGroups] = {};  // state bytes per group
-  auto kind = [](const lbm_solver* s) {
-    const Layout& lay = s->lay;
-    return (lay.mom ? kTiles : lay.column ? kColumns : kPop) + (s->p.wall != LBM_WALL_BB);
-  };
   uint32_t tile = UINT32_MAX;
   int64_t coef_cells = 0;
   for (const lbm_solver* s : act)
@@ -139,7 +142,6 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   for (size_t i = 0; i < act.size(); ++i) {
     descs.push_back(act[i]->desc);
     const Layout& lay = act[i]->lay;
-    (lay.column ? columns : solves).push_back((int32_t)i);
     const int k = kind(act[i]);
     if (!lay.column) front[k].push_back(WorkItem{(int32_t)i, kForceTile});
     if (lay.column) {
@@ -155,9 +157,11 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
                   (lay.mw + lay.cells_per_tile - 1) / lay.cells_per_tile);
     }
   }
-  b->ncolumn = (int)columns.size();
-  solves.insert(solves.end(), columns.begin(), columns.end());
+  b->ncolumn = (int)column_ny.size();
   for (int k = 0; k < kGroups; ++k) {
+    for (size_t i = 0; i < act.size(); ++i)
+      if (kind(act[i]) == k) solves.push_back((int32_t)i);
+    b->first[k + 1] = (int)solves.size();
     if (!front[k].empty()) {
       join_front(&front[k], group[k]);
       group[k].swap(front[k]);
@@ -210,48 +214,73 @@ int collect_timing(lbm_batch* b) {
   return LBM_OK;
 }
 
-// The launches of column-kernel members, nsub steps each, dn steps after the
-// last advance of their counters.
-hipError_t launch_columns(lbm_batch* b, int nsub, int dn, hipStream_t stream, KernelEvents ev) {
+// Steps of each kind of member enqueued since its counters were advanced, and in
+// all (counters advanced).
+struct Enqueued {
+  int since[kGroups] = {};
+  int64_t done[kGroups] = {};
+};
+
+// Advance the counters of the kinds [k0, k1) by the steps enqueued for each (the
+// same for all of them unless a launch failed).
+int advance(lbm_batch* b, int k0, int k1, Enqueued* q, hipStream_t stream) {
+  int rc = LBM_OK;
+  for (int k = k0, e; k < k1; k = e) {
+    for (e = k + 1; e < k1 && q->since[e] == q->since[k]; ++e) {
+    }
+    if (launch_advance(b->d_descs, b->d_solves + b->first[k], b->first[e] - b->first[k],
+                       q->since[k], stream) != hipSuccess)
+      rc = LBM_EHIP;
+    else
+      for (int i = k; i < e; ++i) q->done[i] += q->since[i];
+    for (int i = k; i < e; ++i) q->since[i] = 0;
+  }
+  return rc;
+}
+
+// The launches of column-kernel members, nsub steps each.
+hipError_t launch_columns(lbm_batch* b, int nsub, Enqueued* q, hipStream_t stream,
+                          KernelEvents ev) {
   const bool f64 = b->storage == LBM_STORE_F64;
   const WorkItem* work = b->d_work;
   for (int k = 0; k < kColumns; ++k) work += b->ngroup[k];
   for (int k = kColumns; k < kGroups; ++k) {
     const int n = b->ngroup[k];
-    if (n == 0) continue;
     const hipError_t e =
-        launch_column(b->Q, f64, b->collision == LBM_COLL_BGK, k & 1,
-                      column_shape(b->Q, b->column_nx, b->column.rows, nsub), b->d_descs,
-                      work, n, b->active[0]->klat, dn, stream, ev);
+        n == 0 ? hipSuccess
+               : launch_column(b->Q, f64, b->collision == LBM_COLL_BGK, k & 1,
+                               column_shape(b->Q, b->column_nx, b->column.rows, nsub), b->d_descs,
+                               work, n, b->active[0]->klat, q->since[k], stream, ev);
     if (e != hipSuccess) return e;
+    q->since[k] += nsub;
     work += n;
   }
   return hipSuccess;
 }
 
-// The population- and coefficient-kernel launches of one step, dn steps after
-// the last advance of the members' counters.
-hipError_t launch_tiles(lbm_batch* b, int dn, KernelEvents ev) {
+// The population- and coefficient-kernel launches of one step.
+hipError_t launch_tiles(lbm_batch* b, Enqueued* q, KernelEvents ev) {
   const bool f64 = b->storage == LBM_STORE_F64, bgk = b->collision == LBM_COLL_BGK;
   const KernelLattice& lat = b->active[0]->klat;
   const WorkItem* work = b->d_work;
   for (int k = 0; k < kColumns; ++k) {
-    const int n = b->ngroup[k];
-    if (n == 0) continue;
+    const int n = b->ngroup[k], dn = q->since[k];
     const bool ds = k & 1;
     const hipError_t e =
-        k < kTiles ? launch_step(b->Q, f64, bgk, ds, b->cpt, false, b->d_descs, work, n, lat, dn,
-                                 b->streaming[k], b->stream, ev)
-                   : launch_coef(b->Q, f64, b->launch_k, ds, b->streaming[k], b->d_descs, work, n,
-                                 lat, dn, b->stream, ev);
+        n == 0       ? hipSuccess
+        : k < kTiles ? launch_step(b->Q, f64, bgk, ds, b->cpt, false, b->d_descs, work, n, lat, dn,
+                                   b->streaming[k], b->stream, ev)
+                     : launch_coef(b->Q, f64, b->launch_k, ds, b->streaming[k], b->d_descs, work, n,
+                                   lat, dn, b->stream, ev);
     if (e != hipSuccess) return e;
+    ++q->since[k];
     work += n;
   }
   return hipSuccess;
 }
 
 // One step of every member, its step-kernel launches timed.
-int launch_timed(lbm_batch* b) {
+int launch_timed(lbm_batch* b, Enqueued* q) {
   int nlaunch = 0;
   for (int k = 0; k < kGroups; ++k) nlaunch += b->ngroup[k] > 0;
   if (b->ev_used + 2 > 4096) {
@@ -263,27 +292,24 @@ int launch_timed(lbm_batch* b) {
   // a single launch records its own start and end; several: events around them
   const KernelEvents own = nlaunch == 1 ? KernelEvents{e0, e1} : KernelEvents{};
   if (nlaunch > 1 && hipEventRecord(e0, b->stream) != hipSuccess) return LBM_EHIP;
-  if (launch_columns(b, 1, 0, b->stream, own) != hipSuccess || launch_tiles(b, 0, own) != hipSuccess)
-    return LBM_EHIP;
-  if (nlaunch > 1 && hipEventRecord(e1, b->stream) != hipSuccess) return LBM_EHIP;
-  return launch_advance(b->d_descs, b->d_solves, (int)b->active.size(), 1, b->stream) ==
-                 hipSuccess
-             ? LBM_OK
-             : LBM_EHIP;
+  int rc = LBM_OK;
+  if (launch_columns(b, 1, q, b->stream, own) != hipSuccess ||
+      launch_tiles(b, q, own) != hipSuccess)
+    rc = LBM_EHIP;
+  if (nlaunch > 1 && hipEventRecord(e1, b->stream) != hipSuccess) rc = LBM_EHIP;
+  if (advance(b, 0, kGroups, q, b->stream)) rc = LBM_EHIP;
+  return rc;
 }
 
 // n steps of the column-kernel members, several per launch.
-int launch_column_steps(lbm_batch* b, int64_t n, hipStream_t stream) {
-  const int nfin = (int)b->active.size() - b->ncolumn;
+int launch_column_steps(lbm_batch* b, int64_t n, Enqueued* q, hipStream_t stream) {
   for (int64_t left = b->ncolumn ? n : 0; left > 0;) {
     const int block = (int)std::min<int64_t>(left, kStepBlock);
-    int dn = 0;
-    for (int nsub : odd_pieces(block, b->column.max_sub)) {
-      if (launch_columns(b, nsub, dn, stream, KernelEvents{}) != hipSuccess) return LBM_EHIP;
-      dn += nsub;
-    }
-    if (launch_advance(b->d_descs, b->d_solves + nfin, b->ncolumn, block, stream) != hipSuccess)
-      return LBM_EHIP;
+    int rc = LBM_OK;
+    for (int nsub : odd_pieces(block, b->column.max_sub))
+      if (!rc && launch_columns(b, nsub, q, stream, KernelEvents{}) != hipSuccess) rc = LBM_EHIP;
+    if (advance(b, kColumns, kGroups, q, stream)) rc = LBM_EHIP;
+    if (rc) return rc;
     left -= block;
   }
   return LBM_OK;
@@ -302,14 +328,14 @@ struct Joined {
 };
 
 // n steps of the other members, step by step.
-int launch_tile_steps(lbm_batch* b, int64_t n) {
-  const int count = (int)b->active.size() - b->ncolumn;
-  for (int64_t left = count ? n : 0; left > 0;) {
+int launch_tile_steps(lbm_batch* b, int64_t n, Enqueued* q) {
+  for (int64_t left = (int)b->active.size() > b->ncolumn ? n : 0; left > 0;) {
     const int block = (int)std::min<int64_t>(left, kStepBlock);
-    for (int k = 0; k < block; ++k)
-      if (launch_tiles(b, k, KernelEvents{}) != hipSuccess) return LBM_EHIP;
-    if (launch_advance(b->d_descs, b->d_solves, count, block, b->stream) != hipSuccess)
-      return LBM_EHIP;
+    int rc = LBM_OK;
+    for (int k = 0; k < block && !rc; ++k)
+      if (launch_tiles(b, q, KernelEvents{}) != hipSuccess) rc = LBM_EHIP;
+    if (advance(b, 0, kColumns, q, b->stream)) rc = LBM_EHIP;
+    if (rc) return rc;
     left -= block;
   }
   return LBM_OK;
@@ -323,7 +349,8 @@ bool capture(lbm_batch* b) {
     (void)hipGetLastError();
     return false;
   }
-  const bool ok = launch_tile_steps(b, b->graph_chunk) == LBM_OK;
+  Enqueued q;
+  const bool ok = launch_tile_steps(b, b->graph_chunk, &q) == LBM_OK;
   if (hipStreamEndCapture(b->stream, &g) != hipSuccess || !ok) {
     (void)hipGetLastError();
     if (g) (void)hipGraphDestroy(g);
@@ -339,6 +366,41 @@ bool capture(lbm_batch* b) {
   b->graph = ex;
   b->graph_steps = b->graph_chunk;
   return true;
+}
+
+// chunk steps of the launch set.
+int step_chunk(lbm_batch* b, int64_t chunk, Enqueued* q) {
+  int rc = LBM_OK;
+  if (b->timing) {
+    for (int64_t k = 0; k < chunk && !rc; ++k) rc = launch_timed(b, q);
+    return rc;
+  }
+  // members do not interact: the column-kernel ones take the whole chunk,
+  // several steps per launch, the others step by step, in graphs where the
+  // chunk allows.  Both at once, on two streams: the column launches are
+  // chains of a few hundred workgroups that leave most of the GPU idle (two
+  // 1024 x 1024 boxes with eight plates: 28.9 us per step, one after the
+  // other 35.1)
+  const bool tiles = (int)b->active.size() > b->ncolumn;
+  const bool beside = tiles && b->ncolumn && b->join;
+  if (beside && (hipEventRecord(b->fork, b->stream) != hipSuccess ||
+                 hipStreamWaitEvent(b->side, b->fork, 0) != hipSuccess))
+    return LBM_EHIP;
+  rc = launch_column_steps(b, chunk, q, beside ? b->side : b->stream);
+  // (also after a failed launch: nothing is left running beside the stream)
+  if (beside && hipEventRecord(b->join, b->side) != hipSuccess) rc = LBM_EHIP;
+  Joined joined{beside ? b : nullptr};
+  if (rc) return rc;
+  int64_t k = 0;
+  if (tiles && b->graphs_enabled && chunk >= b->graph_chunk) {
+    if (!b->graph && !capture(b)) b->graphs_enabled = false;
+    for (; b->graph && k + b->graph_steps <= chunk; k += b->graph_steps) {
+      if (hipGraphLaunch(b->graph, b->stream) != hipSuccess) return LBM_EHIP;
+      for (int i = 0; i < kColumns; ++i) q->done[i] += b->graph_steps;
+    }
+  }
+  if ((rc = launch_tile_steps(b, chunk - k, q))) return rc;
+  return joined.wait();
 }
 
 }  // namespace
@@ -434,39 +496,15 @@ int lbm_batch_step(lbm_batch* b, int64_t nsteps) {
     if (act.empty()) break;
     int rc = refresh(b, act);
     if (rc) return rc;
-    int64_t k = 0;
-    if (b->timing) {
-      for (; k < chunk; ++k)
-        if ((rc = launch_timed(b))) return rc;
-    } else {
-      // members do not interact: the column-kernel ones take the whole chunk,
-      // several steps per launch, the others step by step, in graphs where the
-      // chunk allows.  Both at once, on two streams: the column launches are
-      // chains of a few hundred workgroups that leave most of the GPU idle (two
-      // 1024 x 1024 boxes with eight plates: 28.9 us per step, one after the
-      // other 35.1)
-      const bool beside = (int)act.size() > b->ncolumn && b->ncolumn && b->join;
-      if (beside && (hipEventRecord(b->fork, b->stream) != hipSuccess ||
-                     hipStreamWaitEvent(b->side, b->fork, 0) != hipSuccess))
-        return LBM_EHIP;
-      rc = launch_column_steps(b, chunk, beside ? b->side : b->stream);
-      // (also after a failed launch: nothing is left running beside the stream)
-      if (beside && hipEventRecord(b->join, b->side) != hipSuccess) rc = LBM_EHIP;
-      Joined joined{beside ? b : nullptr};
-      if (rc) return rc;
-      if ((int)act.size() > b->ncolumn && b->graphs_enabled && chunk >= b->graph_chunk) {
-        if (!b->graph && !capture(b)) b->graphs_enabled = false;
-        for (; b->graph && k + b->graph_steps <= chunk; k += b->graph_steps)
-          if (hipGraphLaunch(b->graph, b->stream) != hipSuccess) return LBM_EHIP;
-      }
-      if ((rc = launch_tile_steps(b, chunk - k))) return rc;
-      if ((rc = joined.wait())) return rc;
-    }
+    Enqueued q;
+    rc = step_chunk(b, chunk, &q);
+    // what was launched counts, also when a launch failed
     for (size_t i = 0; i < b->members.size(); ++i)
       if (left[i] > 0) {
-        b->members[i]->steps += chunk;
+        b->members[i]->steps += q.done[kind(b->members[i])];
         left[i] -= chunk;
       }
+    if (rc) return rc;
   }
   return LBM_OK;
 }

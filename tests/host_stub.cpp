@@ -184,8 +184,53 @@ static void check_refresh() {
   }
 }
 
+// The n-th launch fails; the run then goes on to its end.  run() checks that no
+// step is launched twice or left out.
+static void check_launch() {
+  const int64_t steps = 2500;
+  for (int timing = 0; timing < 2; ++timing)
+    for (int n = 0; n < 3000; n += 1 + n / 9) {
+      auto ms = members(steps);
+      lbm_batch* b = nullptr;
+      CHECK(lbm_batch_create(nullptr, &b) == LBM_OK);
+      for (lbm_solver* s : ms) CHECK(lbm_batch_add(b, s) == LBM_OK);
+      CHECK(lbm_batch_timing(b, timing) == LBM_OK);
+      g_fail_launch = n;
+      CHECK(lbm_batch_step(b, steps) == LBM_EHIP);
+      for (lbm_solver* s : ms)
+        CHECK(s->steps == g_done[s->desc.state] && s->desc.state->step == s->steps);
+      CHECK(lbm_batch_step(b, steps) == LBM_OK);
+      for (lbm_solver* s : ms) CHECK(s->steps == steps && g_done[s->desc.state] == steps);
+      lbm_batch_destroy(b);
+      for (lbm_solver* s : ms) lbm_destroy(s);
+      g_done.clear();
+    }
+  for (int n = 0; n < 2000; n += 1 + n / 5)
+    for (lbm_solver* s : members(steps)) {
+      g_fail_launch = n;
+      int rc = lbm_step(s, steps);
+      g_fail_launch = -1;
+      CHECK(s->steps == g_done[s->desc.state] && s->desc.state->step == s->steps);
+      CHECK(rc == (s->steps == steps ? LBM_OK : LBM_EHIP));
+      if (s->steps < steps) CHECK(lbm_step(s, steps - s->steps) == LBM_OK);
+      CHECK(s->steps == steps && g_done[s->desc.state] == steps);
+      g_done.erase(s->desc.state);
+      lbm_destroy(s);
+    }
+  // a loaded state is still the one to step from
+  lbm_solver* s = solver(params(LBM_GEOM_BOX, 80, 70, LBM_WALL_BB, 9));
+  std::vector<double> f((size_t)37 * 80 * 70, 0.0);
+  CHECK(lbm_set_deviations(s, f.data(), f.size()) == LBM_OK);
+  g_fail_launch = 0;
+  g_log.clear();
+  CHECK(lbm_step(s, 2) == LBM_EHIP && lbm_step(s, 2) == LBM_OK);
+  CHECK(g_log[0] == "step" && g_log[1] == "step" && s->steps == 2);
+  lbm_destroy(s);
+}
+
 int main(int argc, char** argv) {
-  const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh}};
+  const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh},
+                                                             {"launch", check_launch}};
   CHECK(argc == 2 && checks.count(argv[1]));
   checks.at(argv[1])();
   std::printf("ok\n");
