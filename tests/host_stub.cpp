@@ -228,9 +228,28 @@ static void check_launch() {
   lbm_destroy(s);
 }
 
+// A tile that a member asks for is the tile of the batch's launch.
+static void check_tile() {
+  for (int order = 0; order < 2; ++order) {
+    lbm_params p = params(LBM_GEOM_BOX, 80, 70, LBM_WALL_BB, 9), q = p;
+    p.tile = order ? 3 : 0;
+    q.tile = order ? 0 : 3;
+    lbm_solver *a = solver(p), *c = solver(q);
+    lbm_batch* b = nullptr;
+    CHECK(lbm_batch_create(nullptr, &b) == LBM_OK);
+    CHECK(lbm_batch_add(b, a) == LBM_OK && lbm_batch_add(b, c) == LBM_OK);
+    CHECK(lbm_batch_step(b, 1) == LBM_OK && g_coef_k == 3);
+    lbm_batch_destroy(b);
+    lbm_destroy(a);
+    lbm_destroy(c);
+    g_done.clear();
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh},
-                                                             {"launch", check_launch}};
+                                                             {"launch", check_launch},
+                                                             {"tile", check_tile}};
   CHECK(argc == 2 && checks.count(argv[1]));
   checks.at(argv[1])();
   std::printf("ok\n");
