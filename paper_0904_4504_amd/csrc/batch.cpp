@@ -17,6 +17,12 @@ using namespace lbm;
 namespace {
 // kinds of launch of a batch (even: bounce-back, odd: diffuse or Maxwell wall)
 constexpr int kPop = 0, kTiles = 2, kColumns = 4, kGroups = 6;
+// Least steps of a call for which column launches go beside the others: the
+// events between two streams and the second advance of the counters cost a
+// call about 25 us of waiting (a 512 x 512 box with four 4 x 2048 plates, us per
+// call, beside / one after the other: 1 step 43 / 19, 2 42 / 35, 3 57 / 41,
+// 4 53 / 57, 8 94 / 97; 1024 x 1024 with eight plates: 3 65 / 66, 4 82 / 89).
+constexpr int kBesideSteps = 4;
 }  // namespace
 
 struct lbm_batch {
@@ -383,6 +389,14 @@ int step_chunk(lbm_batch* b, int64_t chunk, Enqueued* q) {
   // other 35.1)
   const bool tiles = (int)b->active.size() > b->ncolumn;
   const bool beside = tiles && b->ncolumn && b->join;
+  if (beside && chunk < kBesideSteps) {
+    for (int nsub : odd_pieces(chunk, b->column.max_sub))
+      if (!rc && launch_columns(b, nsub, q, b->stream, KernelEvents{}) != hipSuccess)
+        rc = LBM_EHIP;
+    for (int64_t k = 0; k < chunk && !rc; ++k)
+      if (launch_tiles(b, q, KernelEvents{}) != hipSuccess) rc = LBM_EHIP;
+    return advance(b, 0, kGroups, q, b->stream) ? LBM_EHIP : rc;
+  }
   if (beside && (hipEventRecord(b->fork, b->stream) != hipSuccess ||
                  hipStreamWaitEvent(b->side, b->fork, 0) != hipSuccess))
     return LBM_EHIP;

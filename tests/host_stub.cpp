@@ -246,10 +246,27 @@ static void check_tile() {
   }
 }
 
+// Calls of one step: a launch per kind of member and one advance, no events.
+static void check_single() {
+  auto ms = members(9);
+  lbm_batch* b = nullptr;
+  CHECK(lbm_batch_create(nullptr, &b) == LBM_OK);
+  for (lbm_solver* s : ms) CHECK(lbm_batch_add(b, s) == LBM_OK);
+  for (int k = 1; k < 4; ++k) {
+    g_log.clear();
+    CHECK(lbm_batch_step(b, 1) == LBM_OK);
+    CHECK(g_log.size() == 7 && g_log.back() == "advance");
+    for (lbm_solver* s : ms) CHECK(s->steps == k && s->desc.state->step == k);
+  }
+  lbm_batch_destroy(b);
+  for (lbm_solver* s : ms) lbm_destroy(s);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh},
                                                              {"launch", check_launch},
-                                                             {"tile", check_tile}};
+                                                             {"tile", check_tile},
+                                                             {"single", check_single}};
   CHECK(argc == 2 && checks.count(argv[1]));
   checks.at(argv[1])();
   std::printf("ok\n");
