@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblbm.so")
 SOURCES = ["lattice.cpp", "api.cpp", "batch.cpp", "kernels.hip", "coef.hip", "column.hip",
-           "readout.hip", "static_solver.hip"]
+           "readout.hip", "readout_pool.cpp", "static_solver.hip"]
 ARCH = "gfx950"
 
 # Packed FP32 instructions are disabled for all device code.

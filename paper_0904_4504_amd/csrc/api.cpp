@@ -968,6 +968,7 @@ int lbm::create_solver(const lbm_params* p, void* stream, void* dev_buf, uint64_
     delete s;
     return rc;
   }
+  readout_users(1);
   *out = s;
   return LBM_OK;
 }
@@ -1493,6 +1494,7 @@ int lbm_destroy(lbm_solver* s) {
   if (s->graph) (void)hipGraphExecDestroy(s->graph);
   if (s->owned && hipFree(s->base) != hipSuccess) rc = LBM_EHIP;
   if (s->in_scratch) release_scratch(s->device);
+  readout_users(-1);
   delete s;
   return rc;
 }

@@ -40,6 +40,11 @@ struct Readout {
   double lockin[6];
   double force[kReadoutSamples][2];
 };
+// A pinned buffer (null: not to be had), and its return once nothing writes it.
+Readout* take_readout();
+void give_readout(Readout* r);
+// Solvers created (1) and destroyed (-1): idle buffers are freed with the last.
+void readout_users(int change);
 // Wait for the stream and read a solver's flag, lock-in sums and `count` force
 // samples from step `first` (null: not wanted).  LBM_ENOMEM: no pinned memory
 // (nothing was enqueued or waited for).

@@ -6,7 +6,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstring>
-#include <mutex>
 
 #include "internal.hpp"
 
@@ -27,43 +26,12 @@ __global__ __launch_bounds__(kBlock) void readout_kernel(const SolveDesc* __rest
   }
 }
 
-// Pinned buffers not in use: at most kKeep are kept, one per thread that reads
-// at the same time is enough.
-constexpr size_t kKeep = 4;
-std::mutex g_mu;
-Readout* g_free[kKeep];
-size_t g_count = 0;
-
-Readout* take_buffer() {
-  {
-    std::lock_guard<std::mutex> lock(g_mu);
-    if (g_count) return g_free[--g_count];
-  }
-  void* p = nullptr;
-  if (hipHostMalloc(&p, sizeof(Readout), hipHostMallocPortable) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  return static_cast<Readout*>(p);
-}
-
-void give_buffer(Readout* r) {
-  {
-    std::lock_guard<std::mutex> lock(g_mu);
-    if (g_count < kKeep) {
-      g_free[g_count++] = r;
-      return;
-    }
-  }
-  (void)hipHostFree(r);
-}
-
 }  // namespace
 
 int read_out(const SolveDesc* desc, int device, hipStream_t stream, int64_t first, int count,
              int32_t* unstable, double lockin[6], double* force) {
   if (count < 0 || count > kReadoutSamples) return LBM_EINVAL;
-  Readout* r = take_buffer();
+  Readout* r = take_readout();
   if (!r) return LBM_ENOMEM;
   // launched on the solver's device, whichever is current
   int current = device;
@@ -78,7 +46,7 @@ int read_out(const SolveDesc* desc, int device, hipStream_t stream, int64_t firs
     if (unstable) *unstable = r->unstable;
     if (lockin) std::memcpy(lockin, r->lockin, sizeof(r->lockin));
     if (force) std::memcpy(force, r->force, sizeof(double) * 2 * (size_t)count);
-    give_buffer(r);
+    give_readout(r);
     return LBM_OK;
   }
   // the kernel may still be going to write: the buffer is not used again

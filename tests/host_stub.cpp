@@ -26,6 +26,7 @@ using namespace lbm;
 // ------------------------------------------------------------ the runtime
 static int g_fail_launch = -1, g_fail_malloc = -1;  // calls until one fails
 static std::vector<std::string> g_log;              // launches and events, in order
+static int g_pinned = 0;                            // pinned buffers allocated
 static int g_coef_k = 0;                            // K of the last coefficient launch
 
 static bool fails(int& counter) { return counter >= 0 && counter-- == 0; }
@@ -35,6 +36,16 @@ hipError_t hipMalloc(void** p, size_t n) {
   if (fails(g_fail_malloc)) return hipErrorOutOfMemory;
   *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
   return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  ++g_pinned;
+  *p = std::malloc(n);
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+  --g_pinned;
+  std::free(p);
+  return hipSuccess;
 }
 hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
@@ -118,8 +129,11 @@ hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int cou
   for (int i = 0; i < count; ++i) descs[solves[i]].state->step += nsteps;
   return hipSuccess;
 }
-int read_out(const SolveDesc*, int, hipStream_t, int64_t, int, int32_t*, double*, double*) {
-  return LBM_ENOMEM;
+int read_out(const SolveDesc*, int, hipStream_t, int64_t, int, int32_t* unstable, double*, double*) {
+  Readout* r = take_readout();
+  *unstable = 0;
+  give_readout(r);
+  return LBM_OK;
 }
 void release_scratch(int) {}
 }  // namespace lbm
@@ -262,11 +276,31 @@ static void check_single() {
   for (lbm_solver* s : ms) lbm_destroy(s);
 }
 
+// Read-outs share pinned buffers, freed with the last solver.
+static void check_pinned() {
+  for (int round = 0; round < 2; ++round) {
+    auto ms = members(9);
+    for (lbm_solver* s : ms) CHECK(lbm_synchronize(s) == LBM_OK);
+    CHECK(g_pinned == 1);
+    std::vector<Readout*> taken;
+    for (int i = 0; i < 9; ++i) taken.push_back(take_readout());
+    CHECK(g_pinned == 9);
+    for (Readout* r : taken) give_readout(r);
+    CHECK(g_pinned == 4);
+    for (lbm_solver* s : ms) {
+      CHECK(g_pinned == 4);
+      lbm_destroy(s);
+    }
+    CHECK(g_pinned == 0);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh},
                                                              {"launch", check_launch},
                                                              {"tile", check_tile},
-                                                             {"single", check_single}};
+                                                             {"single", check_single},
+                                                             {"pinned", check_pinned}};
   CHECK(argc == 2 && checks.count(argv[1]));
   checks.at(argv[1])();
   std::printf("ok\n");

@@ -19,12 +19,13 @@ def stub(tmp_path_factory):
                     "-I", CSRC, "-I", os.path.join(ROOT, "include"),
                     "-I", os.path.join(rocm, "include"),
                     os.path.join(ROOT, "tests", "host_stub.cpp"),
-                    *(os.path.join(CSRC, f) for f in ("api.cpp", "batch.cpp", "lattice.cpp")),
+                    *(os.path.join(CSRC, f) for f in ("api.cpp", "batch.cpp", "lattice.cpp",
+                                                 "readout_pool.cpp")),
                     "-o", exe], check=True)
     return exe
 
 
-@pytest.mark.parametrize("check", ["refresh", "launch", "tile", "single"])
+@pytest.mark.parametrize("check", ["refresh", "launch", "tile", "single", "pinned"])
 def test_host(stub, check):
     r = subprocess.run([stub, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
