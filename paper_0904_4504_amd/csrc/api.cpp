@@ -455,7 +455,8 @@ void build_wall_tables(const lbm_params* p, const HostLattice& L, const Layout& 
     if (iny && !inx) return x < x0 ? 2 : 3;
     return -1;
   };
-  const long double spec = 1.0L - (p->wall == LBM_WALL_MAXWELL ? (long double)p->accommodation : 1.0L);
+  const long double spec =
+      1.0L - (p->wall == LBM_WALL_MAXWELL ? (long double)p->accommodation : 1.0L);
   long double sx = 0, sy = 0, kx = 0, ky = 0;
   CellTable cells(p, L.R, lay, t);
   // -scale v_l times the population of velocity (ux, uy) and weight w at a cell
@@ -722,8 +723,11 @@ void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay, ForceTa
   lay->off_state = take(sizeof(SolveState));
   // the force's item and padding, then the XCD-aware order, which pads each
   // group of 8 rows to full length
-  lay->nwork = 8 + (int32_t)ordered_length(lay->ntiles, (lay->mw + lay->cells_per_tile - 1) /
-                                                            lay->cells_per_tile);
+  // (none for the column kernel, which needs no list and sums the force itself)
+  lay->nwork = lay->column ? 0
+                           : 8 + (int32_t)ordered_length(
+                                     lay->ntiles, (lay->mw + lay->cells_per_tile - 1) /
+                                                      lay->cells_per_tile);
   lay->off_work = take(sizeof(WorkItem) * (uint64_t)lay->nwork);
   if (lay->mom) {
     int64_t nfront = 1;  // the force's item and the wall tiles
@@ -735,6 +739,12 @@ void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay, ForceTa
   lay->off_solves = take(sizeof(int32_t));
   ForceTables& ft = *tables;
   build_force_tables(p, L, *lay, &ft);
+  if (lay->column) {
+    lay->unused_bytes = (int64_t)(sizeof(ForceLink) * ft.links.size() +
+                                  sizeof(LinkWeights) * ft.lweights.size());
+    ft.links.clear();
+    ft.lweights.clear();
+  }
   lay->nlinks = (int32_t)ft.links.size();
   lay->nfcells = (int32_t)ft.cells.size();
   lay->off_links = take(sizeof(ForceLink) * ft.links.size());
@@ -838,9 +848,12 @@ int init_solver(lbm_solver* s, const ForceTables& ft) {
   for (int k = 0; k < 8; ++k) s->klat.w[k] = s->lat.lw.w_orbit[k];
   s->klat.theta = s->lat.lw.theta;
 
-  std::vector<WorkItem> work{WorkItem{0, kForceTile}}, mwork, rest;
-  order_tiles(&rest, 0, lay.ntiles, (lay.mw + lay.cells_per_tile - 1) / lay.cells_per_tile);
-  join_front(&work, rest);
+  std::vector<WorkItem> work, mwork, rest;
+  if (lay.nwork > 0) {
+    work.push_back(WorkItem{0, kForceTile});
+    order_tiles(&rest, 0, lay.ntiles, (lay.mw + lay.cells_per_tile - 1) / lay.cells_per_tile);
+    join_front(&work, rest);
+  }
   if (lay.mom) {
     const CoefGrid g = coef_grid(p, lay.launch_k);
     mwork.push_back(WorkItem{0, kForceTile});
@@ -866,7 +879,8 @@ int init_solver(lbm_solver* s, const ForceTables& ft) {
   hipStream_t st = s->stream;
   int rc;
   if ((rc = hip_rc(hipMemcpyAsync(s->d_desc, &d, sizeof(d), hipMemcpyHostToDevice, st)))) return rc;
-  if ((rc = hip_rc(hipMemcpyAsync(s->d_work, work.data(), sizeof(WorkItem) * work.size(),
+  if (!work.empty() &&
+      (rc = hip_rc(hipMemcpyAsync(s->d_work, work.data(), sizeof(WorkItem) * work.size(),
                                   hipMemcpyHostToDevice, st))))
     return rc;
   if ((rc = hip_rc(hipMemcpyAsync(s->d_solves, &solve0, sizeof(solve0), hipMemcpyHostToDevice,
@@ -1126,7 +1140,7 @@ int sync_and_check(lbm_solver* s, double lockin[6] = nullptr, int64_t first = 0,
 
 namespace lbm {
 
-int required_bytes(const lbm_params* p, uint64_t* bytes, uint64_t* fine) {
+int required_bytes(const lbm_params* p, uint64_t* bytes, int64_t* beyond) {
   if (!bytes) return LBM_EINVAL;
   HostLattice lat;
   int rc = validate(p, &lat);
@@ -1135,7 +1149,7 @@ int required_bytes(const lbm_params* p, uint64_t* bytes, uint64_t* fine) {
   ForceTables tables;
   make_layout(p, lat, &lay, &tables);
   *bytes = lay.total;
-  if (!fine) return LBM_OK;
+  if (!beyond) return LBM_OK;
   // the same lists over plain cells and with the default K, wall tiles aside
   const int64_t cells = (int64_t)p->nx * p->ny, per = lay.cells_per_tile;
   int64_t items = lay.nwork - ordered_length((cells + per - 1) / per, (p->nx + per - 1) / per);
@@ -1148,8 +1162,8 @@ int required_bytes(const lbm_params* p, uint64_t* bytes, uint64_t* fine) {
           ? (int64_t)sizeof(ForceCell) * lay.nfcells + (int64_t)sizeof(CellWeights) * lay.ncweights
           : 0;
   // (a kAlign for the rounding of each)
-  *fine = (uint64_t)std::max<int64_t>(0, items * (int64_t)sizeof(WorkItem) + force_cells) +
-          4 * kAlign;
+  *beyond = items * (int64_t)sizeof(WorkItem) + force_cells - lay.unused_bytes +
+            4 * (int64_t)kAlign;
   return LBM_OK;
 }
 

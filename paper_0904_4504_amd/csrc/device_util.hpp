@@ -28,12 +28,6 @@ inline void launch_kernel(K k, dim3 grid, dim3 block, hipStream_t stream, const 
     hipLaunchKernelGGL(k, grid, block, 0, stream, args...);
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // Sum over the wavefront in lane 63 (other lanes: partial sums), by shifts
 // within rows of 16 lanes and broadcasts between them: register moves of a few
 // cycles, where a shuffle goes through the LDS unit.

@@ -122,9 +122,10 @@ __device__ __forceinline__ void box_link_force(const SolveDesc& d, int64_t n, Fo
 // update.  As a launch of its own after every step it added 4.5 us (bounce-
 // back) to 10 us (diffuse box) and a dependency between launches to each step:
 // a 256 x 256 FP32 box took 21 us per step instead of 14.6 (both at K = 3), a
-// 641 x 1000 box of populations 58.8 instead of 50.6.  The step counter, which every workgroup reads, is advanced by a
-// launch of its own after the last step of a call or graph (advance_kernel);
-// a launch is told how many steps lie in between.
+// 641 x 1000 box of populations 58.8 instead of 50.6.  The step counter, which
+// every workgroup reads, is advanced by a launch of its own after the last step
+// of a call or graph (advance_kernel); a launch is told how many steps lie in
+// between.
 // coeffs: the input state is H2 coefficients, else populations.
 //
 // Bound by the chain of dependent loads per thread.  The force of a
@@ -220,7 +221,8 @@ __device__ __forceinline__ void wall_force(const SolveDesc& d, bool coeffs, int6
     }
     fx = d.fstatic[0] + d.kladd[0] * dr.u + sx;
     fy = d.fstatic[1] + d.kladd[1] * dr.u + sy;
-    if (d.wall == WALL_DS && d.geom == GEOM_PLATE) add_emission_force(wall_emission(d), dr.u, sm, &fx, &fy);
+    if (d.wall == WALL_DS && d.geom == GEOM_PLATE)
+      add_emission_force(wall_emission(d), dr.u, sm, &fx, &fy);
     const int64_t h = n % d.hist_cap;
     d.hist[2 * h] = fx;
     d.hist[2 * h + 1] = fy;

@@ -73,6 +73,7 @@ struct Layout {
   int32_t nlinks = 0, nfcells = 0, nwcols = 0, nwlinks = 0, nlweights = 0, ncweights = 0;
   uint64_t off_links = 0, off_fcells = 0, off_wcols = 0, off_wlinks = 0;
   uint64_t off_lweights = 0, off_cweights = 0;
+  int64_t unused_bytes = 0;  // force links left out (column kernel)
   // coefficient representation (mom): six coefficient planes, updated in
   // tiles of kCoefTileW columns x coef_tile_rows(K) rows
   bool mom = false;
@@ -178,12 +179,13 @@ struct lbm_solver {
 };
 
 namespace lbm {
+// lbm_required_bytes; beyond (if asked for): how much more (or less) that is
+// than the state, every force table by links and the work lists of the default
+// tiles, which the static scratch limit counts.
+int required_bytes(const lbm_params* p, uint64_t* bytes, int64_t* beyond);
 // Create a solver in caller-owned device memory (dev_buf, bytes) or, with
 // dev_buf null, in memory the library allocates.  graphs: lbm_step may
 // capture and replay HIP graphs (off: every step launches directly).
-// lbm_required_bytes; fine (if asked for): how much of it goes beyond the state,
-// the tables and the work lists of the default tiles, at most.
-int required_bytes(const lbm_params* p, uint64_t* bytes, uint64_t* fine);
 int create_solver(const lbm_params* p, void* stream, void* dev_buf, uint64_t bytes, bool graphs,
                   lbm_solver** out);
 // Mark the static scratch array of `device` free again (lbm_destroy of a

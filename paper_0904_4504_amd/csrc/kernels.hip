@@ -475,8 +475,7 @@ __global__ __launch_bounds__(BS) void step_kernel(const SolveDesc* __restrict__ 
 template <class L, typename S, bool BGK, bool DSW>
 static hipError_t launch_step_t(int cpt, const SolveDesc* descs, const WorkItem* work, int nwork,
                                 const KernelLattice& lat, int dn, bool streaming,
-                                hipStream_t stream,
-                                const KernelEvents& ev) {
+                                hipStream_t stream, const KernelEvents& ev) {
   switch (cpt) {
     case 1:
       launch_kernel(step_kernel<L, S, BGK, DSW, kBlock, false>, dim3(nwork), dim3(kBlock), stream,
@@ -520,8 +519,8 @@ static hipError_t launch_step_l(bool bgk, bool ds, int cpt, bool outm, const Sol
 
 hipError_t launch_step(int Q, bool f64, bool bgk, bool ds, int cpt, bool outm,
                        const SolveDesc* descs, const WorkItem* work, int nwork,
-                       const KernelLattice& lat, int dn, bool streaming,
-                                hipStream_t stream, KernelEvents ev) {
+                       const KernelLattice& lat, int dn, bool streaming, hipStream_t stream,
+                       KernelEvents ev) {
   if (nwork <= 0) return hipSuccess;
   if (Q == 9)
     return f64 ? launch_step_l<D2Q9, double>(bgk, ds, cpt, outm, descs, work, nwork, lat, dn,

@@ -40,10 +40,12 @@ void lbm::release_scratch(int device) {
 extern "C" int lbm_create_static(const lbm_params* p, void* hip_stream, lbm_solver** out) {
   if (!out) return LBM_EINVAL;
   *out = nullptr;
-  uint64_t need = 0, fine = 0;
-  int rc = lbm::required_bytes(p, &need, &fine);
+  uint64_t need = 0;
+  int64_t beyond = 0;
+  int rc = lbm::required_bytes(p, &need, &beyond);
   if (rc) return rc;
-  if (need > kScratchBytes + std::min(fine, kScratchSlack)) return LBM_ESCRATCH;
+  if ((int64_t)need - std::min(beyond, (int64_t)kScratchSlack) > (int64_t)kScratchBytes)
+    return LBM_ESCRATCH;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return LBM_EHIP;
   if (dev < 0 || dev >= kMaxDevices) return LBM_EINVAL;

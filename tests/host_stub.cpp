@@ -295,12 +295,34 @@ static void check_pinned() {
   }
 }
 
+// A lattice stepped by the column kernel carries no force links and no work
+// list, and the static limit counts it as if it did.
+static void check_tables() {
+  for (int ny : {100, 5000}) {
+    lbm_params p = params(LBM_GEOM_PLATE, 4, ny, LBM_WALL_BB, 9);
+    lbm_solver* s = solver(p);
+    CHECK(s->lay.column && s->lay.nwork == 0 && s->desc.nlinks == 0);
+    uint64_t bytes = 0;
+    int64_t beyond = 0;
+    CHECK(required_bytes(&p, &bytes, &beyond) == LBM_OK && bytes == s->lay.total);
+    // 4 columns x 26 crossing populations of 15 velocities, a weight pattern for
+    // each, a work item per 256 cells
+    const int64_t list = ((ny * 4 + 255) / 256 + 7) / 8 * 8;
+    CHECK(beyond == 4 * (int64_t)kAlign - 4 * 26 * (int64_t)sizeof(ForceLink) -
+                        15 * (int64_t)sizeof(LinkWeights) - list * (int64_t)sizeof(WorkItem));
+    CHECK(lbm_step(s, 9) == LBM_OK);
+    g_done.erase(s->desc.state);
+    lbm_destroy(s);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh},
                                                              {"launch", check_launch},
                                                              {"tile", check_tile},
                                                              {"single", check_single},
-                                                             {"pinned", check_pinned}};
+                                                             {"pinned", check_pinned},
+                                                             {"tables", check_tables}};
   CHECK(argc == 2 && checks.count(argv[1]));
   checks.at(argv[1])();
   std::printf("ok\n");
