@@ -196,7 +196,6 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
   const int64_t win0 = d.lockin_first - n0, win1 = win0 + d.lockin_count;
   const bool far_eq = d.far == FAR_EQ, diffuse = DSW && d.wall == WALL_DS;
   const WallEmission emission = wall_emission(d);
-  const bool specular = sigma != 1.0;
   const S rho0 = (S)rho0d;
   const double inv_thd = 1.0 / lat.theta;
   const S th = (S)lat.theta, inv_th = (S)(1.0 / lat.theta);
@@ -248,7 +247,7 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
           if constexpr (L::vy[q] < 0)
             if (y < -L::vy[q]) {
               cm += (double)f[q];
-              if (behind_low >= 0 && specular) pop[own + to_low + to * cap] = f[q];
+              if (behind_low >= 0) pop[own + to_low + to * cap] = f[q];
             }
         });
         cross[y * kColumnMaxNx + x] = cm;
@@ -353,13 +352,14 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
         const double e0 = 0.5 * U * U * inv_thd, e1 = U * inv_thd, e2 = e0 * inv_thd;
         const double eb = (rho0d * ds0 + cm) * emit;
         const double ea = (cm - rho0d * (U * U * ds1)) * emit - eb * e0;
+        // (a share of zero leaves the emission as it is)
+        const double ws = 1.0 - sigma;
         static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
           constexpr int q = decltype(qc)::value;
           constexpr int vx = L::vx[q], vy = L::vy[q];
           if constexpr (vy > 0) {
-            double e = lat.w[L::orbit[q]] * (ea + eb * (vx * (e1 + vx * e2)));
-            if (specular) e += (1.0 - sigma) * (double)f[q];
-            f[q] = y < vy ? (S)e : f[q];
+            const double e = lat.w[L::orbit[q]] * (ea + eb * (vx * (e1 + vx * e2)));
+            f[q] = y < vy ? (S)__builtin_fma(ws, (double)f[q], e) : f[q];
           }
         });
       }
