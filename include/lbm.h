@@ -195,8 +195,13 @@ int lbm_create_in(const lbm_params* p, void* hip_stream, void* dev_buf, uint64_t
  * earlier solver left in the array does not matter.  One such solver per
  * device at a time: while it lives (until lbm_destroy), another
  * lbm_create_static on that device returns LBM_ESCRATCH, as do parameters
- * whose lbm_required_bytes exceeds LBM_STATIC_SCRATCH_BYTES (the work list of
- * a small lattice's finer tiles, a few KiB, not counted).  Launches of two
+ * that need more than LBM_STATIC_SCRATCH_BYTES of it.  Not counted in that,
+ * so that lbm_required_bytes may be up to 256 KiB above the limit: what finer
+ * tiles, rows padded to whole wavefronts and the force's items add to the work
+ * lists, and the force cells of boxes with diffuse or Maxwell faces kept as
+ * coefficients.  Counted although left out (a few KiB, so that it may be
+ * below and still refused): force links and work list of lattices that take
+ * several steps per launch (at most 16 columns).  Launches of two
  * processes' static solvers on one device do not share the array (each
  * process has its own copy); work enqueued on the array by a destroyed solver
  * has completed (lbm_destroy waits). */
@@ -290,12 +295,12 @@ int lbm_destroy(lbm_solver* s);
  * A batch advances many solvers -- uneven lattices with the same lattice,
  * storage and collision, created on the batch's stream -- with one fused
  * launch per step and kind of member that updates all their tiles and reduces
- * their wall forces (narrow plates: one launch per several steps, on a stream
- * of the batch's own beside the other members' launches; later work on `hip_stream`
- * waits for it).  Each member runs the
+ * their wall forces (narrow plates: one launch per several steps, in calls of
+ * at least 4 steps on a stream of the batch's own beside the other members'
+ * launches; later work on `hip_stream` waits for it).  Each member runs the
  * kernel it runs when stepped alone, so its results are bit-identical alone
- * and in any mix.  Members may join and leave between steps
- * (continuous batching); a member stops when it reaches its max_steps.
+ * and in any mix.  Members may join and leave between steps (continuous
+ * batching); a member stops when it reaches its max_steps.
  * Member read-out (force history, impedance, populations) goes through the
  * lbm_solver calls above.  The batch never owns or frees its members. */
 typedef struct lbm_batch lbm_batch;
@@ -307,8 +312,9 @@ int lbm_batch_create(void* hip_stream, lbm_batch** out);
 
 /* Add / remove a member (between steps).  LBM_EINVAL if the solver's stream,
  * lattice, storage or collision differs from the batch, if two members kept
- * in the same representation differ in `tile`, or on a double add / a remove of a
- * non-member.  A member joins at its own current step.  The kinds of member
+ * in the same representation differ in `tile` (0 and the default tile -- 1 for
+ * populations, 3 for coefficients -- go together; the launch takes the tile that
+ * a member asks for), or on a double add / a remove of a non-member.  A member joins at its own current step.  The kinds of member
  * -- kept as populations or as coefficients, with a bounce-back or a diffuse
  * (or Maxwell) moving wall -- are advanced by one launch each per step. */
 int lbm_batch_add(lbm_batch* b, lbm_solver* s);
@@ -330,7 +336,10 @@ int lbm_batch_set_graphs(lbm_batch* b, int steps_per_graph);
 /* Measurement: with timing enabled, every fused step-kernel launch is
  * bracketed by HIP events on the batch's stream (graphs are not used);
  * lbm_batch_kernel_time waits and returns the summed kernel time in ms and
- * the number of launches since timing was (re)enabled. */
+ * the number of launches since timing was (re)enabled: one launch set per
+ * step.  Members of at most 16 columns, which take several steps per launch
+ * otherwise, are then stepped once per launch (an 8-plate batch: 9.9 us per
+ * step timed so, 2.6 without timing), so the figure is an upper bound for them. */
 int lbm_batch_timing(lbm_batch* b, int enable);
 int lbm_batch_kernel_time(lbm_batch* b, double* ms, int64_t* launches);
 

@@ -47,7 +47,12 @@ void order_tiles(std::vector<WorkItem>* out, int32_t solve, int32_t ntiles, int3
 // 848 x 848 16.0, 14.9, 13.7, 1024 x 1024 20.3, 17.7, 17.9, 1400 x 1400 32.5,
 // 26.6, 25.7; FP64 512 x 512 12.5, 12.3, 13.5, 640 x 640 17.4, 17.2, 17.6,
 // 768 x 768 21.8, 20.1, 21.0, 1400 x 1400 54.3, 46.3, 48.6 (K = 3 leaves two
-// workgroups per compute unit by LDS).  A cell's bits do not depend on K.
+// workgroups per compute unit by LDS).  States that stream from HBM: FP32
+// 3000 x 3000 133, 102, 91, 4096 x 4096 254, 180, 158; FP64 1800 x 1800 94, 80, 86,
+// 3000 x 3000 243, 205, 230, 4096 x 4096 439, 362, 398 (the larger halo of K = 2
+// costs less than the third workgroup brings).  The lines are D2Q37's; D2Q9 differs
+// by less than 4 % but for FP32 near 640 x 640 (7.9, 7.1, 7.3).  A cell's bits do
+// not depend on K.
 int coef_k_for(uint32_t tile, bool f64, int64_t cells) {
   if (tile) return (int)tile;
   if (f64) return cells <= 400000 ? 1 : 2;

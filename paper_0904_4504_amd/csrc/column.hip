@@ -10,7 +10,7 @@
 // `nsub` steps there: step s updates the rows that later steps still need, so
 // the halo shrinks by R rows a step and the owned rows are exact.  The halo is
 // work done twice, on compute units that would idle otherwise.  Per step now
-// 0.94, 2.8 and 2.3 us.
+// 0.76, 2.6 and 2.2 us.
 //
 // One thread per cell: it pulls the Q populations of its cell from LDS,
 // collides, and writes them back between two barriers.  The sums and the
