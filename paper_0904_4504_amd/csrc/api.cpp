@@ -175,33 +175,35 @@ ColumnPlan column_plan(int Q, bool f64, int nx, const std::vector<int>& ny) {
     for (int n : ny) g += (n + rows - 1) / rows;
     return g;
   };
+  auto banks = [&](int region) { return bank_load(nx, column_stride(region, nx, es), es); };
   ColumnPlan plan;
   plan.rows = 8;
   const int abreast = Q == 9 ? 512 : 256;
   while (plan.rows < fit && groups(plan.rows) > (f64 ? 256 : abreast)) ++plan.rows;
   plan.max_sub = most;
-  auto banks = [&](int region) { return bank_load(nx, column_stride(region, nx, es), es); };
   while (plan.max_sub > 1) {
     const int region = plan.rows + 2 * R * plan.max_sub;
     if (region <= fit && banks(region) <= 4) return plan;
     plan.max_sub -= 2;
   }
-  double least = INFINITY;
-  for (int t = 1; t <= most; t += 2)
-    for (int rows = 4; rows + 2 * R * t <= fit; ++rows) {
+  double load[kColumnCells + 1], least = INFINITY;  // by region
+  for (int region = 1; region <= fit; ++region) load[region] = banks(region);
+  for (int rows = 4; rows + 2 * R <= fit; ++rows) {
+    double rounds = (double)groups(rows) / abreast;
+    rounds = rounds < 4 ? std::ceil(rounds) : rounds + 0.5;
+    for (int t = 1; t <= most && rows + 2 * R * t <= fit; t += 2) {
       const int region = rows + 2 * R * t;
-      if (banks(region) > 4) continue;
+      if (load[region] > 4) continue;
       const double work = (f64 ? 5.0 : 3.0) * region / t +
-                          (rows + R * (t - 1)) * (0.9 + 0.1 * banks(region)) + 100.0 / nx;
-      const double rounds = (double)groups(rows) / abreast;
-      const double cost = (rounds < 4 ? std::ceil(rounds) : rounds + 0.5) * work +
-                          (Q == 9 ? 1300.0 : 500.0) / (nx * t);
+                          (rows + R * (t - 1)) * (0.9 + 0.1 * load[region]) + 100.0 / nx;
+      const double cost = rounds * work + (Q == 9 ? 1300.0 : 500.0) / (nx * t);
       if (cost < least) {
         least = cost;
         plan.rows = rows;
         plan.max_sub = t;
       }
     }
+  }
   return plan;
 }
 
