@@ -303,6 +303,7 @@ int launch_timed(lbm_batch* b, Enqueued* q) {
       launch_tiles(b, q, own) != hipSuccess)
     rc = LBM_EHIP;
   if (nlaunch > 1 && hipEventRecord(e1, b->stream) != hipSuccess) rc = LBM_EHIP;
+  if (rc) b->ev_used -= 2;  // not both recorded: not a measured step
   if (advance(b, 0, kGroups, q, b->stream)) rc = LBM_EHIP;
   return rc;
 }

@@ -26,6 +26,7 @@ using namespace lbm;
 // ------------------------------------------------------------ the runtime
 static int g_fail_launch = -1, g_fail_malloc = -1;  // calls until one fails
 static std::vector<std::string> g_log;              // launches and events, in order
+static std::set<hipEvent_t> g_recorded;
 static int g_pinned = 0;                            // pinned buffers allocated
 static int g_coef_k = 0;                            // K of the last coefficient launch
 
@@ -79,12 +80,19 @@ hipError_t hipStreamDestroy(hipStream_t s) { delete reinterpret_cast<int*>(s); r
 hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(new int); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<int*>(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { g_log.push_back("record"); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+  g_log.push_back("record");
+  g_recorded.insert(e);
+  return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) {
   g_log.push_back("wait");
   return hipSuccess;
 }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1; return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+  *ms = 1;
+  return g_recorded.count(a) && g_recorded.count(b) ? hipSuccess : hipErrorInvalidHandle;
+}
 }
 
 // ------------------------------------------------------------- the kernels
@@ -92,9 +100,10 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1; ret
 static std::map<const SolveState*, int64_t> g_done;
 
 static hipError_t run(const char* name, const SolveDesc* descs, const WorkItem* work, int nwork,
-                      int dn, int nsub) {
+                      int dn, int nsub, const KernelEvents& ev) {
   g_log.push_back(name);
   if (fails(g_fail_launch)) return hipErrorLaunchFailure;
+  g_recorded.insert({ev.start, ev.stop});
   std::set<int> solves;
   for (int i = 0; i < nwork; ++i)
     if (!work || work[i].tile != kNoTile) solves.insert(work ? work[i].solve : 0);
@@ -109,18 +118,18 @@ static hipError_t run(const char* name, const SolveDesc* descs, const WorkItem* 
 namespace lbm {
 hipError_t launch_step(int, bool, bool, bool, int, bool, const SolveDesc* descs,
                        const WorkItem* work, int nwork, const KernelLattice&, int dn, bool,
-                       hipStream_t, KernelEvents) {
-  return run("step", descs, work, nwork, dn, 1);
+                       hipStream_t, KernelEvents ev) {
+  return run("step", descs, work, nwork, dn, 1, ev);
 }
 hipError_t launch_coef(int, bool, int k, bool, bool, const SolveDesc* descs, const WorkItem* work,
-                       int nwork, const KernelLattice&, int dn, hipStream_t, KernelEvents) {
+                       int nwork, const KernelLattice&, int dn, hipStream_t, KernelEvents ev) {
   g_coef_k = k;
-  return run("coef", descs, work, nwork, dn, 1);
+  return run("coef", descs, work, nwork, dn, 1, ev);
 }
 hipError_t launch_column(int, bool, bool, bool, const ColumnShape& sh, const SolveDesc* descs,
                          const WorkItem* work, int nwork, const KernelLattice&, int dn, hipStream_t,
-                         KernelEvents) {
-  return run("column", descs, work, nwork, dn, sh.nsub);
+                         KernelEvents ev) {
+  return run("column", descs, work, nwork, dn, sh.nsub, ev);
 }
 hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int count, int nsteps,
                           hipStream_t) {
@@ -316,13 +325,37 @@ static void check_tables() {
   }
 }
 
+// A timed step whose launch failed is not part of the kernel time.
+static void check_timing() {
+  for (int several = 0; several < 2; ++several) {
+    auto all = members(9);
+    std::vector<lbm_solver*> ms(all.begin(), all.begin() + (several ? all.size() : 1));
+    lbm_batch* b = nullptr;
+    CHECK(lbm_batch_create(nullptr, &b) == LBM_OK);
+    for (lbm_solver* s : ms) CHECK(lbm_batch_add(b, s) == LBM_OK);
+    CHECK(lbm_batch_timing(b, 1) == LBM_OK);
+    CHECK(lbm_batch_step(b, 2) == LBM_OK);
+    g_fail_launch = 0;
+    CHECK(lbm_batch_step(b, 2) == LBM_EHIP);
+    CHECK(lbm_batch_step(b, 1) == LBM_OK);
+    double ms_ = 0;
+    int64_t n = 0;
+    CHECK(lbm_batch_kernel_time(b, &ms_, &n) == LBM_OK && n == 3 && ms_ == 3);
+    lbm_batch_destroy(b);
+    for (lbm_solver* s : all) lbm_destroy(s);
+    g_done.clear();
+    g_recorded.clear();
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh},
                                                              {"launch", check_launch},
                                                              {"tile", check_tile},
                                                              {"single", check_single},
                                                              {"pinned", check_pinned},
-                                                             {"tables", check_tables}};
+                                                             {"tables", check_tables},
+                                                             {"timing", check_timing}};
   CHECK(argc == 2 && checks.count(argv[1]));
   checks.at(argv[1])();
   std::printf("ok\n");
