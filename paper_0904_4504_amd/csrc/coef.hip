@@ -957,7 +957,7 @@ __device__ __forceinline__ void tile_update(const SolveDesc& d, const TileCtx<S>
   // wall drive of the step (for the links): a new table entry every step, so
   // a cache miss; a vector load issued before the staging loads hides it
   // behind them (a scalar load would share its counter with the LDS reads)
-  int nv = (int)ctx.n;
+  uint32_t nv = drive_index(ctx.n);
   asm volatile("" : "+v"(nv));
   const double U = as_global(d.drive)[nv].u;
   {

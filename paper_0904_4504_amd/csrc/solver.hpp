@@ -68,6 +68,10 @@ struct Drive {
   double c;    // cos(omega t_n)
 };
 
+// A step's entry of the drive table as a vector register's index (a solve has at
+// most 2^32 steps, so unsigned).
+__host__ __device__ constexpr uint32_t drive_index(int64_t n) { return (uint32_t)n; }
+
 // Device-resident counters and accumulators of one solve.
 struct SolveState {
   int64_t step;        // steps completed; selects the input buffer (parity) and drive[step]

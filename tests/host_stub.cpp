@@ -348,6 +348,17 @@ static void check_timing() {
   }
 }
 
+// Every step that a solve may have has its entry of the drive table.
+static void check_steps() {
+  lbm_params p = params(LBM_GEOM_BOX, 80, 70, LBM_WALL_BB, (int64_t)1 << 32);
+  uint64_t bytes = 0;
+  CHECK(lbm_required_bytes(&p, &bytes) == LBM_OK);
+  for (int64_t n : {(int64_t)0, ((int64_t)1 << 31) - 1, (int64_t)1 << 31, p.max_steps - 1})
+    CHECK((int64_t)drive_index(n) == n);
+  ++p.max_steps;
+  CHECK(lbm_required_bytes(&p, &bytes) == LBM_EINVAL);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks{{"refresh", check_refresh},
                                                              {"launch", check_launch},
@@ -355,7 +366,8 @@ int main(int argc, char** argv) {
                                                              {"single", check_single},
                                                              {"pinned", check_pinned},
                                                              {"tables", check_tables},
-                                                             {"timing", check_timing}};
+                                                             {"timing", check_timing},
+                                                             {"steps", check_steps}};
   CHECK(argc == 2 && checks.count(argv[1]));
   checks.at(argv[1])();
   std::printf("ok\n");

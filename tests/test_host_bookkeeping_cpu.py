@@ -26,7 +26,7 @@ def stub(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["refresh", "launch", "tile", "single", "pinned", "tables",
-                                   "timing"])
+                                   "timing", "steps"])
 def test_host(stub, check):
     r = subprocess.run([stub, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
