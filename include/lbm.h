@@ -296,7 +296,7 @@ int lbm_destroy(lbm_solver* s);
  * storage and collision, created on the batch's stream -- with one fused
  * launch per step and kind of member that updates all their tiles and reduces
  * their wall forces (narrow plates: one launch per several steps, in calls of
- * at least 4 steps on a stream of the batch's own beside the other members'
+ * more than a few steps on a stream of the batch's own beside the other members'
  * launches; later work on `hip_stream` waits for it).  Each member runs the
  * kernel it runs when stepped alone, so its results are bit-identical alone
  * and in any mix.  Members may join and leave between steps (continuous
@@ -338,8 +338,9 @@ int lbm_batch_set_graphs(lbm_batch* b, int steps_per_graph);
  * lbm_batch_kernel_time waits and returns the summed kernel time in ms and
  * the number of launches since timing was (re)enabled: one launch set per
  * step.  Members of at most 16 columns, which take several steps per launch
- * otherwise, are then stepped once per launch (an 8-plate batch: 9.9 us per
- * step timed so, 2.6 without timing), so the figure is an upper bound for them. */
+ * otherwise, are then stepped once per launch (five plates of 4 x 2048: 9.9 us
+ * per step timed so, 2.3 without timing), so the figure is an upper bound for
+ * them. */
 int lbm_batch_timing(lbm_batch* b, int enable);
 int lbm_batch_kernel_time(lbm_batch* b, double* ms, int64_t* launches);
 

@@ -183,7 +183,10 @@ ColumnPlan column_plan(int Q, bool f64, int nx, const std::vector<int>& ny) {
   plan.max_sub = most;
   while (plan.max_sub > 1) {
     const int region = plan.rows + 2 * R * plan.max_sub;
-    if (region <= fit && banks(region) <= 4) return plan;
+    if (region <= fit && banks(region) <= 4) {
+      plan.groups = groups(plan.rows);
+      return plan;
+    }
     plan.max_sub -= 2;
   }
   double load[kColumnCells + 1], least = INFINITY;  // by region
@@ -204,7 +207,21 @@ ColumnPlan column_plan(int Q, bool f64, int nx, const std::vector<int>& ny) {
       }
     }
   }
+  plan.groups = groups(plan.rows);
+  // about as much halo as rows: steps one by one (column_single_kernel) are faster
+  // (31 plates of 16 x 2048 FP32 69 us per step against 77, 12 x 16384 alone 14.4 against 12.1)
+  if (Q == 37 && !f64 && nx >= 14 && plan.groups > 1500) plan.max_sub = 1;
   return plan;
+}
+
+// A launch of one step: column_kernel where a few rounds of workgroups do,
+// column_single_kernel above (D2Q37 bounce-back, us per call of one step,
+// column / single: FP32 8 x 8192 (216 workgroups) 9 / 10, 16 x 6000 (600) 17 / 13, six of
+// 16 x 4096 (2460) 61 / 28, 61 of 8 x 2048 (3294) 96 / 77; FP64 4 x 16384 (256) 12 / 19,
+// 61 of 8 x 2048 172 / 134; D2Q9 FP32 8 x 65536 15 / 12).  With a diffuse wall the single
+// kernel's wall cells are a chain of 15 us more (16 x 6000 16 / 24).
+bool column_single(int Q, const ColumnPlan& plan, bool ds) {
+  return plan.max_sub == 1 || plan.groups > (Q == 9 ? 800 : 400) * (ds ? 4 : 1);
 }
 
 std::vector<int> odd_pieces(int64_t n, int max_sub) {
@@ -270,8 +287,8 @@ bool uses_coefficients(const lbm_params* p) {
 // 3 steps per launch and about as much halo as rows, so long ones go to the
 // population kernel (16 columns, us per step, column / population kernel: 4096
 // rows FP32 6.2 / 7.5, FP64 9.6 / 10.9, 8192 rows 11.8 / 9.1, 19.2 / 14.4).  The choice
-// is by the lattice alone, since its bits follow from it: batches of many short
-// ones take longer (31 plates of 16 x 2048 FP32 82 / 65, FP64 124 / 114; alone 4.1 / 6.8).
+// is by the lattice alone, since its bits follow from it; batches of many short ones
+// are column_plan's.
 bool uses_columns(const lbm_params* p) {
   if (uses_coefficients(p) || p->geometry == LBM_GEOM_BOX || p->nx > kColumnMaxNx) return false;
   return p->lattice == 9 || p->nx < 14 || (int64_t)p->nx * p->ny <= kColumnWideCells;
@@ -1035,9 +1052,15 @@ int launch_steps(lbm_solver* s, int64_t n, int64_t* done) {
       }
     else
       for (int nsub : odd_pieces(block, s->column.max_sub)) {
-        if (launch_column(Q, f64, s->p.collision == LBM_COLL_BGK, s->p.wall != LBM_WALL_BB,
-                          column_shape(Q, s->p.nx, rows, nsub), s->d_desc, nullptr,
-                          (s->p.ny + rows - 1) / rows, s->klat, k, s->stream) != hipSuccess) {
+        const bool bgk = s->p.collision == LBM_COLL_BGK, ds = s->p.wall != LBM_WALL_BB;
+        const hipError_t e =
+            nsub == 1 && column_single(Q, s->column, ds)
+                ? launch_column_single(Q, f64, bgk, ds, s->d_desc, nullptr,
+                                       column_single_items(s->p.nx, s->p.ny), s->klat, k,
+                                       2 * s->lay.buf_bytes > kCachedPopBytes, s->stream)
+                : launch_column(Q, f64, bgk, ds, column_shape(Q, s->p.nx, rows, nsub), s->d_desc,
+                                nullptr, (s->p.ny + rows - 1) / rows, s->klat, k, s->stream);
+        if (e != hipSuccess) {
           rc = LBM_EHIP;
           break;
         }

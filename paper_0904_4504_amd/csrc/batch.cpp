@@ -42,6 +42,8 @@ struct lbm_batch {
   // (bounce-back wall, diffuse wall), coefficient kernel, column
   // kernel (the same); every member runs the kernel it runs alone
   int ngroup[kGroups] = {};
+  // items of single-step launches of column-kernel members, behind the groups
+  int nsingle[kGroups] = {};
   int first[kGroups + 1] = {};  // the groups' ranges in the solve list
   ColumnPlan column;      // of the column-kernel members
   int column_nx = 0;      // their widest lattice
@@ -122,7 +124,7 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   std::vector<SolveDesc> descs;
   // first every member's force item and (coefficient groups) its wall tiles,
   // the slowest tiles of the launch, then the rest
-  std::vector<WorkItem> group[kGroups], front[kGroups], work;
+  std::vector<WorkItem> group[kGroups], front[kGroups], single[kGroups], work;
   std::vector<int32_t> solves;
   std::vector<int> column_ny;
   b->column_nx = 0;
@@ -153,6 +155,9 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
     if (lay.column) {
       const int tiles = (act[i]->p.ny + b->column.rows - 1) / b->column.rows;
       for (int t = 0; t < tiles; ++t) group[k].push_back(WorkItem{(int32_t)i, t});
+      const int items = column_single_items(act[i]->p.nx, act[i]->p.ny);
+      front[k].push_back(WorkItem{(int32_t)i, kForceTile});
+      for (int t = 0; t + 1 < items; ++t) single[k].push_back(WorkItem{(int32_t)i, t});
     } else if (lay.mom) {
       const CoefGrid g = coef_grid(&act[i]->p, b->launch_k);
       order_coef_tiles(&front[k], &group[k], (int32_t)i,
@@ -168,14 +173,19 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
     for (size_t i = 0; i < act.size(); ++i)
       if (kind(act[i]) == k) solves.push_back((int32_t)i);
     b->first[k + 1] = (int)solves.size();
-    if (!front[k].empty()) {
+    if (k >= kColumns) {
+      single[k].insert(single[k].begin(), front[k].begin(), front[k].end());
+      b->nsingle[k] = (int)single[k].size();
+    } else if (!front[k].empty()) {
       join_front(&front[k], group[k]);
       group[k].swap(front[k]);
     }
     b->ngroup[k] = (int)group[k].size();
-    b->streaming[k] = state[k] > (k < kTiles ? kCachedPopBytes : kCachedStateBytes);
+    b->streaming[k] = state[k] > (k < kTiles || k >= kColumns ? kCachedPopBytes : kCachedStateBytes);
     work.insert(work.end(), group[k].begin(), group[k].end());
   }
+  for (int k = kColumns; k < kGroups; ++k)
+    work.insert(work.end(), single[k].begin(), single[k].end());
   if (act.empty()) {
     b->dirty = false;
     return LBM_OK;
@@ -247,19 +257,26 @@ int advance(lbm_batch* b, int k0, int k1, Enqueued* q, hipStream_t stream) {
 // The launches of column-kernel members, nsub steps each.
 hipError_t launch_columns(lbm_batch* b, int nsub, Enqueued* q, hipStream_t stream,
                           KernelEvents ev) {
-  const bool f64 = b->storage == LBM_STORE_F64;
-  const WorkItem* work = b->d_work;
-  for (int k = 0; k < kColumns; ++k) work += b->ngroup[k];
+  const bool f64 = b->storage == LBM_STORE_F64, bgk = b->collision == LBM_COLL_BGK;
+  const KernelLattice& lat = b->active[0]->klat;
+  const WorkItem *work = b->d_work, *single = b->d_work;
+  for (int k = 0; k < kGroups; ++k) (k < kColumns ? work : single) += b->ngroup[k];
+  single += work - b->d_work;
   for (int k = kColumns; k < kGroups; ++k) {
-    const int n = b->ngroup[k];
-    const hipError_t e =
-        n == 0 ? hipSuccess
-               : launch_column(b->Q, f64, b->collision == LBM_COLL_BGK, k & 1,
-                               column_shape(b->Q, b->column_nx, b->column.rows, nsub), b->d_descs,
-                               work, n, b->active[0]->klat, q->since[k], stream, ev);
+    const int n = b->ngroup[k], dn = q->since[k];
+    const bool ds = k & 1;
+    hipError_t e = hipSuccess;
+    if (nsub == 1 && n > 0 && column_single(b->Q, b->column, ds))
+      e = launch_column_single(b->Q, f64, bgk, ds, b->d_descs, single, b->nsingle[k], lat, dn,
+                               b->streaming[k], stream, ev);
+    else if (n > 0)
+      e = launch_column(b->Q, f64, bgk, ds,
+                        column_shape(b->Q, b->column_nx, b->column.rows, nsub), b->d_descs, work,
+                        n, lat, dn, stream, ev);
     if (e != hipSuccess) return e;
     q->since[k] += nsub;
     work += n;
+    single += b->nsingle[k];
   }
   return hipSuccess;
 }

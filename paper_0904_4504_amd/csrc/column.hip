@@ -151,6 +151,123 @@ __device__ __forceinline__ void expand(S a0, S bx, S by, S cxx, S cxy, S cyy, F&
       });
 }
 
+// A solve's constants of the update and of its moving wall.
+template <typename S>
+struct StepConst {
+  double rho0d, ladd_scale, sigma, ds0, ds1, inv_thd;
+  S rho0, th, inv_th, h2, om;
+  __device__ __forceinline__ StepConst(const SolveDesc& d, const KernelLattice& lat)
+      : rho0d(d.rho0),
+        ladd_scale(d.ladd_scale),
+        sigma(d.sigma),
+        ds0(d.ds[0]),
+        ds1(d.ds[1]),
+        inv_thd(1.0 / lat.theta),
+        rho0((S)d.rho0),
+        th((S)lat.theta),
+        inv_th((S)(1.0 / lat.theta)),
+        h2((S)(0.5 / (lat.theta * lat.theta))),
+        om((S)d.inv_tau) {}
+};
+
+// The arrivals of a row y < R from a diffuse or Maxwell wall: the emission
+// w (ea + eb (e1 vx + e2 vx^2)) of the cell's column (see ds_arrival; cm: the
+// deviation of the mass crossing the wall in it), mixed in FP64 with the
+// specular image that f holds, rounded once.
+template <class L, typename S>
+__device__ __forceinline__ void emission_arrivals(S (&f)[L::Q], const StepConst<S>& c,
+                                                  const KernelLattice& lat, int y, double U,
+                                                  double cm) {
+  const double emit = c.sigma / (c.ds0 + U * U * c.ds1);
+  const double e0 = 0.5 * U * U * c.inv_thd, e1 = U * c.inv_thd, e2 = e0 * c.inv_thd;
+  const double eb = (c.rho0d * c.ds0 + cm) * emit;
+  const double ea = (cm - c.rho0d * (U * U * c.ds1)) * emit - eb * e0;
+  // (a share of zero leaves the emission as it is)
+  const double ws = 1.0 - c.sigma;
+  static_for<0, L::Q>([&](auto qc) __attribute__((always_inline)) {
+    constexpr int q = decltype(qc)::value;
+    constexpr int vx = L::vx[q], vy = L::vy[q];
+    if constexpr (vy > 0) {
+      const double e = lat.w[L::orbit[q]] * (ea + eb * (vx * (e1 + vx * e2)));
+      f[q] = y < vy ? (S)__builtin_fma(ws, (double)f[q], e) : f[q];
+    }
+  });
+}
+
+// The collision of the pulled populations f; returns the density.
+template <class L, typename S, bool BGK>
+__device__ __forceinline__ S collide(S (&f)[L::Q], const StepConst<S>& c,
+                                     const KernelLattice& lat) {
+  S m[6];
+  moments_of<L>(f, m);
+  const S drho = m[0], jx = m[1], jy = m[2];
+  const S rho = c.rho0 + drho;
+  const S inv_rho = S(1) / rho;
+  const S uxx = jx * jx * inv_rho, uxy = jx * jy * inv_rho, uyy = jy * jy * inv_rho;
+  S bxx = uxx, bxy = uxy, byy = uyy;
+  if constexpr (!BGK) {
+    const S axx = m[3] - drho * c.th, ayy = m[5] - drho * c.th, axy = m[4];
+    bxx = axx - c.om * (axx - uxx);
+    bxy = axy - c.om * (axy - uxy);
+    byy = ayy - c.om * (ayy - uyy);
+  }
+  expand<L>(drho - (bxx + byy) * (S(0.5) * c.inv_th), jx * c.inv_th, jy * c.inv_th, bxx * c.h2,
+            bxy * (S(2) * c.h2), byy * c.h2, [&](auto qc, S p) __attribute__((always_inline)) {
+              constexpr int q = decltype(qc)::value;
+              const S g = (S)lat.w[L::orbit[q]] * p;
+              f[q] = BGK ? f[q] + c.om * (g - f[q]) : g;
+            });
+  return rho;
+}
+
+// Force of a step by one wavefront: the momentum exchange of the moving wall's
+// links (value(i): the crossing population of link i, vel(i, k): its reflected
+// velocity) in a fixed order, complete in lane 63; and its share of the lock-in
+// sums.
+struct WallForce {
+  double mwx, mwy, fs0, fs1, kl0, kl1;
+  WallEmission emission;
+  bool diffuse;
+  __device__ __forceinline__ WallForce(const SolveDesc& d, bool diffuse_wall)
+      : mwx(diffuse_wall ? d.sigma : 2.0),
+        mwy(diffuse_wall ? 2.0 - d.sigma : 2.0),
+        fs0(d.fstatic[0]),
+        fs1(d.fstatic[1]),
+        kl0(d.kladd[0]),
+        kl1(d.kladd[1]),
+        emission(wall_emission(d)),
+        diffuse(diffuse_wall) {}
+  template <class V, class W>
+  __device__ __forceinline__ void sum(int lane, int nlinks, V&& value, W&& vel, double& fx,
+                                      double& fy, double& fm) const {
+    fx = fy = fm = 0.0;
+    for (int i = lane; i < nlinks; i += 64) {
+      const double v = value(i);
+      fx -= mwx * vel(i, 0) * v;
+      fy -= mwy * vel(i, 1) * v;
+      fm += v;
+    }
+    fx = wave_sum_63(fx);
+    fy = wave_sum_63(fy);
+    if (diffuse) fm = wave_sum_63(fm);
+  }
+  // lane 63
+  __device__ __forceinline__ void finish(const Drive& dr, bool in_window, double& fx, double& fy,
+                                         double fm, double (&lk)[6]) const {
+    fx += fs0 + kl0 * dr.u;
+    fy += fs1 + kl1 * dr.u;
+    if (diffuse) add_emission_force(emission, dr.u, fm, &fx, &fy);
+    if (in_window) {
+      lk[0] += fx * dr.s;
+      lk[1] += fx * dr.c;
+      lk[2] += fx;
+      lk[3] += fy * dr.s;
+      lk[4] += fy * dr.c;
+      lk[5] += fy;
+    }
+  }
+};
+
 }  // namespace
 
 // LDS: the populations as Q planes of a compile-time size, column x of a plane
@@ -190,17 +307,10 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
   const bool mine = row < region && (yper || (y >= 0 && y < ny));
   // the descriptor's values, read once: the loop below touches LDS only, so
   // that its barriers wait for no global access
-  const double rho0d = d.rho0, ladd_scale = d.ladd_scale, sigma = d.sigma;
-  const double ds0 = d.ds[0], ds1 = d.ds[1];
-  const double fs0 = d.fstatic[0], fs1 = d.fstatic[1], kl0 = d.kladd[0], kl1 = d.kladd[1];
-  const int64_t win0 = d.lockin_first - n0, win1 = win0 + d.lockin_count;
+  const StepConst<S> c(d, lat);
   const bool far_eq = d.far == FAR_EQ, diffuse = DSW && d.wall == WALL_DS;
-  const WallEmission emission = wall_emission(d);
-  const S rho0 = (S)rho0d;
-  const double inv_thd = 1.0 / lat.theta;
-  const S th = (S)lat.theta, inv_th = (S)(1.0 / lat.theta);
-  const S h2 = (S)(0.5 / (lat.theta * lat.theta));
-  const S om = (S)d.inv_tau;
+  const WallForce wall(d, diffuse);
+  const int64_t win0 = d.lockin_first - n0, win1 = win0 + d.lockin_count;
 
   for (int i = tid; i < 3 * nsub; i += (int)blockDim.x)
     reinterpret_cast<double*>(drive)[i] = reinterpret_cast<const double*>(d.drive + n0)[i];
@@ -252,7 +362,7 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
         });
         cross[y * kColumnMaxNx + x] = cm;
       } else if (behind_low >= 0) {
-        const double ladd = ladd_scale * U;
+        const double ladd = c.ladd_scale * U;
         static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
           constexpr int q = decltype(qc)::value;  // the arrival
           constexpr int vx = L::vx[q], vy = L::vy[q], o = opposite<L>(q);
@@ -298,7 +408,6 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
     if (lane == 63)
       for (int k = 0; k < 6; ++k) lk[k] = d.state->lockin[k];
   }
-  const double mwx = diffuse ? sigma : 2.0, mwy = diffuse ? 2.0 - sigma : 2.0;
   bool bad = false;
   __syncthreads();
 
@@ -307,32 +416,14 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
     const int more = R * (nsub - 1 - s);
     const bool active = mine && y >= y0 - more && y < y1 + more;
     if (force) {
-      // momentum exchange of the wall's links in this step's input state
-      double fx = 0.0, fy = 0.0, fm = 0.0;
-      for (int i = lane; i < nlinks; i += 64) {
-        const double v = (double)pop[link_at[i]];
-        fx -= mwx * link_v[i][0] * v;
-        fy -= mwy * link_v[i][1] * v;
-        fm += v;
-      }
-      fx = wave_sum_63(fx);
-      fy = wave_sum_63(fy);
-      if (diffuse) fm = wave_sum_63(fm);
+      double fx, fy, fm;
+      wall.sum(
+          lane, nlinks, [&](int i) { return (double)pop[link_at[i]]; },
+          [&](int i, int k) { return link_v[i][k]; }, fx, fy, fm);
       if (lane == 63) {
-        const Drive dr = drive[s];
-        fx += fs0 + kl0 * dr.u;
-        fy += fs1 + kl1 * dr.u;
-        if (diffuse) add_emission_force(emission, dr.u, fm, &fx, &fy);
+        wall.finish(drive[s], s >= win0 && s < win1, fx, fy, fm, lk);
         hist[2 * s] = fx;
         hist[2 * s + 1] = fy;
-        if (s >= win0 && s < win1) {
-          lk[0] += fx * dr.s;
-          lk[1] += fx * dr.c;
-          lk[2] += fx;
-          lk[3] += fy * dr.s;
-          lk[4] += fy * dr.c;
-          lk[5] += fy;
-        }
       }
     }
     if (__any(active)) {
@@ -341,48 +432,13 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
         f[q] = pop[base[R + L::vx[q]] + (q * cap - L::vy[q])];
       });
       if (DSW && diffuse && low) {
-        // the emission w (ea + eb (e1 vx + e2 vx^2)) of the cell's column (see
-        // ds_arrival), mixed in FP64 with the specular image pulled from behind
-        // the wall, rounded once
-        const double U = drive[s].u;
         double cm = 0.0;
 #pragma unroll
         for (int r = 0; r < R; ++r) cm += cross[r * kColumnMaxNx + x];
-        const double emit = sigma / (ds0 + U * U * ds1);
-        const double e0 = 0.5 * U * U * inv_thd, e1 = U * inv_thd, e2 = e0 * inv_thd;
-        const double eb = (rho0d * ds0 + cm) * emit;
-        const double ea = (cm - rho0d * (U * U * ds1)) * emit - eb * e0;
-        // (a share of zero leaves the emission as it is)
-        const double ws = 1.0 - sigma;
-        static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
-          constexpr int q = decltype(qc)::value;
-          constexpr int vx = L::vx[q], vy = L::vy[q];
-          if constexpr (vy > 0) {
-            const double e = lat.w[L::orbit[q]] * (ea + eb * (vx * (e1 + vx * e2)));
-            f[q] = y < vy ? (S)__builtin_fma(ws, (double)f[q], e) : f[q];
-          }
-        });
+        emission_arrivals<L>(f, c, lat, y, drive[s].u, cm);
       }
-      S m[6];
-      moments_of<L>(f, m);
-      const S drho = m[0], jx = m[1], jy = m[2];
-      const S rho = rho0 + drho;
+      const S rho = collide<L, S, BGK>(f, c, lat);
       bad |= active && !(rho > S(0) && rho < S(INFINITY));
-      const S inv_rho = S(1) / rho;
-      const S uxx = jx * jx * inv_rho, uxy = jx * jy * inv_rho, uyy = jy * jy * inv_rho;
-      S bxx = uxx, bxy = uxy, byy = uyy;
-      if constexpr (!BGK) {
-        const S axx = m[3] - drho * th, ayy = m[5] - drho * th, axy = m[4];
-        bxx = axx - om * (axx - uxx);
-        bxy = axy - om * (axy - uxy);
-        byy = ayy - om * (ayy - uyy);
-      }
-      expand<L>(drho - (bxx + byy) * (S(0.5) * inv_th), jx * inv_th, jy * inv_th, bxx * h2,
-                bxy * (S(2) * h2), byy * h2, [&](auto qc, S p) __attribute__((always_inline)) {
-                  constexpr int q = decltype(qc)::value;
-                  const S g = (S)lat.w[L::orbit[q]] * p;
-                  f[q] = BGK ? f[q] + om * (g - f[q]) : g;
-                });
     }
     if (s + 1 < nsub) {
       __syncthreads();
@@ -407,6 +463,148 @@ __global__ __launch_bounds__(kColumnThreads) void column_kernel(
       for (int k = 0; k < 6; ++k) d.state->lockin[k] = lk[k];
   }
   if (bad) d.state->unstable = 1;
+}
+
+// One step of the same lattices, straight from and to the state buffers: the
+// same arithmetic on the same values as a step of column_kernel, so the same
+// bits, and the choice is free per launch.  One thread per cell of 256
+// consecutive ones, and a workgroup for the force (kForceTile).  For calls of
+// one step and the odd steps of others where a launch of column_kernel takes
+// many rounds of workgroups (column_single): its LDS leaves one or two
+// workgroups per compute unit, and loading, update and storing of a workgroup
+// follow one another.  Bound by memory: 31 plates of 16 x 2048 D2Q37, us per step,
+// FP32 69 (column_kernel 77 at 3 steps per launch, 93 at one), FP64 122 (121, 163):
+// 4.4 and 4.9 TB/s.
+template <class L, typename S, bool BGK, bool DSW>
+__global__ __launch_bounds__(kBlock) void column_single_kernel(
+    const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ work, KernelLattice lat,
+    int dn, int streaming) {
+  constexpr int Q = L::Q, R = L::R;
+  // a launch over one solve needs no work list
+  const WorkItem wi =
+      work ? work[blockIdx.x]
+           : WorkItem{0, blockIdx.x ? (int32_t)blockIdx.x - 1 : kForceTile};
+  const SolveDesc& d = descs[wi.solve];
+  const int64_t n = d.state->step + dn;
+  const S* __restrict__ fin = static_cast<const S*>(d.buf[n & 1]);
+  S* __restrict__ fout = static_cast<S*>(d.buf[(n & 1) ^ 1]);
+  const int nx = d.nx, ny = d.ny, tid = (int)threadIdx.x;
+  const int64_t qs = d.qs;
+  const bool yper = d.geom == GEOM_PERIODIC;
+  const bool far_eq = d.far == FAR_EQ, diffuse = DSW && d.wall == WALL_DS;
+  if (wi.tile == kForceTile) {
+    if (tid >= 64) return;
+    const WallForce wall(d, diffuse);
+    double lk[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    Drive dr{};
+    if (tid == 63) {
+      dr = d.drive[n];
+      for (int k = 0; k < 6; ++k) lk[k] = d.state->lockin[k];
+    }
+    double fx, fy, fm;
+    wall.sum(
+        tid, yper ? 0 : CrossTable<L>::N * nx,
+        [&](int i) {
+          const int k = i / nx;
+          return (double)fin[kCross<L>.q[k] * qs + kCross<L>.r[k] * nx + (i - k * nx)];
+        },
+        [&](int i, int k) { return k ? kCross<L>.vy[i / nx] : kCross<L>.vx[i / nx]; }, fx, fy, fm);
+    if (tid == 63) {
+      wall.finish(dr, n >= d.lockin_first && n < d.lockin_first + d.lockin_count, fx, fy, fm, lk);
+      const int64_t h = n % d.hist_cap;
+      d.hist[2 * h] = fx;
+      d.hist[2 * h + 1] = fy;
+      for (int k = 0; k < 6; ++k) d.state->lockin[k] = lk[k];
+    }
+    return;
+  }
+  const StepConst<S> c(d, lat);
+  const int at = wi.tile * kBlock + tid, cy = at / nx;
+  const bool active = cy < ny;
+  if (!__any(active)) return;
+  // (lanes past the last cell read as cell 0 does, inside the buffer: rows before
+  // a plane are the plane before's)
+  const int y = active ? cy : 0, x = active ? at - cy * nx : 0;
+  // the columns x - vx and the rows y - vy (those behind a wall are not read)
+  int col[2 * R + 1], row[2 * R + 1];
+#pragma unroll
+  for (int k = 0; k <= 2 * R; ++k) {
+    int sx = x - (k - R), sy = y - (k - R);
+    sx += sx < 0 ? nx : 0;
+    sx -= sx >= nx ? nx : 0;
+    if (yper) {
+      sy += sy < 0 ? ny : 0;
+      sy -= sy >= ny ? ny : 0;
+    }
+    col[k] = sx;
+    row[k] = sy * nx;
+  }
+  const bool low = active && !yper && y < R, high = active && !yper && y >= ny - R;
+  S f[Q];
+  if (!__any(low || high)) {
+    static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
+      constexpr int q = decltype(qc)::value;
+      f[q] = fin[q * qs + (row[R + L::vy[q]] + col[R + L::vx[q]])];
+    });
+  } else {
+    const double U = d.drive[n].u, ladd = c.ladd_scale * U;
+    static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
+      constexpr int q = decltype(qc)::value;
+      constexpr int vx = L::vx[q], vy = L::vy[q], o = opposite<L>(q);
+      int64_t src = q * qs + (row[R + vy] + col[R + vx]);
+      bool moving = false, zero = false;
+      if constexpr (vy > 0) {
+        // from the moving wall: the reflection (bounce-back with the moving-wall
+        // term, or the specular image)
+        moving = low && y < vy;
+        const int at_wall = (vy - 1 - y) * nx;
+        if (diffuse)
+          src = moving ? reflect_y<L>(q) * qs + (at_wall + col[R + vx]) : src;
+        else
+          src = moving ? o * qs + (at_wall + x) : src;
+      }
+      if constexpr (vy < 0) {
+        // from the stationary far wall, or the rest-equilibrium far field
+        const bool far = high && ny - 1 - y < -vy;
+        src = far ? o * qs + ((2 * ny - 1 - (y - vy)) * nx + x) : src;
+        zero = far && far_eq;
+      }
+      f[q] = fin[src];
+      if constexpr (vy > 0)
+        if (moving && !diffuse) f[q] = f[q] + (S)(lat.w[L::orbit[q]] * vx * ladd);
+      if constexpr (vy < 0) f[q] = zero ? S(0) : f[q];
+    });
+    if (DSW && diffuse && low) {
+      double cm = 0.0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        double cr = 0.0;
+        static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
+          constexpr int q = decltype(qc)::value;
+          if constexpr (L::vy[q] < 0)
+            if (r < -L::vy[q]) cr += (double)fin[q * qs + (r * nx + x)];
+        });
+        cm += cr;
+      }
+      emission_arrivals<L>(f, c, lat, y, U, cm);
+    }
+  }
+  const S rho = collide<L, S, BGK>(f, c, lat);
+  if (!active) return;
+  if (!(rho > S(0) && rho < S(INFINITY))) d.state->unstable = 1;
+  S* const dst = fout + at;
+  if (streaming)
+    static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
+      constexpr int q = decltype(qc)::value;
+      __builtin_nontemporal_store(f[q], &dst[q * qs]);
+    });
+  else
+    static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
+      constexpr int q = decltype(qc)::value;
+      // (empty, but keeps the compiler from merging the two forms)
+      asm volatile("" ::: "memory");
+      dst[q * qs] = f[q];
+    });
 }
 
 // Advance the step counters of solves stepped by column_kernel.
@@ -449,6 +647,37 @@ hipError_t launch_column(int Q, bool f64, bool bgk, bool ds, const ColumnShape& 
                : launch_column_l<D2Q9, float>(bgk, ds, sh, descs, work, nwork, lat, dn, stream, ev);
   return f64 ? launch_column_l<D2Q37, double>(bgk, ds, sh, descs, work, nwork, lat, dn, stream, ev)
              : launch_column_l<D2Q37, float>(bgk, ds, sh, descs, work, nwork, lat, dn, stream, ev);
+}
+
+template <class L, typename S>
+static hipError_t launch_single_l(bool bgk, bool ds, const SolveDesc* descs, const WorkItem* work,
+                                  int nwork, const KernelLattice& lat, int dn, bool streaming,
+                                  hipStream_t stream, const KernelEvents& ev) {
+  auto go = [&](auto kernel) {
+    launch_kernel(kernel, dim3(nwork), dim3(kBlock), stream, ev, descs, work, lat, dn,
+                  (int)streaming);
+    return hipGetLastError();
+  };
+  if (bgk)
+    return ds ? go(column_single_kernel<L, S, true, true>)
+              : go(column_single_kernel<L, S, true, false>);
+  return ds ? go(column_single_kernel<L, S, false, true>)
+            : go(column_single_kernel<L, S, false, false>);
+}
+
+hipError_t launch_column_single(int Q, bool f64, bool bgk, bool ds, const SolveDesc* descs,
+                                const WorkItem* work, int nwork, const KernelLattice& lat, int dn,
+                                bool streaming, hipStream_t stream, KernelEvents ev) {
+  if (nwork <= 0) return hipSuccess;
+  if (Q == 9)
+    return f64 ? launch_single_l<D2Q9, double>(bgk, ds, descs, work, nwork, lat, dn, streaming,
+                                               stream, ev)
+               : launch_single_l<D2Q9, float>(bgk, ds, descs, work, nwork, lat, dn, streaming,
+                                              stream, ev);
+  return f64 ? launch_single_l<D2Q37, double>(bgk, ds, descs, work, nwork, lat, dn, streaming,
+                                              stream, ev)
+             : launch_single_l<D2Q37, float>(bgk, ds, descs, work, nwork, lat, dn, streaming,
+                                             stream, ev);
 }
 
 hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int count, int nsteps,

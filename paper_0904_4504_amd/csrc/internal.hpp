@@ -29,6 +29,12 @@ hipError_t launch_column(int Q, bool f64, bool bgk, bool ds, const ColumnShape& 
                          const SolveDesc* descs, const WorkItem* work, int nwork,
                          const KernelLattice& lat, int dn, hipStream_t stream,
                          KernelEvents ev = {});
+// One step of narrow lattices.
+// work: (solve, tile of kBlock cells or kForceTile) items, or null for solve 0
+// (nwork: its tiles and one).
+hipError_t launch_column_single(int Q, bool f64, bool bgk, bool ds, const SolveDesc* descs,
+                                const WorkItem* work, int nwork, const KernelLattice& lat, int dn,
+                                bool streaming, hipStream_t stream, KernelEvents ev = {});
 // Advance the step counters of the listed solves.
 hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int count, int nsteps,
                           hipStream_t stream);
@@ -130,7 +136,14 @@ constexpr int kStepBlock = 1024;
 // launch, for lattices of ny rows each and at most nx columns.
 struct ColumnPlan {
   int rows = 0, max_sub = 1;
+  int64_t groups = 0;  // workgroups
 };
+// Whether launches of one step go to column_single_kernel.
+bool column_single(int Q, const ColumnPlan& plan, bool ds);
+// Work items of a narrow lattice in a single-step launch: the force and the tiles.
+inline int column_single_items(int nx, int ny) {
+  return 1 + (int)(((int64_t)nx * ny + kBlock - 1) / kBlock);
+}
 ColumnPlan column_plan(int Q, bool f64, int nx, const std::vector<int>& ny);
 ColumnShape column_shape(int Q, int nx, int rows, int nsub);
 // n as a sum of odd numbers of at most max_sub (odd): the steps per launch of

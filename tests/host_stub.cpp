@@ -131,6 +131,11 @@ hipError_t launch_column(int, bool, bool, bool, const ColumnShape& sh, const Sol
                          KernelEvents ev) {
   return run("column", descs, work, nwork, dn, sh.nsub, ev);
 }
+hipError_t launch_column_single(int, bool, bool, bool, const SolveDesc* descs, const WorkItem* work,
+                                int nwork, const KernelLattice&, int dn, bool, hipStream_t,
+                                KernelEvents ev) {
+  return run("single", descs, work, nwork, dn, 1, ev);
+}
 hipError_t launch_advance(const SolveDesc* descs, const int32_t* solves, int count, int nsteps,
                           hipStream_t) {
   if (count <= 0 || nsteps <= 0) return hipSuccess;

@@ -122,6 +122,57 @@ def test_batch_of_long_plates(P, nx, lengths):  # noqa: F811
         m.close()
 
 
+@pytest.mark.parametrize("geom,far,wall,sigma,coll", [
+    (W.PLATE, W.FAR_WALL, "bb", 1.0, "regularized"),
+    (W.PLATE, W.FAR_EQ, "bb", 1.0, "bgk"),
+    (W.PLATE, W.FAR_EQ, "maxwell", 0.35, "regularized"),
+    (W.PLATE, W.FAR_WALL, "ds", 1.0, "bgk"),
+    (W.PERIODIC, W.FAR_EQ, "bb", 1.0, "regularized"),
+    (W.PERIODIC, W.FAR_EQ, "bb", 1.0, "bgk"),
+])
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("Q,nx,lengths", [(37, 16, [3301, 3300, 3, 3299, 3310, 3400]),
+                                          (37, 3, [77000] * 3),
+                                          (9, 16, [7300] * 8 + [4])])
+def test_single_steps(P, Q, nx, lengths, storage, geom, far, wall, sigma, coll):  # noqa: F811
+    """Batches so long that calls of one step go straight through memory: the
+    fields, forces and lock-in sums of each lattice alone in one call (several
+    steps per launch in LDS), bit for bit."""
+    import torch
+    n = 5
+    print(f"case {nx} Q{Q} {storage} {geom} {far} {wall} {coll}", flush=True)
+    v, w, th = P.lattice(Q)
+    rng = np.random.default_rng(21)
+    kinds = [rng.standard_normal((Q, 1, nx)) * 1e-3 * np.asarray(w)[:, None, None]
+             for _ in range(2)]
+    solves, fields, alone = [], [], []
+    for i, ny in enumerate(lengths):
+        s = W.Solve(Q=Q, geometry=geom, far=far, nx=nx, ny=ny, tau=0.9, omega=2 * math.pi / 40,
+                    nsteps=n, window_first=1, window_count=n - 1, storage=storage,
+                    collision=coll, wall=wall, accommodation=sigma)
+        # different in every row
+        f = kinds[i % 2] * np.cos(0.37 * np.arange(ny) + i)[None, :, None]
+        with P.Solver(P.params_from_solve(s)) as sv:
+            sv.set_deviations(f)
+            sv.step(n)
+            alone.append((*sv.force_history(), sv.lockin()[0], sv.get_deviations()))
+        solves.append(s)
+        fields.append(f)
+    stream = torch.cuda.Stream()
+    members = [P.Solver(P.params_from_solve(s), stream=stream) for s in solves]
+    with P.Batch(stream) as batch:
+        for m, f in zip(members, fields):
+            batch.add(m)
+            m.set_deviations(f)
+        for k in (1, 2, 1, 1):
+            batch.step(k)
+        for m, a in zip(members, alone):
+            got = (*m.force_history(), m.lockin()[0], m.get_deviations())
+            assert all(np.array_equal(x, y) for x, y in zip(got, a))
+    for m in members:
+        m.close()
+
+
 @pytest.mark.parametrize("nx,ny", [(16, 6250), (16, 6251), (14, 7142), (14, 7143), (13, 7700)])
 def test_wide_line(P, nx, ny):  # noqa: F811
     """Lengths on both sides of the line where D2Q37 lattices of 14 to 16 columns
