@@ -22,7 +22,10 @@ constexpr int kPop = 0, kTiles = 2, kColumns = 4, kGroups = 6;
 // call about 25 us of waiting (a 512 x 512 box with four 4 x 2048 plates, us per
 // call, beside / one after the other: 1 step 43 / 19, 2 42 / 35, 3 57 / 41,
 // 4 53 / 57, 8 94 / 97; 1024 x 1024 with eight plates: 3 65 / 66, 4 82 / 89).
-constexpr int kBesideSteps = 4;
+// Beside members of fewer cells than kBesideCells there is less to gain (a
+// 20 x 300 plate with four of 4 x 2048, D2Q9 FP32: 5 steps 51 / 29, 8 68 / 46).
+constexpr int kBesideSteps = 4, kBesideStepsSmall = 12;
+constexpr int64_t kBesideCells = 200000;
 }  // namespace
 
 struct lbm_batch {
@@ -48,6 +51,7 @@ struct lbm_batch {
   ColumnPlan column;      // of the column-kernel members
   int column_nx = 0;      // their widest lattice
   int ncolumn = 0;        // how many
+  int64_t tile_cells = 0; // cells of the others
   // where other members step too, the column launches go on a stream of their
   // own between these events on the batch's stream
   hipStream_t side = nullptr;
@@ -128,10 +132,13 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
   std::vector<int32_t> solves;
   std::vector<int> column_ny;
   b->column_nx = 0;
+  b->tile_cells = 0;
   for (lbm_solver* s : act)
     if (s->lay.column) {
       b->column_nx = std::max(b->column_nx, s->p.nx);
       column_ny.push_back(s->p.ny);
+    } else {
+      b->tile_cells += (int64_t)s->p.nx * s->p.ny;
     }
   if (b->column_nx)
     b->column = column_plan(b->Q, b->storage == LBM_STORE_F64, b->column_nx, column_ny);
@@ -407,7 +414,7 @@ int step_chunk(lbm_batch* b, int64_t chunk, Enqueued* q) {
   // other 35.1)
   const bool tiles = (int)b->active.size() > b->ncolumn;
   const bool beside = tiles && b->ncolumn && b->join;
-  if (beside && chunk < kBesideSteps) {
+  if (beside && chunk < (b->tile_cells < kBesideCells ? kBesideStepsSmall : kBesideSteps)) {
     for (int nsub : odd_pieces(chunk, b->column.max_sub))
       if (!rc && launch_columns(b, nsub, q, b->stream, KernelEvents{}) != hipSuccess)
         rc = LBM_EHIP;

@@ -290,6 +290,28 @@ static void check_single() {
   for (lbm_solver* s : ms) lbm_destroy(s);
 }
 
+// Column launches go beside those of other members from 4 steps, beside small
+// members from 12.
+static void check_beside() {
+  for (int n : {200, 500}) {
+    std::vector<lbm_solver*> ms = {solver(params(LBM_GEOM_PLATE, 4, 100, LBM_WALL_BB, 99)),
+                                   solver(params(LBM_GEOM_BOX, n, n, LBM_WALL_BB, 99))};
+    lbm_batch* b = nullptr;
+    CHECK(lbm_batch_create(nullptr, &b) == LBM_OK);
+    for (lbm_solver* s : ms) CHECK(lbm_batch_add(b, s) == LBM_OK);
+    CHECK(lbm_batch_step(b, 1) == LBM_OK);
+    for (int k : {2, 3, 4, 11, 12, 20}) {
+      g_log.clear();
+      CHECK(lbm_batch_step(b, k) == LBM_OK);
+      const bool beside = std::count(g_log.begin(), g_log.end(), "wait") > 0;
+      CHECK(beside == (k >= (n < 400 ? 12 : 4)));
+    }
+    lbm_batch_destroy(b);
+    for (lbm_solver* s : ms) lbm_destroy(s);
+    g_done.clear();
+  }
+}
+
 // Read-outs share pinned buffers, freed with the last solver.
 static void check_pinned() {
   for (int round = 0; round < 2; ++round) {
@@ -369,6 +391,7 @@ int main(int argc, char** argv) {
                                                              {"launch", check_launch},
                                                              {"tile", check_tile},
                                                              {"single", check_single},
+                                                             {"beside", check_beside},
                                                              {"pinned", check_pinned},
                                                              {"tables", check_tables},
                                                              {"timing", check_timing},

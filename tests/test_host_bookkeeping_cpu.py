@@ -25,8 +25,8 @@ def stub(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["refresh", "launch", "tile", "single", "pinned", "tables",
-                                   "timing", "steps"])
+@pytest.mark.parametrize("check", ["refresh", "launch", "tile", "single", "beside", "pinned",
+                                   "tables", "timing", "steps"])
 def test_host(stub, check):
     r = subprocess.run([stub, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
