@@ -51,12 +51,18 @@ void order_tiles(std::vector<WorkItem>* out, int32_t solve, int32_t ntiles, int3
 // 3000 x 3000 133, 102, 91, 4096 x 4096 254, 180, 158; FP64 1800 x 1800 94, 80, 86,
 // 3000 x 3000 243, 205, 230, 4096 x 4096 439, 362, 398 (the larger halo of K = 2
 // costs less than the third workgroup brings).  The lines are D2Q37's; D2Q9 differs
-// by less than 4 % but for FP32 near 640 x 640 (7.9, 7.1, 7.3).  A cell's bits do
-// not depend on K.
+// by less than 4 % but for FP32 near 640 x 640 (7.9, 7.1, 7.3).  The cells are those
+// of whole tile columns (coef_cells), since a wavefront with idle lanes takes as
+// long as a full one: D2Q37 FP32 12 x 39318 42.4, 32.2, 27.4, 20 x 12000 16.6, 13.9,
+// 11.9, 70 x 9000 21.3, 17.5, 16.8.  A cell's bits do not depend on K.
 int coef_k_for(uint32_t tile, bool f64, int64_t cells) {
   if (tile) return (int)tile;
   if (f64) return cells <= 400000 ? 1 : 2;
   return cells <= 420000 ? 1 : cells <= 650000 ? 2 : kCoefKDefault;
+}
+
+int64_t coef_cells(const lbm_params* p) {
+  return (int64_t)(p->nx + kCoefTileW - 1) / kCoefTileW * kCoefTileW * p->ny;
 }
 
 CoefGrid coef_grid(const lbm_params* p, int K) {
@@ -706,7 +712,7 @@ void make_layout(const lbm_params* p, const HostLattice& L, Layout* lay, ForceTa
   lay->loadable = !(lay->mom && p->representation == LBM_REPR_COEFFICIENTS_NOLOAD);
   if (lay->mom) {
     lay->coef_k = p->tile ? (int32_t)p->tile : kCoefKDefault;
-    lay->launch_k = coef_k_for(p->tile, es == 8, (int64_t)p->nx * p->ny);
+    lay->launch_k = coef_k_for(p->tile, es == 8, coef_cells(p));
     // element (k, y, x) of a buffer at k*mks + y*mpitch + x.  Row-interleaved
     // where the whole buffer stays addressable with 32-bit byte offsets: the
     // six coefficient rows of lattice row y side by side, so the staged rows

@@ -144,16 +144,16 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
     b->column = column_plan(b->Q, b->storage == LBM_STORE_F64, b->column_nx, column_ny);
   uint64_t state[kGroups] = {};  // state bytes per group
   uint32_t tile = 0;  // as a member asks (0: none does)
-  int64_t coef_cells = 0;
+  int64_t cells = 0;
   for (const lbm_solver* s : act)
     if (!s->lay.mom) {
       state[kind(s)] += 2 * s->lay.buf_bytes;
     } else {
       state[kind(s)] += 2 * s->lay.mbuf_bytes;
       tile = std::max(tile, s->p.tile);
-      coef_cells += (int64_t)s->p.nx * s->p.ny;
+      cells += coef_cells(&s->p);
     }
-  b->launch_k = coef_cells ? coef_k_for(tile, b->storage == LBM_STORE_F64, coef_cells) : 0;
+  b->launch_k = cells ? coef_k_for(tile, b->storage == LBM_STORE_F64, cells) : 0;
   for (size_t i = 0; i < act.size(); ++i) {
     descs.push_back(act[i]->desc);
     const Layout& lay = act[i]->lay;

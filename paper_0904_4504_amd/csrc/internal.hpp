@@ -103,9 +103,11 @@ void order_tiles(std::vector<WorkItem>* out, int32_t solve, int32_t ntiles, int3
 // the same length as order_tiles.
 void order_tiles_banded(std::vector<WorkItem>* out, int32_t solve, int32_t ntiles,
                         int32_t span);
-// Cells per thread of the coefficient kernel for a launch over `cells` cells:
-// the tile asked for, or (0) by the launch's size.
+// Cells per thread of the coefficient kernel for a launch over `cells` cells
+// (coef_cells of each lattice): the tile asked for, or (0) by the launch's size.
 int coef_k_for(uint32_t tile, bool f64, int64_t cells);
+// The cells of a lattice, its width rounded up to whole tiles.
+int64_t coef_cells(const lbm_params* p);
 // Tiles of a solve for K cells per thread, and the mask of those with a wall link.
 struct CoefGrid {
   int32_t tiles_x = 0, ntiles = 0;

@@ -256,8 +256,25 @@ static void check_launch() {
   lbm_destroy(s);
 }
 
-// A tile that a member asks for is the tile of the batch's launch.
+// A tile that a member asks for is the tile of the batch's launch; with none
+// asked for the launch's wavefronts count, full or not.
 static void check_tile() {
+  for (int nx : {20, 64, 65}) {
+    lbm_params p = params(LBM_GEOM_PLATE, nx, 12000, LBM_WALL_BB, 9);
+    p.ny = nx == 65 ? 6000 : 12000;
+    p.representation = LBM_REPR_COEFFICIENTS_NOLOAD;
+    lbm_solver *a = solver(p), *c = solver(params(LBM_GEOM_BOX, 80, 70, LBM_WALL_BB, 9));
+    CHECK(lbm_step(a, 1) == LBM_OK && g_coef_k == 3);
+    CHECK(lbm_step(c, 1) == LBM_OK && g_coef_k == 1);
+    lbm_batch* b = nullptr;
+    CHECK(lbm_batch_create(nullptr, &b) == LBM_OK);
+    CHECK(lbm_batch_add(b, a) == LBM_OK && lbm_batch_add(b, c) == LBM_OK);
+    CHECK(lbm_batch_step(b, 1) == LBM_OK && g_coef_k == 3);
+    lbm_batch_destroy(b);
+    lbm_destroy(a);
+    lbm_destroy(c);
+    g_done.clear();
+  }
   for (int order = 0; order < 2; ++order) {
     lbm_params p = params(LBM_GEOM_BOX, 80, 70, LBM_WALL_BB, 9), q = p;
     p.tile = order ? 3 : 0;
