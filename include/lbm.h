@@ -211,9 +211,10 @@ int lbm_create_static(const lbm_params* p, void* hip_stream, lbm_solver** out);
 /* Enqueue nsteps steps on the solver's stream and return without waiting.
  * Calls of 32 steps or more replay a HIP graph of 32 steps that the first
  * such call captures on the stream; populations of at most 16 columns (plates
- * and periodic lattices) take several steps per launch instead.  On the null stream, or if that first
- * call finds the stream already being captured by the caller, the solver
- * launches step by step from then on (into the caller's capture, if any).
+ * and periodic lattices) take several steps per launch instead.  On the null
+ * stream, or if that first call finds the stream already being captured by the
+ * caller, the solver launches step by step from then on (into the caller's
+ * capture, if any).
  * Results are the same either way.
  * LBM_ERANGE if the run would pass max_steps (nothing is enqueued). */
 int lbm_step(lbm_solver* s, int64_t nsteps);
@@ -314,9 +315,10 @@ int lbm_batch_create(void* hip_stream, lbm_batch** out);
  * lattice, storage or collision differs from the batch, if two members kept
  * in the same representation differ in `tile` (0 and the default tile -- 1 for
  * populations, 3 for coefficients -- go together; the launch takes the tile that
- * a member asks for), or on a double add / a remove of a non-member.  A member joins at its own current step.  The kinds of member
- * -- kept as populations or as coefficients, with a bounce-back or a diffuse
- * (or Maxwell) moving wall -- are advanced by one launch each per step. */
+ * a member asks for), or on a double add / a remove of a non-member.  A member
+ * joins at its own current step.  The kinds of member -- kept as populations or
+ * as coefficients, with a bounce-back or a diffuse (or Maxwell) moving wall --
+ * are advanced by one launch each per step. */
 int lbm_batch_add(lbm_batch* b, lbm_solver* s);
 int lbm_batch_remove(lbm_batch* b, lbm_solver* s);
 

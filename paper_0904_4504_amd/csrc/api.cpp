@@ -221,13 +221,17 @@ ColumnPlan column_plan(int Q, bool f64, int nx, const std::vector<int>& ny) {
 }
 
 // A launch of one step: column_kernel where a few rounds of workgroups do,
-// column_single_kernel above (D2Q37 bounce-back, us per call of one step,
-// column / single: FP32 8 x 8192 (216 workgroups) 9 / 10, 16 x 6000 (600) 17 / 13, six of
-// 16 x 4096 (2460) 61 / 28, 61 of 8 x 2048 (3294) 96 / 77; FP64 4 x 16384 (256) 12 / 19,
-// 61 of 8 x 2048 172 / 134; D2Q9 FP32 8 x 65536 15 / 12).  With a diffuse wall the single
-// kernel's wall cells are a chain of 15 us more (16 x 6000 16 / 24).
-bool column_single(int Q, const ColumnPlan& plan, bool ds) {
-  return plan.max_sub == 1 || plan.groups > (Q == 9 ? 800 : 400) * (ds ? 4 : 1);
+// column_single_kernel above (us per call of one step, column / single).  D2Q37
+// bounce-back: FP32 4 x 10448 (255 workgroups) 7.8 / 9.2, 8 x 13217 (509) 14 / 13,
+// 16 x 6000 (750) 17 / 11, 61 of 8 x 2048 (3294) 96 / 72; FP64 8 x 4000 (250) 9.9 / 11,
+// 61 of 8 x 2048 172 / 128.  With a diffuse wall the single kernel's wall cells are
+// a chain of 15 us more: FP32 two of 12 x 8000 (1000) 24 / 29, 8 x 40000 (1177)
+// 29 / 29; FP64, one workgroup per compute unit, 16 x 6000 (750) 23 / 29, two of
+// 12 x 8000 38 / 33, 8 x 40000 46 / 34.  D2Q9 has no such chain: 4 x 2048 6.0 / 5.6,
+// six of 16 x 4096 16 / 10, FP64 20 / 14.
+bool column_single(int Q, bool f64, const ColumnPlan& plan, bool ds) {
+  if (Q == 9 || plan.max_sub == 1) return true;
+  return plan.groups > (!ds ? 400 : f64 ? 900 : 1600);
 }
 
 std::vector<int> odd_pieces(int64_t n, int max_sub) {
@@ -1060,7 +1064,7 @@ int launch_steps(lbm_solver* s, int64_t n, int64_t* done) {
       for (int nsub : odd_pieces(block, s->column.max_sub)) {
         const bool bgk = s->p.collision == LBM_COLL_BGK, ds = s->p.wall != LBM_WALL_BB;
         const hipError_t e =
-            nsub == 1 && column_single(Q, s->column, ds)
+            nsub == 1 && column_single(Q, f64, s->column, ds)
                 ? launch_column_single(Q, f64, bgk, ds, s->d_desc, nullptr,
                                        column_single_items(s->p.nx, s->p.ny), s->klat, k,
                                        2 * s->lay.buf_bytes > kCachedPopBytes, s->stream)

@@ -188,7 +188,8 @@ int refresh(lbm_batch* b, const std::vector<lbm_solver*>& act) {
       group[k].swap(front[k]);
     }
     b->ngroup[k] = (int)group[k].size();
-    b->streaming[k] = state[k] > (k < kTiles || k >= kColumns ? kCachedPopBytes : kCachedStateBytes);
+    b->streaming[k] =
+        state[k] > (k < kTiles || k >= kColumns ? kCachedPopBytes : kCachedStateBytes);
     work.insert(work.end(), group[k].begin(), group[k].end());
   }
   for (int k = kColumns; k < kGroups; ++k)
@@ -273,7 +274,7 @@ hipError_t launch_columns(lbm_batch* b, int nsub, Enqueued* q, hipStream_t strea
     const int n = b->ngroup[k], dn = q->since[k];
     const bool ds = k & 1;
     hipError_t e = hipSuccess;
-    if (nsub == 1 && n > 0 && column_single(b->Q, b->column, ds))
+    if (nsub == 1 && n > 0 && column_single(b->Q, f64, b->column, ds))
       e = launch_column_single(b->Q, f64, bgk, ds, b->d_descs, single, b->nsingle[k], lat, dn,
                                b->streaming[k], stream, ev);
     else if (n > 0)

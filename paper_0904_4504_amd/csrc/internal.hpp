@@ -141,7 +141,7 @@ struct ColumnPlan {
   int64_t groups = 0;  // workgroups
 };
 // Whether launches of one step go to column_single_kernel.
-bool column_single(int Q, const ColumnPlan& plan, bool ds);
+bool column_single(int Q, bool f64, const ColumnPlan& plan, bool ds);
 // Work items of a narrow lattice in a single-step launch: the force and the tiles.
 inline int column_single_items(int nx, int ny) {
   return 1 + (int)(((int64_t)nx * ny + kBlock - 1) / kBlock);

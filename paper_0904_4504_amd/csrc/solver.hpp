@@ -24,7 +24,8 @@ __host__ __device__ constexpr int coef_tile_rows(int K) { return kCoefWaves * K;
 
 // Column kernel (several steps per launch of lattices of a few columns).
 constexpr int kColumnMaxNx = 16;    // widest lattice it takes
-constexpr int kColumnThreads = 512; // most threads of a workgroup (7 waves of cells, 1 for the force)
+// Most threads of a workgroup (7 waves of cells, 1 for the force).
+constexpr int kColumnThreads = 512;
 constexpr int kColumnMaxSub = 27;   // most steps per launch (odd)
 constexpr int kColumnWideCells = 100000;  // most cells of a D2Q37 lattice of 14 to 16 columns
 // Cells of a workgroup, one thread each; its Q populations of them take 66
