@@ -340,7 +340,7 @@ int lbm_batch_set_graphs(lbm_batch* b, int steps_per_graph);
  * lbm_batch_kernel_time waits and returns the summed kernel time in ms and
  * the number of launches since timing was (re)enabled: one launch set per
  * step.  Members of at most 16 columns, which take several steps per launch
- * otherwise, are then stepped once per launch (five plates of 4 x 2048: 9.9 us
+ * otherwise, are then stepped once per launch (five plates of 4 x 2048: 9.2 us
  * per step timed so, 2.3 without timing), so the figure is an upper bound for
  * them. */
 int lbm_batch_timing(lbm_batch* b, int enable);

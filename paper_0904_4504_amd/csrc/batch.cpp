@@ -24,6 +24,10 @@ constexpr int kPop = 0, kTiles = 2, kColumns = 4, kGroups = 6;
 // 4 53 / 57, 8 94 / 97; 1024 x 1024 with eight plates: 3 65 / 66, 4 82 / 89).
 // Beside members of fewer cells than kBesideCells there is less to gain (a
 // 20 x 300 plate with four of 4 x 2048, D2Q9 FP32: 5 steps 51 / 29, 8 68 / 46).
+// The runtime deals a process's streams to its hardware queues (4 by default).  If
+// both streams fall to one queue, the launches take turns and the call lasts as
+// long as one after the other (two 1024 x 1024 boxes with eight plates, 256 steps: 8.8
+// ms instead of 7.4).
 constexpr int kBesideSteps = 4, kBesideStepsSmall = 12;
 constexpr int64_t kBesideCells = 200000;
 }  // namespace
